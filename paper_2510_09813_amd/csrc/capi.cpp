@@ -21,28 +21,27 @@ bool finite_all(const double* p, size_t n) {
   return true;
 }
 
-// Temporary device scratch from the context for one output call.
+// Temporary device scratch and pinned scalars (kPinnedDoubles) of the context for one output
+// call on stream s.
 struct Scratch {
   rsv_ctx* ctx;
+  hipStream_t s;
   void* p = nullptr;
   size_t bytes = 0;
   double* h = nullptr;
-  explicit Scratch(rsv_ctx* c) : ctx(c) {}
+  Scratch(rsv_ctx* c, hipStream_t st) : ctx(c), s(st) {}
   int get(size_t b) {
     bytes = b;
     RSV_TRY(ctx->dev->alloc(b, &p));
-    if (hipHostMalloc((void**)&h, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-      h = nullptr;
-      return fail(RSV_EDEVICE, "hipHostMalloc failed");
-    }
+    h = ctx->dev->pinned_take();
+    if (!h) return fail(RSV_EDEVICE, "hipHostMalloc failed");
     return RSV_OK;
   }
   ~Scratch() {
-    if (p) {
-      (void)hipDeviceSynchronize();
-      ctx->dev->release(p, bytes);
-    }
-    if (h) (void)hipHostFree(h);
+    if (!p) return;
+    const bool idle = hipStreamSynchronize(s) == hipSuccess;
+    ctx->dev->release(p, bytes, idle);
+    ctx->dev->pinned_give(h);
   }
 };
 
@@ -51,7 +50,7 @@ int occupations_impl(rsv_ctx* ctx, int n, int prec, const void* d_psi, double* o
   RSV_TRY(check_state_args(n, prec));
   if (!ctx || !d_psi || !out) return fail(RSV_EINVAL, "NULL argument");
   HIP_TRY(hipSetDevice(ctx->device));
-  Scratch sc(ctx);
+  Scratch sc(ctx, s);
   RSV_TRY(sc.get(occupation_scratch_bytes(n)));
   return occupations_with(n, prec, d_psi, sc.p, sc.h, out, s);
 }
@@ -63,7 +62,7 @@ int sample_impl(rsv_ctx* ctx, int n, int prec, const void* d_psi, uint64_t seed,
   if (shots < 0) return fail(RSV_EINVAL, "n_shots must be >= 0");
   if (shots == 0) return RSV_OK;
   HIP_TRY(hipSetDevice(ctx->device));
-  Scratch sc(ctx);
+  Scratch sc(ctx, s);
   RSV_TRY(sc.get(sample_scratch_bytes(n, shots)));
   return sample_with(n, prec, d_psi, seed, shots, sc.p, out, s);
 }
@@ -87,7 +86,9 @@ int rsv_ctx_create(int hip_device, size_t budget, rsv_ctx** out) {
   rsv_ctx* c = new (std::nothrow) rsv_ctx();
   if (!c) return fail(RSV_ENOMEM, "host allocation failed");
   c->device = hip_device;
-  c->dev = new (std::nothrow) DeviceAllocator(budget);
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) total_b = 0;
+  c->dev = new (std::nothrow) DeviceAllocator(budget, total_b);
   if (!c->dev) {
     delete c;
     return fail(RSV_ENOMEM, "host allocation failed");
@@ -208,8 +209,8 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
   double h[2] = {0.0, 0.0};
   if (e == hipSuccess) e = hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipStreamSynchronize(s);
-  reg->alloc->release(blk, bytes);
+  const bool idle = hipStreamSynchronize(s) == hipSuccess;
+  reg->alloc->release(blk, bytes, idle);
   if (e != hipSuccess) return fail(RSV_EDEVICE, "energy: %s", hipGetErrorString(e));
   if (!(h[1] > 0.0)) return fail(RSV_ENUMERIC, "state has zero norm");
   *energy = h[0] / h[1];
@@ -221,9 +222,9 @@ int rsv_correlations_device(rsv_ctx* ctx, int n, rsv_precision prec, const void*
   RSV_TRY(check_state_args(n, prec));
   if (!ctx || !d_psi || !out) return fail(RSV_EINVAL, "NULL argument");
   HIP_TRY(hipSetDevice(ctx->device));
-  Scratch sc(ctx);
-  RSV_TRY(sc.get((size_t)corr_scratch_doubles(n) * sizeof(double)));
   hipStream_t s = as_stream(stream);
+  Scratch sc(ctx, s);
+  RSV_TRY(sc.get((size_t)corr_scratch_doubles(n) * sizeof(double)));
   double* dev = nullptr;
   HIP_TRY(correlations(prec, n, d_psi, (double*)sc.p, &dev, s));
   std::vector<double> h(1 + (size_t)n * n);
@@ -268,7 +269,7 @@ int rsv_evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o
         e = hipMemcpy(tmp, psi0_host, b128, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = convert_from_c128(prec, n, tmp, r->d_psi, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
-        reg->ctx->dev->release(tmp, b128);
+        reg->ctx->dev->release(tmp, b128, e == hipSuccess);
       }
     }
   } else {
@@ -306,7 +307,7 @@ int rsv_result_state(const rsv_result* r, void* host) {
   RSV_TRY(r->ctx->dev->alloc(b128, &tmp));
   hipError_t e = convert_to_c128(r->prec, r->n, r->d_psi, tmp, nullptr);
   if (e == hipSuccess) e = hipMemcpy(host, tmp, b128, hipMemcpyDeviceToHost);
-  r->ctx->dev->release(tmp, b128);
+  r->ctx->dev->release(tmp, b128, e == hipSuccess);  // hipMemcpy waited
   if (e != hipSuccess) return fail(RSV_EDEVICE, "state download: %s", hipGetErrorString(e));
   return RSV_OK;
 }
@@ -330,7 +331,8 @@ int rsv_result_stats(const rsv_result* r, rsv_stats* out) {
 void rsv_result_destroy(rsv_result* r) {
   if (!r) return;
   (void)hipSetDevice(r->ctx->device);
-  r->ctx->dev->release(r->d_psi, r->bytes);
+  const bool idle = hipStreamSynchronize(nullptr) == hipSuccess;  // results use the null stream
+  r->ctx->dev->release(r->d_psi, r->bytes, idle);
   delete r;
 }
 

@@ -47,16 +47,43 @@ int fail(int code, const char* fmt, ...) {
 const char* last_error() { return g_err.c_str(); }
 
 // ------------------------------------------------------------------------------ memory
+namespace {
+constexpr size_t kKeepBlocks = 32, kKeepPinned = 16;
+// Blocks are kept and matched by this size.
+inline size_t block_size(size_t bytes) { return (bytes + 4095) / 4096 * 4096; }
+}  // namespace
+
+DeviceAllocator::~DeviceAllocator() {
+  trim();
+  for (double* h : pinned_) (void)hipHostFree(h);
+}
+
 int DeviceAllocator::alloc(size_t bytes, void** p) {
   *p = nullptr;
+  const size_t size = block_size(bytes);
+  bool squeeze = false;
   {
     std::lock_guard<std::mutex> lk(mu_);
     if (budget_ && in_use_ + bytes > budget_)
       return fail(RSV_ENOMEM, "HBM budget exceeded: %zu in use + %zu requested > %zu budget",
                   in_use_, bytes, budget_);
     in_use_ += bytes;
+    for (size_t i = kept_.size(); i-- > 0;) {
+      if (kept_[i].size != size) continue;
+      *p = kept_[i].p;
+      kept_bytes_ -= size;
+      kept_.erase(kept_.begin() + i);
+      return RSV_OK;
+    }
+    squeeze = budget_ && in_use_ + kept_bytes_ > budget_;
   }
-  hipError_t e = hipMalloc(p, bytes);
+  if (squeeze) trim();  // a budget bounds what the context holds, kept blocks included
+  hipError_t e = hipMalloc(p, size);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    trim();
+    e = hipMalloc(p, size);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -67,11 +94,68 @@ int DeviceAllocator::alloc(size_t bytes, void** p) {
   return RSV_OK;
 }
 
-void DeviceAllocator::release(void* p, size_t bytes) {
+void DeviceAllocator::release(void* p, size_t bytes, bool idle) {
   if (!p) return;
-  (void)hipFree(p);
-  std::lock_guard<std::mutex> lk(mu_);
-  in_use_ -= bytes;
+  // a kept block may next be used on another stream, so nothing may still run on it (hipFree
+  // waits for the device too)
+  if (!idle) (void)hipDeviceSynchronize();
+  const size_t size = block_size(bytes);
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lk(mu_);
+    in_use_ -= bytes;
+    if (size > keep_max_) {
+      out.push_back(p);
+    } else {
+      kept_.push_back(Kept{p, size});
+      kept_bytes_ += size;
+      while (kept_bytes_ > keep_max_ || kept_.size() > kKeepBlocks) {
+        out.push_back(kept_.front().p);
+        kept_bytes_ -= kept_.front().size;
+        kept_.erase(kept_.begin());
+      }
+    }
+  }
+  for (void* q : out) (void)hipFree(q);
+}
+
+void DeviceAllocator::trim() {
+  std::vector<Kept> out;
+  {
+    std::lock_guard<std::mutex> lk(mu_);
+    out.swap(kept_);
+    kept_bytes_ = 0;
+  }
+  for (const Kept& k : out) (void)hipFree(k.p);
+}
+
+double* DeviceAllocator::pinned_take() {
+  {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (!pinned_.empty()) {
+      double* h = pinned_.back();
+      pinned_.pop_back();
+      return h;
+    }
+  }
+  double* h = nullptr;
+  if (hipHostMalloc((void**)&h, kPinnedDoubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return h;
+}
+
+void DeviceAllocator::pinned_give(double* h) {
+  if (!h) return;
+  {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (pinned_.size() < kKeepPinned) {
+      pinned_.push_back(h);
+      return;
+    }
+  }
+  (void)hipHostFree(h);
 }
 
 size_t DeviceAllocator::in_use() const {
@@ -108,7 +192,7 @@ int ArenaAllocator::alloc(size_t bytes, void** p) {
   return RSV_OK;
 }
 
-void ArenaAllocator::release(void* p, size_t bytes) {
+void ArenaAllocator::release(void* p, size_t bytes, bool) {
   if (!p) return;
   bytes = round_up(bytes ? bytes : 1);
   std::lock_guard<std::mutex> lk(mu_);
@@ -570,8 +654,8 @@ struct Borrowed {
   hipStream_t s = nullptr;
   ~Borrowed() {
     if (p) {
-      (void)hipStreamSynchronize(s);
-      a->release(p, bytes);
+      const bool idle = hipStreamSynchronize(s) == hipSuccess;
+      a->release(p, bytes, idle);
     }
   }
 };

@@ -39,22 +39,41 @@ class Allocator {
  public:
   virtual ~Allocator() = default;
   virtual int alloc(size_t bytes, void** p) = 0;
-  virtual void release(void* p, size_t bytes) = 0;
+  // idle: the caller has waited for every kernel and copy that used the block
+  virtual void release(void* p, size_t bytes, bool idle = false) = 0;
   virtual size_t in_use() const = 0;
 };
 
-// hipMalloc / hipFree under an optional byte budget.
+// hipMalloc / hipFree under an optional byte budget, keeping released blocks for the next
+// request of the same size: a call's scratch would otherwise cost more than its kernels
+// (measured on one MI355X: the outputs of a 25-atom state 16.8 ms of which 2.0 ms kernels, a
+// 12-atom Lindblad step with its 9 GB Arnoldi space 260 ms of which 92 ms).  Kept blocks total
+// at most an eighth of the device's memory and 32 blocks, oldest freed first; they count
+// neither as in use nor against the budget, and all are freed before a request fails.
 class DeviceAllocator : public Allocator {
  public:
-  explicit DeviceAllocator(size_t budget) : budget_(budget) {}
+  explicit DeviceAllocator(size_t budget, size_t device_bytes = 0)
+      : budget_(budget), keep_max_(device_bytes / 8) {}
+  ~DeviceAllocator() override;
   int alloc(size_t bytes, void** p) override;
-  void release(void* p, size_t bytes) override;
+  void release(void* p, size_t bytes, bool idle = false) override;
   size_t in_use() const override;
+  void trim();  // frees every kept block
+  // pinned host scalars (kPinnedDoubles) of one call
+  double* pinned_take();
+  void pinned_give(double* h);
 
  private:
-  size_t budget_, in_use_ = 0;
+  struct Kept {
+    void* p;
+    size_t size;
+  };
+  size_t budget_, in_use_ = 0, keep_max_ = 0, kept_bytes_ = 0;
+  std::vector<Kept> kept_;  // oldest first
+  std::vector<double*> pinned_;
   mutable std::mutex mu_;
 };
+constexpr int kPinnedDoubles = 64;
 
 // First-fit sub-allocation of one device block (256-byte granules).  Nothing allocates or
 // frees device memory while it serves, so sub-allocations never synchronise the device.
@@ -64,7 +83,7 @@ class ArenaAllocator : public Allocator {
   ~ArenaAllocator() override;
   int init(size_t bytes);
   int alloc(size_t bytes, void** p) override;  // RSV_ENOMEM when no gap is large enough
-  void release(void* p, size_t bytes) override;
+  void release(void* p, size_t bytes, bool idle = false) override;
   size_t in_use() const override;
   size_t capacity() const { return ff_.size(); }
 

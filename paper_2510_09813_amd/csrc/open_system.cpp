@@ -62,8 +62,8 @@ struct Block {
   }
   ~Block() {
     if (p) {
-      (void)hipStreamSynchronize(s);
-      a->release(p, bytes);
+      const bool idle = hipStreamSynchronize(s) == hipSuccess;
+      a->release(p, bytes, idle);
     }
   }
 };
