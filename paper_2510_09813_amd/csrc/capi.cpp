@@ -189,9 +189,10 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
   const TilePlan plan = make_tile_plan(prec, n);
   if (plan.n_hi_passes > 0 && !reg->d_hbuf)
     RSV_TRY(reg->alloc->alloc(vec_bytes(n, prec), &reg->d_hbuf));
-  // H psi, the partial sums of Re<psi, H psi> and of |psi|^2, their two sums
+  // H psi, the partial sums of Re<psi, H psi> and of |psi|^2 (both from the same sweep: the
+  // first pass reads the state, a sum of its own read it once more), their two sums
   const size_t vb = (vec_bytes(n, prec) + 255) / 256 * 256;
-  const int64_t np_dot = sweep_dot_partials(prec, n), np_norm = vec_num_partials(prec, n);
+  const int64_t np_dot = sweep_dot_partials(prec, n), np_norm = sweep_norm_partials(prec, n);
   const size_t bytes = vb + (size_t)(np_dot + np_norm + 2) * sizeof(double);
   void* blk = nullptr;
   RSV_TRY(reg->alloc->alloc(bytes, &blk));
@@ -201,10 +202,9 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
   double* res = pnorm + np_norm;
   const StepCoef c = step_coef(pl, n, step, dt_ns);
   const SweepIn in{d_psi, nullptr, nullptr, 1.0, 0.0, 0.0, nullptr, 0.0};
-  const SweepOut so{nullptr, nullptr, pdot};
+  const SweepOut so{nullptr, pnorm, pdot};
   hipError_t e = hpsi_sweep(prec, n, c, reg->d_dtab, in, blk, reg->d_hbuf, so, kAllPasses, s);
   if (e == hipSuccess) e = finalize_sum(pdot, np_dot, res, s);
-  if (e == hipSuccess) e = norm2_partial(prec, n, d_psi, pnorm, s);
   if (e == hipSuccess) e = finalize_sum(pnorm, np_norm, res + 1, s);
   double h[2] = {0.0, 0.0};
   if (e == hipSuccess) e = hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, s);

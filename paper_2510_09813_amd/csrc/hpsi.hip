@@ -377,6 +377,8 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
   if (p.u_out) {
 #pragma unroll
     for (int s = 0; s < A; s += V) st_run<R, VB>(&p.u_out[base + lo_pos<TB, VB>(tid, s)], &v[s], p.streaming);
+  }
+  if (p.part_norm) {
 #pragma unroll
     for (int s = 0; s < A; ++s) nrm = norm_add(nrm, (double)v[s].x, (double)v[s].y);
   }
@@ -492,10 +494,8 @@ __global__ __launch_bounds__(kBlock) void hpsi_small_kernel(const StepCoef c, co
   if (tid < dim) {
     v = form<R>(p, input_coefs(p), tid);
     tile[tid] = v;
-    if (p.u_out) {
-      p.u_out[tid] = v;
-      nrm = norm_add(0.0, (double)v.x, (double)v.y);
-    }
+    if (p.u_out) p.u_out[tid] = v;
+    nrm = norm_add(0.0, (double)v.x, (double)v.y);
   }
   __syncthreads();
   if (tid < dim) {
@@ -552,10 +552,11 @@ __global__ __launch_bounds__(NT) void hpsi_hi_kernel(const StepCoef c, const Pas
   for (int s = 0; s < A; ++s) tile[tid + NT * s] = v[s];
   if (p.u_out) {
 #pragma unroll
-    for (int s = 0; s < A; ++s) {
-      put(&p.u_out[gi[s]], v[s], p.streaming);
-      nrm = norm_add(nrm, (double)v[s].x, (double)v[s].y);
-    }
+    for (int s = 0; s < A; ++s) put(&p.u_out[gi[s]], v[s], p.streaming);
+  }
+  if (p.part_norm) {
+#pragma unroll
+    for (int s = 0; s < A; ++s) nrm = norm_add(nrm, (double)v[s].x, (double)v[s].y);
   }
   __syncthreads();
 

@@ -26,6 +26,7 @@ __device__ __forceinline__ double prob(const Cx<R>& v) {
   return norm_add(0.0, (double)v.x, (double)v.y);
 }
 
+// partial[slot * nchunk + chunk] (slot-major, so that the second stage's loads are coalesced).
 template <class R>
 __global__ __launch_bounds__(kBlock) void occ_partial_kernel(const Cx<R>* __restrict__ x,
                                                              const int cbits,
@@ -44,121 +45,150 @@ __global__ __launch_bounds__(kBlock) void occ_partial_kernel(const Cx<R>* __rest
     for (int q = 0; q < 4; ++q)
       if ((s >> q) & 1) reg[q] += p;
   }
-  double* out = partial + (size_t)blockIdx.x * kOccStride;
+  double* out = partial + blockIdx.x;
+  const size_t nchunk = gridDim.x;
   const double t_all = block_sum_256(tot, red);
   if (tid == 0) out[0] = t_all;
   for (int p = 0; p < 8; ++p) {
     const double t = block_sum_256(((tid >> p) & 1) ? tot : 0.0, red);
-    if (tid == 0) out[1 + p] = t;
+    if (tid == 0) out[(1 + p) * nchunk] = t;
   }
   for (int q = 0; q < 4; ++q) {
     const double t = block_sum_256(reg[q], red);
-    if (tid == 0) out[9 + q] = t;
+    if (tid == 0) out[(9 + q) * nchunk] = t;
   }
 }
 
-// Second stage: thread t sums chunks [t*per, (t+1)*per) for every output, then a fixed tree.
+// Second stage, one workgroup per output (0: the total, 1 + p: bit p): thread t sums chunks t,
+// t + 256, ... (four independent chains), then a fixed tree.  One workgroup that looped over
+// the outputs took 174 us at 25 atoms and 0.69 ms at 27, longer than the pass over the state (now
+// 12 us at 25).
 __global__ __launch_bounds__(kBlock) void occ_finalize_kernel(const double* __restrict__ partial,
                                                               const int64_t nchunk,
-                                                              const int n, const int cbits,
+                                                              const int cbits,
                                                               double* __restrict__ out) {
   __shared__ double red[4];
-  const int64_t per = (nchunk + kBlock - 1) / kBlock;
-  const int64_t lo = (int64_t)threadIdx.x * per;
-  const int64_t hi = lo + per < nchunk ? lo + per : nchunk;
-  for (int p = -1; p < n; ++p) {  // p = -1: the total
-    double acc = 0.0;
-    for (int64_t ch = lo; ch < hi; ++ch) {
-      const double* c = partial + ch * kOccStride;
-      if (p < 0) acc += c[0];
-      else if (p < cbits) acc += c[1 + p];
-      else if ((ch >> (p - cbits)) & 1) acc += c[0];
+  const int p = (int)blockIdx.x - 1;
+  const double* c = partial + (p >= 0 && p < cbits ? (int64_t)(1 + p) * nchunk : 0);
+  const int sh = p - cbits;  // >= 0: the total of the chunks whose index bit sh is set
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t ch = threadIdx.x; ch < nchunk; ch += 4 * kBlock) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t w = ch + j * kBlock;
+      if (w < nchunk && (sh < 0 || ((w >> sh) & 1))) acc[j] += c[w];
     }
-    const double t = block_sum_256(acc, red);
-    if (threadIdx.x == 0) out[1 + p] = t;
   }
+  const double t = block_sum_256((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
+  if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
 // --------------------------------------------------------------------------- correlations
-// <n_i n_j> numerators.  Per chunk of 2^C amplitudes (C = min(n, 12)) the low C bits vary and
-// the bits above are constant, so a chunk contributes its total T, its single-bit sums S_p
-// (p < C) and its pair sums P_pq (p < q < C); pairs involving high bits follow from T and
-// S_p and the chunk index.  Thread t holds 16 amplitudes e = t + 256 s: bits 0..7 of e are
-// t's, bits 8..11 are s's.  Each thread keeps its total, its sums over the s bits and over
-// pairs of s bits; the 79 chunk values are then sums over threads in a fixed order.
-constexpr int kCorrSlots = 1 + 12 + 66;
+// <n_i n_j> numerators.  Per chunk of 2^C amplitudes the low C bits vary and the bits above
+// are constant, so a chunk contributes its total T, its single-bit sums S_p (p < C) and its
+// pair sums P_pq (p < q < C); pairs involving high bits follow from T and S_p and the chunk
+// index.  Thread t holds 2^SB amplitudes e = t + 256 s: bits 0..7 of e are t's, the SB others
+// s's (C = 8 + SB).  Each thread keeps its total, its sums over the s bits and over pairs of s
+// bits; the chunk's values are then sums over threads in a fixed order, a loop of 256 LDS reads
+// per value.  That loop bounds the kernel on chunks of 2^12 (187 us at 25 atoms complex128, 2.9
+// TB/s), so from 20 atoms on, where they still fill the chip, chunks of 2^14 run it a quarter
+// as often (146 us, 3.7 TB/s).  (On 2^15 the 29 sums per thread take 59 KB of LDS: two workgroups per CU.)
+template <int SB>
+struct Corr {
+  static constexpr int C = 8 + SB, NV = 1 + SB + SB * (SB - 1) / 2;
+  static constexpr int kSlots = 1 + C + C * (C - 1) / 2;
+  static __device__ __forceinline__ int pair_slot(int p, int q) {  // p < q < C
+    return 1 + C + p * C - p * (p + 1) / 2 + (q - p - 1);
+  }
+  static constexpr __host__ __device__ int s_pair(int a, int b) {  // a < b < SB
+    return 1 + SB + a * SB - a * (a + 1) / 2 + (b - a - 1);
+  }
+};
 
-__device__ __forceinline__ int corr_pair_slot(int p, int q) {  // p < q < 12
-  return 13 + p * 12 - p * (p + 1) / 2 + (q - p - 1);
-}
-
-template <class R>
+// partial[slot * nchunk + chunk]
+template <class R, int SB>
 __global__ __launch_bounds__(kBlock) void corr_partial_kernel(const Cx<R>* __restrict__ x,
                                                               const int cbits,
                                                               double* __restrict__ partial) {
-  __shared__ double th[11][kBlock];  // total, 4 s-bit sums, 6 s-bit pair sums per thread
+  using G = Corr<SB>;
+  __shared__ double th[G::NV][kBlock];
   const uint32_t tid = threadIdx.x;
   const uint32_t chunk = 1u << cbits;
   const size_t base = (size_t)blockIdx.x << cbits;
-  double v[11];
+  double v[G::NV];
 #pragma unroll
-  for (int j = 0; j < 11; ++j) v[j] = 0.0;
-  for (int s = 0; s < 16; ++s) {
-    const uint32_t e = tid + kBlock * s;
-    if (e >= chunk) break;
-    const double p = prob<R>(x[base + e]);
-    v[0] += p;
-    int j = 5;
+  for (int j = 0; j < G::NV; ++j) v[j] = 0.0;
+  // 16 amplitudes at a time: their four s bits first, then the group's sums join the others
+  for (uint32_t g = 0; g < (1u << (SB - 4)); ++g) {
+    if (tid + kBlock * 16 * g >= chunk) break;
+    double w[Corr<4>::NV];
+#pragma unroll
+    for (int j = 0; j < Corr<4>::NV; ++j) w[j] = 0.0;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const uint32_t e = tid + kBlock * (16 * g + s);
+      const double p = e < chunk ? prob<R>(x[base + e]) : 0.0;
+      w[0] += p;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if ((s >> q) & 1) w[1 + q] += p;
+#pragma unroll
+        for (int r = q + 1; r < 4; ++r)
+          if (((s >> q) & 1) && ((s >> r) & 1)) w[Corr<4>::s_pair(q, r)] += p;
+      }
+    }
+    v[0] += w[0];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if ((s >> q) & 1) v[1 + q] += p;
+      v[1 + q] += w[1 + q];
 #pragma unroll
-      for (int r = q + 1; r < 4; ++r, ++j)
-        if (((s >> q) & 1) && ((s >> r) & 1)) v[j] += p;
+      for (int r = q + 1; r < 4; ++r) v[G::s_pair(q, r)] += w[Corr<4>::s_pair(q, r)];
+    }
+#pragma unroll
+    for (int r = 4; r < SB; ++r) {
+      if (!((g >> (r - 4)) & 1)) continue;
+      v[1 + r] += w[0];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[G::s_pair(q, r)] += w[1 + q];
+#pragma unroll
+      for (int q = 4; q < r; ++q)
+        if ((g >> (q - 4)) & 1) v[G::s_pair(q, r)] += w[0];
     }
   }
 #pragma unroll
-  for (int j = 0; j < 11; ++j) th[j][tid] = v[j];
+  for (int j = 0; j < G::NV; ++j) th[j][tid] = v[j];
   __syncthreads();
-  if (tid < kCorrSlots) {
+  if (tid < G::kSlots) {
     // which per-thread value, and which thread bits must be set, for slot tid
-    int src = 0, ta = -1, tb = -1;
+    int src = 0;
+    uint32_t need = 0;
     const int slot = (int)tid;
-    if (slot == 0) {
-      src = 0;
-    } else if (slot < 13) {  // single bit p
-      const int p = slot - 1;
-      if (p < 8) ta = p;
-      else src = 1 + (p - 8);
-    } else {  // pair p < q
+    if (slot > G::C) {  // pair p < q
       int p = 0, q = 1;
-      for (int a = 0; a < 12; ++a)
-        for (int b = a + 1; b < 12; ++b)
-          if (corr_pair_slot(a, b) == slot) p = a, q = b;
-      if (q < 8) {
-        ta = p, tb = q;
-      } else if (p < 8) {
-        ta = p, src = 1 + (q - 8);
-      } else {
-        const int a = p - 8, b = q - 8;  // s-bit pair index in the order the loop above used
-        int j = 5;
-        for (int qq = 0; qq < 4; ++qq)
-          for (int rr = qq + 1; rr < 4; ++rr, ++j)
-            if (qq == a && rr == b) src = j;
-      }
+      for (int a = 0; a < G::C; ++a)
+        for (int b = a + 1; b < G::C; ++b)
+          if (G::pair_slot(a, b) == slot) p = a, q = b;
+      if (q < 8) need = (1u << p) | (1u << q);
+      else if (p < 8) need = 1u << p, src = 1 + (q - 8);
+      else src = G::s_pair(p - 8, q - 8);
+    } else if (slot > 8) {  // single bit of s
+      src = slot - 8;
+    } else if (slot > 0) {  // single bit of t
+      need = 1u << (slot - 1);
     }
     double acc = 0.0;
-    for (int t = 0; t < kBlock; ++t) {
-      if (ta >= 0 && !((t >> ta) & 1)) continue;
-      if (tb >= 0 && !((t >> tb) & 1)) continue;
-      acc += th[src][t];
+#pragma unroll 8
+    for (uint32_t t = 0; t < kBlock; ++t) {
+      const double a = th[src][t];
+      acc += (t & need) == need ? a : 0.0;
     }
-    partial[(size_t)blockIdx.x * kCorrSlots + slot] = acc;
+    partial[(size_t)slot * gridDim.x + blockIdx.x] = acc;
   }
 }
 
 // out[0] = total; out[1 + p * n + q] (p <= q, bit positions) = sum |x_b|^2 b_p b_q.  One
 // workgroup per output; thread t sums chunks t, t + 256, ... then a fixed tree.
+template <int SB>
 __global__ __launch_bounds__(kBlock) void corr_finalize_kernel(const double* __restrict__ partial,
                                                                const int64_t nchunk, const int n,
                                                                const int cbits,
@@ -174,29 +204,46 @@ __global__ __launch_bounds__(kBlock) void corr_finalize_kernel(const double* __r
           break;
         }
   }
-  double acc = 0.0;
-  for (int64_t ch = threadIdx.x; ch < nchunk; ch += kBlock) {
-    const double* c = partial + ch * kCorrSlots;
-    double v;
-    if (p < 0) {
-      v = c[0];
-    } else if (p == q) {
-      v = p < cbits ? c[1 + p] : (((ch >> (p - cbits)) & 1) ? c[0] : 0.0);
-    } else if (q < cbits) {
-      v = c[corr_pair_slot(p, q)];
-    } else if (p < cbits) {
-      v = ((ch >> (q - cbits)) & 1) ? c[1 + p] : 0.0;
-    } else {
-      v = (((ch >> (p - cbits)) & 1) && ((ch >> (q - cbits)) & 1)) ? c[0] : 0.0;
-    }
-    acc += v;
+  // the slot to sum, and the chunk-index bits that must be set
+  int slot = 0;
+  int64_t need = 0;
+  if (p >= 0 && q < cbits) {
+    slot = p == q ? 1 + p : Corr<SB>::pair_slot(p, q);
+  } else if (p >= 0) {
+    need = int64_t(1) << (q - cbits);
+    if (p < cbits) slot = 1 + p;
+    else need |= int64_t(1) << (p - cbits);
   }
+  const double* c = partial + (int64_t)slot * nchunk;
+  double acc = 0.0;
+  for (int64_t ch = threadIdx.x; ch < nchunk; ch += kBlock)
+    if ((ch & need) == need) acc += c[ch];
   const double t = block_sum_256(acc, red);
   if (threadIdx.x == 0) {
     if (p < 0) out[0] = t;
     else out[1 + p * n + q] = t;
   }
 }
+
+template <int SB>
+hipError_t correlations_sb(int prec, int n, const void* x, double* scratch, double** out_dev,
+                           hipStream_t s) {
+  const int cbits = n < Corr<SB>::C ? n : Corr<SB>::C;
+  const uint32_t nchunk = 1u << (n - cbits);
+  double* out = scratch + (size_t)nchunk * Corr<SB>::kSlots;
+  if (prec == kC128)
+    hipLaunchKernelGGL((corr_partial_kernel<double, SB>), dim3(nchunk), dim3(kBlock), 0, s,
+                       (const double2*)x, cbits, scratch);
+  else
+    hipLaunchKernelGGL((corr_partial_kernel<float, SB>), dim3(nchunk), dim3(kBlock), 0, s,
+                       (const float2*)x, cbits, scratch);
+  hipLaunchKernelGGL(corr_finalize_kernel<SB>, dim3(1 + n * (n + 1) / 2), dim3(kBlock), 0, s,
+                     scratch, (int64_t)nchunk, n, cbits, out);
+  *out_dev = out;
+  return hipGetLastError();
+}
+
+constexpr int kCorrWideAtoms = 20;  // 2^14-amplitude chunks from here on
 
 // ------------------------------------------------------------------------------- sampling
 __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t s) {
@@ -206,24 +253,57 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t s) {
   return z ^ (z >> 31);
 }
 
+// LDS position of probability e of a chunk: one word of padding per 16, so that a thread's 16
+// consecutive values and its neighbours' start in different banks.
+__device__ __forceinline__ uint32_t padded(uint32_t e) { return e + (e >> 4); }
+constexpr int kPaddedChunk = (1 << kChunkBits) + (1 << (kChunkBits - 4));
+
+// Exclusive prefix of tsum[0..255] on top of `run`, in thread order (thread 0; 16 values at a
+// time through registers, so that the adds do not wait for the LDS); returns the end.
+__device__ __forceinline__ double serial_scan(double* tsum, double run) {
+  for (int t0 = 0; t0 < kBlock; t0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = tsum[t0 + j];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const double w = v[j];
+      v[j] = run;
+      run += w;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) tsum[t0 + j] = v[j];
+  }
+  return run;
+}
+
+// Sum of |x|^2 per chunk.  Thread t adds amplitudes 16 t .. 16 t + 15, the order of the in-block
+// scan of sample_kernel; they reach it through LDS, because loads of 16 consecutive
+// amplitudes per lane use a sixteenth of each cache line they touch (25 atoms complex128: 565
+// us that way, 0.95 TB/s; now 101 us, 5.3 TB/s).
 template <class R>
 __global__ __launch_bounds__(kBlock) void block_prob_kernel(const Cx<R>* __restrict__ x,
                                                             const int cbits,
                                                             double* __restrict__ bsum) {
   __shared__ double red[4];
+  __shared__ double pr[kPaddedChunk];
   const uint32_t chunk = 1u << cbits;
   const size_t base = (size_t)blockIdx.x << cbits;
-  double acc = 0.0;
-  // the same per-thread order as the in-block scan of sample_kernel
+#pragma unroll
   for (uint32_t j = 0; j < 16; ++j) {
-    const uint32_t e = threadIdx.x * 16 + j;
-    if (e < chunk) acc += prob<R>(x[base + e]);
+    const uint32_t e = threadIdx.x + kBlock * j;
+    pr[padded(e)] = e < chunk ? prob<R>(x[base + e]) : 0.0;
   }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (uint32_t j = 0; j < 16; ++j) acc += pr[padded(threadIdx.x * 16 + j)];
   const double t = block_sum_256(acc, red);
   if (threadIdx.x == 0) bsum[blockIdx.x] = t;
 }
 
-// Exclusive scan of nb block sums into pre[0..nb], pre[nb] = total.  One workgroup.
+// Exclusive scan of nb block sums into pre[0..nb], pre[nb] = total.  One workgroup; thread t
+// owns a contiguous range, read eight values at a time.
 __global__ __launch_bounds__(kBlock) void block_scan_kernel(const double* __restrict__ bsum,
                                                             const int64_t nb,
                                                             double* __restrict__ pre) {
@@ -232,21 +312,32 @@ __global__ __launch_bounds__(kBlock) void block_scan_kernel(const double* __rest
   const int64_t lo = (int64_t)threadIdx.x * per;
   const int64_t hi = lo + per < nb ? lo + per : nb;
   double acc = 0.0;
-  for (int64_t i = lo; i < hi; ++i) acc += bsum[i];
+  int64_t i = lo;
+  for (; i + 8 <= hi; i += 8) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = bsum[i + j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc += v[j];
+  }
+  for (; i < hi; ++i) acc += bsum[i];
   tsum[threadIdx.x] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double run = 0.0;
-    for (int t = 0; t < kBlock; ++t) {
-      const double v = tsum[t];
-      tsum[t] = run;
-      run += v;
-    }
-    pre[nb] = run;
-  }
+  if (threadIdx.x == 0) pre[nb] = serial_scan(tsum, 0.0);
   __syncthreads();
   double run = tsum[threadIdx.x];
-  for (int64_t i = lo; i < hi; ++i) {
+  i = lo;
+  for (; i + 8 <= hi; i += 8) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = bsum[i + j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      pre[i + j] = run;
+      run += v[j];
+    }
+  }
+  for (; i < hi; ++i) {
     pre[i] = run;
     run += bsum[i];
   }
@@ -260,24 +351,38 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
                                                         const uint64_t seed,
                                                         uint64_t* __restrict__ idx) {
   __shared__ double tsum[kBlock];
+  __shared__ double pr[kPaddedChunk];
   __shared__ int64_t blk_sh;
-  __shared__ double target_sh;
   __shared__ int fallback_sh;
-  __shared__ unsigned int cand, last_sh;
+  __shared__ unsigned int cand, last_sh, hit;
   const uint32_t tid = threadIdx.x;
   const uint32_t chunk = 1u << cbits;
-  if (tid == 0) {
-    const uint64_t r = splitmix64_at(seed, blockIdx.x);
-    const double u = (double)(r >> 11) * 0x1.0p-53;
-    const double total = pre[nb];
-    const double target = u * total;
-    // smallest block whose inclusive prefix exceeds the target
-    int64_t lo = 0, hi = nb;  // answer in [lo, hi]; hi == nb means none
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (pre[mid + 1] > target) hi = mid;
-      else lo = mid + 1;
+  const double u = (double)(splitmix64_at(seed, blockIdx.x) >> 11) * 0x1.0p-53;
+  const double target = u * pre[nb];
+  // smallest block whose inclusive prefix exceeds the target: the prefixes do not decrease, so
+  // each round tests 256 spaced candidates of the open range and keeps the gap below the first
+  // that does (one memory latency per factor of 256 where a bisection takes eight)
+  int64_t lo = 0, hi = nb;  // answer in [lo, hi]; hi == nb means none
+  while (lo < hi) {
+    if (tid == 0) hit = kBlock;
+    __syncthreads();
+    const int64_t step = (hi - lo + kBlock - 1) / kBlock;
+    const int64_t c = lo + (int64_t)(tid + 1) * step - 1;  // the last block of gap tid
+    if (c < hi && pre[c + 1] > target) atomicMin(&hit, tid);
+    __syncthreads();
+    const int64_t h = hit;
+    __syncthreads();
+    const int64_t glo = lo + h * step;  // the answer lies in gap h, or beyond the last full one
+    if (h < kBlock) {
+      hi = glo + step - 1;
+      lo = glo;
+    } else {
+      const int64_t full = (hi - lo) / step;  // gaps whose last block was tested
+      lo += full * step;
+      if (step == 1) lo = hi;
     }
+  }
+  if (tid == 0) {
     int fb = 0;
     if (lo == nb) {  // no block: fall back to the last block with mass
       fb = 1;
@@ -285,33 +390,29 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
       while (lo > 0 && !(bsum[lo] > 0.0)) --lo;
     }
     blk_sh = lo;
-    target_sh = target;
     fallback_sh = fb;
     cand = 0xFFFFFFFFu;
     last_sh = 0u;
   }
   __syncthreads();
   const int64_t blk = blk_sh;
-  const double target = target_sh;
   const size_t base = (size_t)blk << cbits;
+#pragma unroll
+  for (uint32_t j = 0; j < 16; ++j) {
+    const uint32_t e = tid + kBlock * j;
+    pr[padded(e)] = e < chunk ? prob<R>(x[base + e]) : 0.0;
+  }
+  __syncthreads();
   double p[16];
   double own = 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
-    const uint32_t e = tid * 16 + j;
-    p[j] = e < chunk ? prob<R>(x[base + e]) : 0.0;
+    p[j] = pr[padded(tid * 16 + j)];
     own += p[j];
   }
   tsum[tid] = own;
   __syncthreads();
-  if (tid == 0) {
-    double run = pre[blk];
-    for (int t = 0; t < kBlock; ++t) {
-      const double v = tsum[t];
-      tsum[t] = run;
-      run += v;
-    }
-  }
+  if (tid == 0) serial_scan(tsum, pre[blk]);
   __syncthreads();
   if (!fallback_sh) {
     double c = tsum[tid];
@@ -382,31 +483,23 @@ hipError_t occupations(int prec, int n, const void* x, double* partial, double* 
   else
     hipLaunchKernelGGL(occ_partial_kernel<float>, dim3(nchunk), dim3(kBlock), 0, s,
                        (const float2*)x, cbits, partial);
-  hipLaunchKernelGGL(occ_finalize_kernel, dim3(1), dim3(kBlock), 0, s, partial,
-                     (int64_t)nchunk, n, cbits, out);
+  hipLaunchKernelGGL(occ_finalize_kernel, dim3(n + 1), dim3(kBlock), 0, s, partial,
+                     (int64_t)nchunk, cbits, out);
   return hipGetLastError();
 }
 
 int64_t corr_scratch_doubles(int n) {
-  const int cbits = n < kChunkBits ? n : kChunkBits;
-  return (int64_t(1) << (n - cbits)) * kCorrSlots + 1 + (int64_t)n * n;
+  const bool wide = n >= kCorrWideAtoms;
+  const int C = wide ? Corr<6>::C : Corr<4>::C;
+  const int cbits = n < C ? n : C;
+  return (int64_t(1) << (n - cbits)) * (wide ? Corr<6>::kSlots : Corr<4>::kSlots) + 1 +
+         (int64_t)n * n;
 }
 
 hipError_t correlations(int prec, int n, const void* x, double* scratch, double** out_dev,
                         hipStream_t s) {
-  const int cbits = n < kChunkBits ? n : kChunkBits;
-  const uint32_t nchunk = 1u << (n - cbits);
-  double* out = scratch + (size_t)nchunk * kCorrSlots;
-  if (prec == kC128)
-    hipLaunchKernelGGL(corr_partial_kernel<double>, dim3(nchunk), dim3(kBlock), 0, s,
-                       (const double2*)x, cbits, scratch);
-  else
-    hipLaunchKernelGGL(corr_partial_kernel<float>, dim3(nchunk), dim3(kBlock), 0, s,
-                       (const float2*)x, cbits, scratch);
-  hipLaunchKernelGGL(corr_finalize_kernel, dim3(1 + n * (n + 1) / 2), dim3(kBlock), 0, s, scratch,
-                     (int64_t)nchunk, n, cbits, out);
-  *out_dev = out;
-  return hipGetLastError();
+  return n >= kCorrWideAtoms ? correlations_sb<6>(prec, n, x, scratch, out_dev, s)
+                             : correlations_sb<4>(prec, n, x, scratch, out_dev, s);
 }
 
 int64_t sample_scratch_doubles(int n) {
