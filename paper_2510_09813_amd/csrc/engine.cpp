@@ -8,7 +8,12 @@
 // diagonalises the tridiagonal T_k in FP64 and stops when the a-posteriori estimate
 // beta_{k-1} |[exp(-i dt T_k) e_1]_k| |psi| is at most tol.  Then
 // psi_{k+1} = |psi_k| sum_l y_l v_l (one combine sweep, which also returns |psi_{k+1}|^2).
+//
+// Registers that fit one workgroup (packed_max_atoms) run whole calls on the device instead, by
+// the kernel of packed jobs: see evolve_small.
 #include "engine.h"
+
+#include "packed.h"
 
 #include <algorithm>
 #include <chrono>
@@ -250,6 +255,10 @@ static double midpoint(const double* x, int64_t k, int dt_ns) {
   return 0.5 * (x[lo] + x[hi]);
 }
 
+void step_midpoints(const double* x, int64_t first, int64_t count, int dt_ns, double* out) {
+  for (int64_t j = 0; j < count; ++j) out[j] = midpoint(x, first + j, dt_ns);
+}
+
 StepCoef step_coef(const rsv_pulses* pl, int n, int64_t k, int dt_ns) {
   StepCoef c;
   std::memset(&c, 0, sizeof c);
@@ -331,6 +340,8 @@ int register_create(rsv_ctx* ctx, Allocator* alloc, int n, const double* xyz, do
   r->n = n;
   r->prec = prec;
   r->c6 = c6;
+  for (int p = 1; p < n; ++p)
+    for (int q = 0; q < p; ++q) r->u_abs += std::fabs(ub[p * 32 + q]);
   if (h_scal) {
     r->h_scal = h_scal;
   } else {
@@ -662,6 +673,125 @@ struct Borrowed {
 
 }  // namespace
 
+// Whether calls on this register run on one workgroup: it fits, nothing asks for the host driver
+// (re-orthogonalisation does), and every step's exponential fits the device's series (else the
+// device would sub-step where the host's eigendecomposition need not, or give up where it would
+// not).  A step there costs its iterations' latency on the chip (about 1 us each at 10 atoms),
+// on the host driver five API calls per iteration (20 us).
+static bool small_route(const rsv_register* reg, double tau, double max_drive, double max_detuning) {
+  return reg->n <= packed_max_atoms(reg->prec) &&
+         packed_resolves(tau, 0.5 * (reg->u_abs + max_detuning + max_drive));
+}
+
+// Steps [0, count) of values mid(j, dst) -> the n_steps x sites values of omega, delta (and phi)
+// of steps j.., in launches of as many steps as the kernel arguments hold.
+struct SmallRun {
+  rsv_register* reg;
+  double tau, tol, dir;
+  int kmax, max_depth, per_site, direct;
+  bool with_phi;  // direct: whether any coupling has an imaginary part
+};
+
+static int run_small(const SmallRun& r, const double* om, const double* de, const double* ph,
+                     int64_t stride, int64_t count, void* d_psi, double* obs, int64_t obs_every,
+                     hipStream_t s, rsv_stats* st, double* norm2) {
+  rsv_register* reg = r.reg;
+  RSV_TRY(workspace_acquire(reg, r.kmax));
+  Workspace& ws = reg->ws;
+  const int n = reg->n, prec = reg->prec;
+  const size_t vb = vec_bytes(n, prec);
+  const int64_t sites = r.per_site ? n : 1;
+  const int64_t per = kMidValues / (sites * (r.with_phi ? 3 : 2));
+  char* blk = (char*)ws.block;  // kmax + 1 basis vectors, then two more
+  PackedJob jb{};
+  jb.n = n;
+  jb.kmax = r.kmax;
+  jb.max_depth = r.max_depth;
+  jb.per_site = r.per_site;
+  jb.real = !r.per_site && !r.with_phi;
+  jb.direct = r.direct;
+  jb.dir = r.dir;
+  jb.tau = r.tau;
+  jb.tol = r.tol;
+  jb.ub = reg->d_ub;
+  jb.diag = (double*)(blk + (size_t)(r.kmax + 1) * vb);  // 8 bytes per amplitude at least
+  void* carry = blk + (size_t)(r.kmax + 2) * vb;         // the state between launches
+  jb.basis = blk;
+  jb.out = ws.dscal;
+  jb.obs = obs;
+  jb.obs_every = obs_every;
+  double mid[kMidValues];
+  for (int64_t k = 0; k < count; k += per) {
+    const int64_t c = std::min(per, count - k);
+    double* dst = mid;
+    for (const double* x : {om, de, ph}) {
+      if (!x) continue;
+      for (int64_t i = 0; i < sites; ++i, dst += c)
+        std::memcpy(dst, x + i * stride + k, (size_t)c * sizeof(double));
+    }
+    jb.n_steps = c;
+    jb.resume = k > 0;
+    jb.obs_first = k;
+    jb.psi_in = k == 0 ? d_psi : carry;
+    jb.psi_out = k + c == count ? d_psi : carry;
+    HIP_TRY(small_evolve(prec, jb, mid, r.with_phi, s));
+  }
+  double* h = reg->h_scal;
+  HIP_TRY(hipMemcpyAsync(h, ws.dscal, 8 * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  const int status = (int)h[0];
+  st->krylov_iters += (int64_t)h[1];
+  st->krylov_max = std::max<int64_t>(st->krylov_max, (int64_t)h[2]);
+  st->substeps += (int64_t)h[3];
+  st->bytes_hpsi += h[1] * (double)(size_t(1) << n) * (prec == kC128 ? 40.0 : 20.0);
+  *norm2 = h[4];
+  if (status == RSV_ENOTCONV)
+    return fail(RSV_ENOTCONV, "Krylov exponential not converged with kmax = %d", r.kmax);
+  if (status != RSV_OK) {
+    if (!(h[4] > 0.0) || !std::isfinite(h[4]))
+      return fail(RSV_ENUMERIC, "state norm is %g", std::sqrt(h[4]));
+    return fail(RSV_ENUMERIC, "Lanczos coefficient not finite");
+  }
+  return RSV_OK;
+}
+
+// evolve on one workgroup.  *taken = 0: the call takes the host driver.
+static int evolve_small(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o,
+                        int64_t first, int64_t count, void* d_psi, double* obs_dev, int obs_every,
+                        hipStream_t s, rsv_stats* st, double* norm2, bool* taken) {
+  const int n = reg->n;
+  const double tau = o->dt_ns * 1e-3;
+  const int64_t rows = pl->per_site ? n : 1;
+  *taken = false;
+  if (count < 1 || o->reorth || n > packed_max_atoms(reg->prec)) return RSV_OK;
+  std::vector<double> v((size_t)3 * rows * count);
+  double* om = v.data();
+  double* de = om + rows * count;
+  double* ph = de + rows * count;
+  for (int64_t i = 0; i < rows; ++i) {
+    const int64_t src = i * pl->n_samples;
+    step_midpoints(pl->omega + src, first, count, o->dt_ns, om + i * count);
+    step_midpoints(pl->delta + src, first, count, o->dt_ns, de + i * count);
+    if (pl->phi) step_midpoints(pl->phi + src, first, count, o->dt_ns, ph + i * count);
+  }
+  double drive = 0.0, detuning = 0.0;
+  for (int64_t k = 0; k < count; ++k) {
+    double a = 0.0, d = 0.0;
+    for (int64_t i = 0; i < rows; ++i) {
+      a += std::fabs(om[i * count + k]);
+      d += std::fabs(de[i * count + k]);
+    }
+    drive = std::max(drive, a * (double)(n / rows));
+    detuning = std::max(detuning, d * (double)(n / rows));
+  }
+  if (!small_route(reg, tau, drive, detuning)) return RSV_OK;
+  *taken = true;
+  const SmallRun r{reg, tau, o->tol, 1.0, o->kmax, o->max_substep_depth, pl->per_site, 0,
+                   pl->phi != nullptr};
+  return run_small(r, om, de, pl->phi ? ph : nullptr, count, count, d_psi, obs_dev, obs_every, s, st,
+                   norm2);
+}
+
 int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, void* d_psi,
            hipStream_t s, rsv_stats* st, int obs_every, double* obs_out) {
   if (!reg) return fail(RSV_EINVAL, "register is NULL");
@@ -677,18 +807,6 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
   Workspace& ws = reg->ws;
   const int n = reg->n, prec = reg->prec;
   const size_t vb = vec_bytes(n, prec);
-  HIP_TRY(hipMemcpyAsync(ws.basis[0], d_psi, vb, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(norm2_partial(prec, n, ws.basis[0], ws.pnorm, s));
-  HIP_TRY(finalize_sum(ws.pnorm, vec_num_partials(prec, n), ws.dscal + kNormSlot, s));
-  Lanczos L;
-  L.reg = reg;
-  L.s = s;
-  L.st = st;
-  std::memset(L.alpha, 0, sizeof L.alpha);
-  std::memset(L.beta, 0, sizeof L.beta);
-  std::memset(L.scale, 0, sizeof L.scale);
-  L.work.assign(tridiag_work_doubles(kMaxKrylov), 0.0);
-  RSV_TRY(fetch_scalars(L, kNormSlot, 1, &L.norm2));
   // observed steps: fused occupation partials, then n + 1 sums per observation
   Borrowed ob;
   double* obs_dev = nullptr;
@@ -698,20 +816,40 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
     ob.s = s;
     ob.bytes = (part + (size_t)n_obs * (n + 1)) * sizeof(double);
     RSV_TRY(reg->alloc->alloc(ob.bytes, &ob.p));
+    obs_dev = (double*)ob.p + part;
+  }
+  double norm2 = 0.0;
+  bool small = false;
+  RSV_TRY(evolve_small(reg, pl, o, first, count, d_psi, obs_dev, obs_every, s, st, &norm2, &small));
+  if (small) {
+    st->steps += count;
+  } else {
+    HIP_TRY(hipMemcpyAsync(ws.basis[0], d_psi, vb, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(norm2_partial(prec, n, ws.basis[0], ws.pnorm, s));
+    HIP_TRY(finalize_sum(ws.pnorm, vec_num_partials(prec, n), ws.dscal + kNormSlot, s));
+    Lanczos L;
     L.occ_partial = (double*)ob.p;
-    obs_dev = L.occ_partial + part;
+    L.reg = reg;
+    L.s = s;
+    L.st = st;
+    std::memset(L.alpha, 0, sizeof L.alpha);
+    std::memset(L.beta, 0, sizeof L.beta);
+    std::memset(L.scale, 0, sizeof L.scale);
+    L.work.assign(tridiag_work_doubles(kMaxKrylov), 0.0);
+    RSV_TRY(fetch_scalars(L, kNormSlot, 1, &L.norm2));
+    const double tau = o->dt_ns * 1e-3;  // us
+    for (int64_t k = first; k < first + count; ++k) {
+      const StepCoef c = step_coef(pl, n, k, o->dt_ns);
+      const int64_t j = k - first + 1;  // steps done after this one
+      double* slot = (n_obs > 0 && j % obs_every == 0) ? obs_dev + (j / obs_every - 1) * (n + 1)
+                                                        : nullptr;
+      RSV_TRY(propagate(L, c, tau, o->tol, o->kmax, o->max_substep_depth, o->reorth != 0, slot));
+      st->steps += 1;
+    }
+    HIP_TRY(hipMemcpyAsync(d_psi, ws.basis[0], vb, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    norm2 = L.norm2;
   }
-  const double tau = o->dt_ns * 1e-3;  // us
-  for (int64_t k = first; k < first + count; ++k) {
-    const StepCoef c = step_coef(pl, n, k, o->dt_ns);
-    const int64_t j = k - first + 1;  // steps done after this one
-    double* slot = (n_obs > 0 && j % obs_every == 0) ? obs_dev + (j / obs_every - 1) * (n + 1)
-                                                      : nullptr;
-    RSV_TRY(propagate(L, c, tau, o->tol, o->kmax, o->max_substep_depth, o->reorth != 0, slot));
-    st->steps += 1;
-  }
-  HIP_TRY(hipMemcpyAsync(d_psi, ws.basis[0], vb, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
   if (n_obs > 0) {
     std::vector<double> h((size_t)n_obs * (n + 1));
     HIP_TRY(hipMemcpy(h.data(), obs_dev, h.size() * sizeof(double), hipMemcpyDeviceToHost));
@@ -721,7 +859,7 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
       for (int i = 0; i < n; ++i) obs_out[r * n + i] = v[1 + (n - 1 - i)] / v[0];
     }
   }
-  st->norm_final = std::sqrt(L.norm2);
+  st->norm_final = std::sqrt(norm2);
   st->seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return RSV_OK;
 }
@@ -730,9 +868,26 @@ int krylov_exp(rsv_register* reg, const StepCoef& c, double tau, double dir, dou
                int kmax, int max_depth, void* d_psi, hipStream_t s, rsv_stats* st) {
   if (!reg || !d_psi) return fail(RSV_EINVAL, "NULL argument");
   HIP_TRY(hipSetDevice(reg->ctx->device));
+  const int n = reg->n, prec = reg->prec;
+  double drive = 0.0, detuning = 0.0, v[3 * kMaxAtoms];  // by atom: bit p is atom n-1-p
+  const int sites = c.mode == kCoefSite ? n : 1;
+  for (int p = 0; p < sites; ++p) {
+    const int i = sites - 1 - p;
+    v[i] = 2.0 * c.up_re[p];
+    v[sites + i] = c.delta[p];
+    v[2 * sites + i] = 2.0 * c.up_im[p];
+    drive += std::hypot(v[i], v[2 * sites + i]) * (n / sites);
+    detuning += std::fabs(c.delta[p]) * (n / sites);
+  }
+  if (small_route(reg, tau, drive, detuning)) {
+    const bool phi = c.mode != kCoefReal;
+    const SmallRun r{reg, tau, tol, dir < 0 ? -1.0 : 1.0, kmax, max_depth, sites > 1 ? 1 : 0, 1, phi};
+    double norm2 = 1.0;
+    const int rc = run_small(r, v, v + sites, phi ? v + 2 * sites : nullptr, 1, 1, d_psi, nullptr, 1, s, st, &norm2);
+    return norm2 == 0.0 ? RSV_OK : rc;  // exp(...) 0 = 0
+  }
   RSV_TRY(workspace_acquire(reg, kmax));
   Workspace& ws = reg->ws;
-  const int n = reg->n, prec = reg->prec;
   const size_t vb = vec_bytes(n, prec);
   HIP_TRY(hipMemcpyAsync(ws.basis[0], d_psi, vb, hipMemcpyDeviceToDevice, s));
   HIP_TRY(norm2_partial(prec, n, ws.basis[0], ws.pnorm, s));

@@ -101,6 +101,8 @@ int check_state_args(int n, int prec);
 int check_pulses(const rsv_pulses* pl, int n);
 int check_opts(const rsv_evolve_opts* o, const rsv_pulses* pl, int64_t* first, int64_t* count);
 StepCoef step_coef(const rsv_pulses* pl, int n, int64_t k, int dt_ns);
+// out[j] = the midpoint value of step first + j (Sec. III), j < count.
+void step_midpoints(const double* x, int64_t first, int64_t count, int dt_ns, double* out);
 
 struct Workspace {
   int kmax = 0;
@@ -136,6 +138,7 @@ struct rsv_register {
   int prec = 0;
   double c6 = 0;
   double* d_ub = nullptr;
+  double u_abs = 0;  // sum of |U_ij| over the pairs
   double* d_dtab = nullptr;  // interaction-diagonal tables of the H psi low pass
   void* d_hbuf = nullptr;  // high-bit partial of rsv_apply_hamiltonian
   double* d_efull = nullptr;  // the 2^N interaction energies (FP64) of the Lindblad path

@@ -1,477 +1,824 @@
-// Packed small-job evolution: one workgroup per job runs the whole time evolution of a
-// small register (2^n amplitudes held by the workgroup) without host round trips.
+// Evolution of small registers: one workgroup per job runs a whole time evolution (2^n
+// amplitudes held by the workgroup) without host round trips.  The server packs many jobs into
+// a launch; rsv_evolve and its device forms run their small registers the same way.
 //
-// Each step is the same method as the host-driven path (Sec. III and III.A): midpoint
-// parameters of step k, Lanczos recurrence with FP64 reductions, the a-posteriori estimate
+// Each step is the method of the host-driven path (Sec. III and III.A): midpoint parameters,
+// the three-term Lanczos recurrence with FP64 scalars, the a-posteriori estimate
 // beta_{m-1} |[exp(-i dt T_m) e_1]_{m-1}| |psi| <= tol, sub-steps on non-convergence, and
 // psi <- |psi| sum_l y_l v_l.  Only the small exponential differs: instead of the host
-// eigendecomposition, y = exp(-i tau T) e_1 is evaluated on the device by the Chebyshev
+// eigendecomposition, y = exp(-i tau T) e_1 is evaluated by one wave with the Chebyshev
 // expansion
 //   exp(-i a x) = J_0(a) + 2 sum_{k>=1} (-i)^k J_k(a) T_k(x),   x in [-1, 1],
-// applied to X = (T - c)/r with c, r from Gershgorin bounds and a = tau r (Bessel
-// coefficients by Miller's backward recurrence normalised with J_0 + 2 sum J_2k = 1).  One
-// wave evaluates it, lane i holding row i of T (m <= 64).  The series is capped at
-// kMaxBessel terms; a step whose tau r exceeds what that resolves is shortened (halved
-// until it fits) before the estimate is tested, which only adds sub-steps.
+// applied to X = (T - c)/r with c, r from Gershgorin bounds and a = tau r (Bessel coefficients
+// by Miller's backward recurrence normalised with J_0 + 2 sum J_2k = 1), lane i holding row i of
+// T (m <= 64).  The series is capped at kMaxBessel terms; a step whose tau r exceeds what that
+// resolves is shortened (halved until it fits) before the estimate is tested, which only adds
+// sub-steps.
 //
-// Krylov vectors of a job live in global memory (L2-resident at these sizes); the newest
-// one is kept in the LDS tile, where the level swaps read it, and H u in registers.
+// What bounds it is latency: a step is a chain of Krylov iterations, each a few hundred
+// nanoseconds of LDS reads between two barriers.  So
+//  * the workgroup holds the three vectors of the recurrence in registers (the Krylov basis is
+//    only written, to the L2, and read back once per step by the thread that wrote it); the
+//    level swaps of the thread-index bits read the LDS tile, the others are register moves;
+//  * |u_k|^2 and <u_k, H u_k> are summed together (DPP adds inside a wave, one LDS exchange
+//    between waves): two barriers per iteration;
+//  * the estimate is first tested at the dimension where an a-priori value of it (`expected`)
+//    comes within a factor 2^10 of the tolerance, and a test that fails says how far that value
+//    is off, so the next test waits until the corrected one meets the tolerance.  All this
+//    depends on T alone, so a run split at a step boundary takes the same dimensions as the
+//    whole run; a dimension larger than the smallest one that meets the tolerance is as exact;
+//  * sizes are compile-time constants, and a launch's threads fit its registers: 256 for up to
+//    kPackSmallBits atoms (four or fewer amplitudes per thread, several jobs per CU), 512 or 1024
+//    above.
+// Measured on one MI355X: 100 steps of the 10-atom chain (27 iterations each, complex128) 5.0 ms,
+// 66 ms by the host driver; 64 jobs of 6..13 atoms (complex64, 50..400 steps) 56 ms, 205 ms with
+// runtime sizes, two reductions and an LDS read per swap.  Per iteration 0.6 us at 8 atoms, 1.6
+// us at 10 (complex128), 5 us at 13 (complex64, the FP64 sums and conversions of 8192
+// amplitudes on one CU).
 #include "device_common.h"
 #include "packed.h"
+
+#include <cmath>
+#include <cstring>
 
 namespace rsv {
 namespace {
 
-constexpr int kThreadBits = 9;
-constexpr int kThreads = 1 << kThreadBits;
-constexpr int kWaves = kThreads / 64;
 constexpr int kMaxBessel = 512;
+constexpr int kBesselPad = 16;  // Miller's start above the last term, and the loop's round-up
 
-template <class R> struct PackGeo;
-template <> struct PackGeo<double> { static constexpr int A = 8; };   // n <= 12
-template <> struct PackGeo<float> { static constexpr int A = 16; };   // n <= 13
+// ------------------------------------------------------------------ sums inside a wave (DPP)
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_update_dpp(
+                                       0u, __builtin_bit_cast(uint32_t, v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppFromBelow = 0x138, kDppFromAbove = 0x130;  // lane i takes lane i - 1 / i + 1
 
-__device__ __forceinline__ double wg_sum(double v, double* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double r = 0.0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) r += red[w];
-  __syncthreads();
-  return r;
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+struct OpAdd { __device__ double operator()(double a, double b) const { return a + b; } };
+struct OpMin { __device__ double operator()(double a, double b) const { return fmin(a, b); } };
+struct OpMax { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
+
+// Reduction over rows of 16 lanes, the same value in all of a row's lanes.
+template <class Op>
+__device__ __forceinline__ double row_reduce(double v, Op op) {
+  v = op(v, dpp<kDppXor1>(v));
+  v = op(v, dpp<kDppXor2>(v));
+  v = op(v, dpp<kDppHalfMirror>(v));
+  return op(v, dpp<kDppMirror>(v));
+}
+// Over the wave, uniform.  Every lane must be active.
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  v = row_reduce(v, op);
+  return op(op(lane_value(v, 0), lane_value(v, 16)), op(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ __forceinline__ double wave_total(double v) { return wave_reduce(v, OpAdd()); }
+
+// exp(i x).  Not inlined: its range reduction would take registers from the whole kernel.
+__device__ __attribute__((noinline)) double2 unit_phase(double x) {
+  double s, c;
+  sincos(x, &s, &c);
+  return double2{c, s};
 }
 
 struct Shared {
   double alpha[kMaxKrylov + 1], beta[kMaxKrylov + 1], scale[kMaxKrylov + 1];
-  double yre[kMaxKrylov], yim[kMaxKrylov];
-  double bessel[kMaxBessel + 1];
-  double dl[kMaxAtoms];  // detuning of bit p at the current step
-  double red[kWaves];
-  double est, cheb_c, cheb_r;
-  int cheb_k;
+  double cre[kMaxKrylov], cim[kMaxKrylov];  // |psi| y_l s_l
+  double bessel[kMaxBessel + kBesselPad];
+  double2 red[16];                          // per wave (|u|^2, <u, H u>)
+  double occ[16][kMaxPackBits + 1];
+  double dl[kMaxPackBits];                  // detuning of bit p at the current step
+  double est;
+  double ba, binv, bscale;                  // the series in bessel: argument, 1 / a, normalisation
+  int bk;                                   // and its terms
 };
 
-// Midpoint value of step k (Sec. III): mean of the samples at floor(m) and ceil(m),
-// m = (k + 1/2) dt in ns.
-__device__ __forceinline__ double midpoint(const double* x, long k, int dt_ns) {
-  const long twice = (2 * k + 1) * (long)dt_ns;
-  return 0.5 * (x[twice / 2] + x[(twice + 1) / 2]);
+// Bessel coefficients of a series of argument a, by one wave, into sh (unnormalised; the factor
+// that normalises them goes to sh.bscale).  Returns false where more than kMaxBessel terms are
+// needed.
+__device__ __forceinline__ bool bessel_series(Shared& sh, double a) {
+  const int lane = threadIdx.x & 63;
+  // terms: a + 8 a^(1/3) + 20 leaves a tail below 1e-15 for any a; for small a fewer do: J_k(a)
+  // <= (a/2)^k / k! < (e a / 2k)^k, below e^-42 where k (ln(2k/a) - 1) >= 42 (Newton from above,
+  // each iterate stays on the safe side of the convex function's root)
+  const float fa = (float)fmin(a, 1e6);
+  float kt = fa + 8.0f * __powf(fa, 0.33333334f) + 20.0f;
+  if (kt > (float)(kMaxBessel - 1)) return false;
+  {
+    float k = kt;
+#pragma unroll 1
+    for (int it = 0; it < 6; ++it) {
+      const float l = __logf(2.0f * k / fa);
+      const float f = k * (l - 1.0f) - 42.0f;
+      if (!(f > 0.0f && l > 0.1f)) break;
+      k -= __fdividef(f, l);
+    }
+    kt = fminf(kt, fmaxf(k, 1.0f));
+  }
+  const int K = min((int)kt + 2, kMaxBessel - 1);
+  // Miller's backward recurrence for J_K+8..J_0 (J_K is below the rounding of J_0, so a start
+  // a few orders above it is enough), normalised by J_0 + 2 sum J_2k = 1
+  const int M = K + 8;
+  const double inv = 1.0 / a, two_over_a = 2.0 * inv;
+  double jp = 0.0, j = 1e-250, norm = 0.0;
+  if (lane < 8) sh.bessel[M + lane] = 0.0;  // read by the last group of the series' loop
+#pragma unroll 2
+  for (int k = M; k >= 1; --k) {
+    if (lane == 0) sh.bessel[k] = j;
+    norm += (k & 1) ? 0.0 : j;
+    const double jm = fma(k * two_over_a, j, -jp);
+    jp = j;
+    j = jm;
+    if (fabs(j) > 1e250) {  // rescale everything recurred so far (only where a is tiny)
+      j *= 1e-250;
+      jp *= 1e-250;
+      norm *= 1e-250;
+      if (lane == 0)
+        for (int q = k; q <= M; ++q) sh.bessel[q] *= 1e-250;
+    }
+  }
+  if (lane == 0) {
+    sh.bessel[0] = j;
+    sh.bscale = 2.0 / (2.0 * norm + j);
+    sh.ba = a;
+    sh.binv = inv;
+    sh.bk = K;
+  }
+  // one wave: its LDS accesses are in order; keep the compiler from moving them
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return true;
 }
 
-// y = exp(-i tau T_m) e_1 (all m rows into sh.yre / sh.yim when full, else |y_{m-1}| into
-// sh.est).  Called by every thread of the workgroup; thread 0 computes the Bessel
-// coefficients, wave 0 runs the Chebyshev recurrence with lane i holding row i.  Returns
-// false (and est = inf) when tau times the spectral half-width of T_m needs more than
-// kMaxBessel terms: the caller shortens tau.
-__device__ bool cheb_expm(Shared& sh, int m, double tau, bool full) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) {
-    double lo = 1e300, hi = -1e300;
-    for (int i = 0; i < m; ++i) {
-      const double bl = i > 0 ? fabs(sh.beta[i - 1]) : 0.0;
-      const double br = i + 1 < m ? fabs(sh.beta[i]) : 0.0;
-      lo = fmin(lo, sh.alpha[i] - bl - br);
-      hi = fmax(hi, sh.alpha[i] + bl + br);
-    }
-    const double c = 0.5 * (hi + lo), r = 0.5 * (hi - lo);
-    sh.cheb_c = c;
-    sh.cheb_r = r;
-    int K = -1;  // -1: T is numerically a multiple of the identity; -2: series too long
-    if (r > 1e-300 && tau * r > 1e-30) {
-      const double a = tau * r;
-      // terms: J_k(a) <= (a/2)^k / k! bounds the tail for small a; a + 8 a^(1/3) + 20 for
-      // large a (both leave a tail below 1e-15)
-      K = (int)(a + 8.0 * cbrt(a) + 20.0);
-      double bound = 1.0;
-      for (int k = 1; k < K; ++k) {
-        bound *= 0.5 * a / k;
-        if (k > 0.5 * a + 1.0 && bound < 1e-17) {
-          K = k;
-          break;
-        }
-      }
-      if (K > kMaxBessel - 1) {
-        sh.cheb_k = -2;
-        K = -3;
-      }
-    }
-    if (K >= 0) {
-      const double a = tau * r;
-      // Miller's backward recurrence for J_0..J_K(a), normalised by J_0 + 2 sum J_2k = 1
-      const int M = K + 24 + (int)sqrt(40.0 * (K + 1));
-      const double two_over_a = 2.0 / a;
-      double jp = 0.0, j = 1e-280, norm = 0.0;
-      for (int k = 0; k <= K; ++k) sh.bessel[k] = 0.0;
-      for (int k = M; k >= 1; --k) {
-        if (k <= K) sh.bessel[k] = j;
-        if (!(k & 1)) norm += 2.0 * j;
-        const double jm = (k * two_over_a) * j - jp;
-        jp = j;
-        j = jm;
-        if (fabs(j) > 1e200) {  // rescale everything recurred so far
-          j *= 1e-200;
-          jp *= 1e-200;
-          norm *= 1e-200;
-          for (int q = k; q <= K; ++q) sh.bessel[q] *= 1e-200;
-        }
-      }
-      norm += j;
-      sh.bessel[0] = j;
-      const double inv = 1.0 / norm;
-      for (int k = 0; k <= K; ++k) sh.bessel[k] *= inv;
-    }
-    if (K != -3) sh.cheb_k = K;
+// [exp(-i tau T_m) e_1] by one wave: lane i returns row i without the common phase factor
+// exp(i phase); the return value is |row m - 1| (uniform), or -1 when tau times the spectral
+// half-width of T_m needs more than kMaxBessel terms (the caller shortens tau).  The half-width
+// is rounded up (by at most a quarter), so that most tests find the coefficients of the one
+// before: Miller's recurrence costs as much as the series.
+__device__ __forceinline__ double cheb_rows(Shared& sh, int m, double tau, double& yr, double& yi,
+                                            double& phase) {
+  const int lane = threadIdx.x & 63;
+  const bool live = lane < m;
+  const double al = live ? sh.alpha[lane] : 0.0;
+  const double bl = live && lane > 0 ? sh.beta[lane - 1] : 0.0;
+  const double br = live && lane + 1 < m ? sh.beta[lane] : 0.0;
+  const double w = bl + br;
+  const double lo = wave_reduce(live ? al - w : 1e300, OpMin());
+  const double hi = wave_reduce(live ? al + w : -1e300, OpMax());
+  const double c = 0.5 * (hi + lo);
+  // a rounded up to three significant bits (at least 1/2)
+  double a = fmax(0.5, 0.5 * tau * (hi - lo));
+  {
+    const uint64_t b = __builtin_bit_cast(uint64_t, a);
+    a = __builtin_bit_cast(double, (b + ((uint64_t(1) << 50) - 1)) & ~((uint64_t(1) << 50) - 1));
   }
-  __syncthreads();
-  const int K = sh.cheb_k;  // every thread reads it before the closing barrier
-  if (tid < 64) {
-    const bool live = lane < m;
-    const double c = sh.cheb_c, r = sh.cheb_r;
-    const double a_i = live ? sh.alpha[lane] : 0.0;
-    const double bl = (live && lane > 0) ? sh.beta[lane - 1] : 0.0;
-    const double br = (live && lane + 1 < m) ? sh.beta[lane] : 0.0;
-    double yr = 0.0, yi = 0.0;
-    if (K == -2) {  // not resolvable with kMaxBessel terms: report "not converged"
-      yr = __builtin_inf();
-    } else if (K < 0) {
-      yr = lane == 0 ? 1.0 : 0.0;
+  phase = -tau * c;
+  yr = yi = 0.0;
+  if (!(sh.ba == a) && !bessel_series(sh, a)) return -1.0;
+  const int K = sh.bk;
+  // t_0 = e_1, t_1 = X e_1, t_{k+1} = 2 X t_k - t_{k-1}; the coefficients carry the factor 2
+  const double s = 2.0 * tau * sh.binv;
+  const double xa = live ? (al - c) * s : 0.0, xl = bl * s, xr = br * s;
+  double t0 = lane == 0 ? 1.0 : 0.0;
+  double t1 = 0.5 * fma(xa, t0, xl * dpp<kDppFromBelow>(t0));
+  yr = 0.5 * sh.bessel[0] * t0;
+  auto next = [&]() {
+    const double below = dpp<kDppFromBelow>(t1), above = dpp<kDppFromAbove>(t1);
+    const double t2 = fma(xr, above, fma(xl, below, fma(xa, t1, -t0)));
+    t0 = t1;
+    t1 = t2;
+  };
+#pragma unroll 1
+  for (int k = 1; k <= K; k += 4) {  // (-i)^k: -i, -1, +i, +1
+    const double b0 = sh.bessel[k], b1 = sh.bessel[k + 1], b2 = sh.bessel[k + 2], b3 = sh.bessel[k + 3];
+    yi = fma(-b0, t1, yi);
+    next();
+    yr = fma(-b1, t1, yr);
+    next();
+    yi = fma(b2, t1, yi);
+    next();
+    yr = fma(b3, t1, yr);
+    next();
+  }
+  yr *= sh.bscale;
+  yi *= sh.bscale;
+  const double er = lane_value(yr, m - 1), ei = lane_value(yi, m - 1);
+  return sqrt(er * er + ei * ei);
+}
+
+// log2 of an a-priori value of the estimate beta |psi| |[exp(-i tau T_k) e_1]_{k-1}|: the
+// component is at most prod (tau beta_j) / (k - 1)! (the leading term of the exponential; lead
+// holds it times beta |psi|), and for a spectrum of half-width a / tau it falls below that by
+// about exp(-a^2 / 4k) (J_k(a) against (a/2)^k / k!).  Gershgorin's half-width is up to twice the
+// true one, so the first test (tight = false) takes that factor and later ones its fourth root.
+__device__ __forceinline__ float expected(double lead, double a, int k, bool tight) {
+  const float fa = (float)fmin(a, 1e6);
+  return (float)__builtin_amdgcn_frexp_exp(lead) -
+         (tight ? 0.0902f : 0.3607f) * fa * fa * __frcp_rn((float)k);
+}
+
+// ------------------------------------------------------------------------------- one job
+// N atoms on 2^TB threads, A amplitudes each: the thread bits of the index are TB consecutive
+// ones; the bits above (and, for complex64, bit 0, so that every access moves 16 bytes per lane)
+// number the thread's own amplitudes.  MODE: kCoefReal (one real coupling for every atom) or
+// kCoefSite (any other drive).
+template <class R, int N, int TB, int MODE>
+struct Runner {
+  using C = Cx<R>;
+  static constexpr int T = 1 << TB, W = T / 64;
+  static constexpr int RB = N > TB ? N - TB : 0, A = 1 << RB;
+  static constexpr int VB = sizeof(R) == 4 && RB > 0 ? 1 : 0;  // register bits below the thread bits
+  static constexpr int LB = N < TB ? N : TB;  // bits of the index that are thread bits
+  static constexpr uint32_t dim = 1u << N;
+
+  // Index of amplitude s of thread tid; the slot bit of index bit p (-1: a thread bit).
+  static __device__ __forceinline__ uint32_t pos(uint32_t tid, int s) {
+    return (tid << VB) + (uint32_t)(s & ((1 << VB) - 1)) + ((uint32_t)(s >> VB) << (TB + VB));
+  }
+  static constexpr int slot_bit(int p) { return p < VB ? p : p >= TB + VB ? p - TB : -1; }
+
+  // The thread index, opaque to the optimiser: without it every address and predicate derived
+  // from the index is kept in a register across the whole kernel, and the vectors spill.
+  static __device__ __forceinline__ uint32_t fresh(uint32_t tid) {
+    asm volatile("" : "+v"(tid));
+    return tid;
+  }
+
+  // Thread bits whose swap is a DPP move inside the wave rather than an LDS read: with complex64
+  // it joins the add (bits 0, 1) or takes one move more (2, 3), where the LDS pipe takes 4 cycles
+  // of the CU per wave and amplitude; complex128 needs four moves per amplitude against 8 cycles.
+  static constexpr int DB = LB < (sizeof(R) == 4 ? 4 : 2) ? LB : (sizeof(R) == 4 ? 4 : 2);
+
+  static __device__ __forceinline__ R moved(R v, int q) {
+    switch (q) {
+      case 0: return dpp<kDppXor1>(v);
+      case 1: return dpp<kDppXor2>(v);
+      case 2: return dpp<kDppXor3>(dpp<kDppHalfMirror>(v));
+      default: return dpp<kDppHalfMirror>(dpp<kDppMirror>(v));
+    }
+  }
+
+  // The amplitude with index bit p swapped (p < N known at compile time once unrolled).
+  static __device__ __forceinline__ C neighbour(const C* tile, const C (&u)[A], uint32_t tid, int p,
+                                                int s) {
+    if (slot_bit(p) >= 0) return u[(s ^ (1 << (slot_bit(p) & 31))) & (A - 1)];
+    const int q = p - VB;
+    if (q < DB) return C{moved(u[s].x, q), moved(u[s].y, q)};
+    return tile[pos(tid ^ (1u << q), s)];
+  }
+
+  // z = H u (u in the tile and in registers) and this thread's Re<u, z>
+  static __device__ __forceinline__ double apply(const C* tile, const C (&u)[A], const R (&dg)[A],
+                                                 const R* cf, uint32_t tid, C (&z)[A]) {
+    if constexpr (MODE == kCoefReal) {
+      // sum the neighbours, then apply the coupling once
+#pragma unroll
+      for (int s = 0; s < A; ++s) z[s] = C{0, 0};
+#pragma unroll
+      for (int p = 0; p < N; ++p) {
+#pragma unroll
+        for (int s = 0; s < A; ++s) {
+          const C nb = neighbour(tile, u, tid, p, s);
+          z[s].x += nb.x;
+          z[s].y += nb.y;
+        }
+      }
+      const R ur = cf[0];
+#pragma unroll
+      for (int s = 0; s < A; ++s)
+        z[s] = C{dg[s] * u[s].x + ur * z[s].x, dg[s] * u[s].y + ur * z[s].y};
     } else {
-      // t_0 = e_1, t_1 = X e_1, t_{k+1} = 2 X t_k - t_{k-1};  X = (T - c) / r
-      auto apply_x = [&](double t) {
-        const double tm = __shfl_up(t, 1, 64);
-        const double tp = __shfl_down(t, 1, 64);
-        double v = (a_i - c) * t;
-        if (lane > 0) v += bl * tm;
-        if (lane < 63) v += br * tp;
-        return live ? v / r : 0.0;
-      };
-      double t0 = lane == 0 ? 1.0 : 0.0;
-      double t1 = apply_x(t0);
-      yr = sh.bessel[0] * t0;
-      for (int k = 1; k <= K; ++k) {
-        const double w = 2.0 * sh.bessel[k] * t1;
-        switch (k & 3) {  // (-i)^k
-          case 0: yr += w; break;
-          case 1: yi -= w; break;
-          case 2: yr -= w; break;
-          default: yi += w; break;
+#pragma unroll
+      for (int s = 0; s < A; ++s) z[s] = C{dg[s] * u[s].x, dg[s] * u[s].y};
+#pragma unroll
+      for (int p = 0; p < N; ++p) {
+        // <0|h|1> is the conjugate of <1|h|0>; a register bit's level is known per slot
+        const R cr = cf[2 * p], ci1 = cf[2 * p + 1];
+        const R ci = slot_bit(p) < 0 && !((tid >> (p - VB)) & 1u) ? -ci1 : ci1;
+#pragma unroll
+        for (int s = 0; s < A; ++s) {
+          const C nb = neighbour(tile, u, tid, p, s);
+          const R c = slot_bit(p) >= 0 && !((s >> (slot_bit(p) & 31)) & 1) ? -ci : ci;
+          z[s].x += cr * nb.x - c * nb.y;
+          z[s].y += cr * nb.y + c * nb.x;
         }
-        const double t2 = 2.0 * apply_x(t1) - t0;
-        t0 = t1;
-        t1 = t2;
       }
     }
-    const double ph = -tau * c;
-    const double er = cos(ph), ei = sin(ph);
-    const double zr = er * yr - ei * yi, zi = er * yi + ei * yr;
-    if (full) {
-      if (live) {
-        sh.yre[lane] = zr;
-        sh.yim[lane] = zi;
+    double dot = 0.0;
+#pragma unroll
+    for (int s = 0; s < A; ++s)
+      dot += (double)u[s].x * (double)z[s].x + (double)u[s].y * (double)z[s].y;
+    return dot;
+  }
+
+  // Tile write, H, and both sums over the workgroup (uniform): the tile is free again after it.
+  static __device__ __forceinline__ double2 sweep(Shared& sh, C* tile, const C (&u)[A],
+                                                  const R (&dg)[A], const R* cf,
+                                                  uint32_t tid0, bool live, C (&z)[A]) {
+    const uint32_t tid = fresh(tid0);
+#pragma unroll
+    for (int s = 0; s < A; ++s) tile[pos(tid, s)] = u[s];
+    double nn = 0.0;
+#pragma unroll
+    for (int s = 0; s < A; ++s) nn = norm_add(nn, (double)u[s].x, (double)u[s].y);
+    __syncthreads();
+    double dot = apply(tile, u, dg, cf, tid, z);
+    if (!live) dot = 0.0;  // threads beyond the register hold zeros, and read zeros or rubbish
+    nn = wave_total(nn);
+    dot = wave_total(dot);
+    if ((tid & 63u) == 0) sh.red[tid >> 6] = double2{nn, dot};
+    __syncthreads();
+    if constexpr (W <= 4) {
+      double2 r = sh.red[0];
+#pragma unroll
+      for (int w = 1; w < W; ++w) {
+        const double2 o = sh.red[w];
+        r.x += o.x;
+        r.y += o.y;
       }
-    } else if (lane == m - 1) {
-      sh.est = hypot(zr, zi);
+      return r;
+    } else {
+      static_assert(W == 8 || W == 16, "every row of 16 lanes holds all waves' sums");
+      double2 o = sh.red[tid & (W - 1)];
+      o.x += dpp<kDppXor1>(o.x);
+      o.y += dpp<kDppXor1>(o.y);
+      o.x += dpp<kDppXor2>(o.x);
+      o.y += dpp<kDppXor2>(o.y);
+      o.x += dpp<kDppHalfMirror>(o.x);
+      o.y += dpp<kDppHalfMirror>(o.y);
+      if constexpr (W == 16) {
+        o.x += dpp<kDppMirror>(o.x);
+        o.y += dpp<kDppMirror>(o.y);
+      }
+      return double2{lane_value(o.x, 0), lane_value(o.y, 0)};
     }
   }
+
+  static __device__ __forceinline__ void occupations(Shared& sh, const C (&u)[A], uint32_t tid,
+                                                     double* dst) {
+    tid = fresh(tid);
+    double pr[A], tot = 0.0;
+#pragma unroll
+    for (int s = 0; s < A; ++s) {
+      pr[s] = norm_add(0.0, (double)u[s].x, (double)u[s].y);
+      tot += pr[s];
+    }
+#pragma unroll 1
+    for (int p = -1; p < N; ++p) {  // -1: the total
+      double v = tot;
+      if (p >= 0) {
+        v = 0.0;
+#pragma unroll
+        for (int s = 0; s < A; ++s) v += (pos(tid, s) >> p) & 1u ? pr[s] : 0.0;
+      }
+      v = wave_total(v);
+      if ((tid & 63u) == 0) sh.occ[tid >> 6][1 + p] = v;
+    }
+    __syncthreads();
+    if (tid <= (uint32_t)N) {
+      double v = 0.0;
+#pragma unroll 1
+      for (int w = 0; w < W; ++w) v += sh.occ[w][tid];
+      dst[tid] = v;
+    }
+    __syncthreads();
+  }
+
+  static __device__ __forceinline__ void run(const PackedJob& jb, const double* om, const double* de,
+                                             const double* ph, bool has_phi, Shared& sh, C* tile,
+                                             R* cf) {
+    const uint32_t tid = threadIdx.x;
+    const bool live = N >= TB || tid < dim;
+    const bool wave0 = tid < 64;
+    C* basis = (C*)jb.basis;
+    int64_t iters = 0, kmax_used = 0, substeps = 0;
+    int status = RSV_OK;
+    if (jb.resume) {
+      status = (int)jb.out[0];
+      iters = (int64_t)jb.out[1];
+      kmax_used = (int64_t)jb.out[2];
+      substeps = (int64_t)jb.out[3];
+      if (status != RSV_OK) return;  // (uniform)
+    }
+    C u[A];  // the newest Krylov vector; between steps the state
+#pragma unroll
+    for (int s = 0; s < A; ++s) {
+      const uint32_t e = pos(tid, s);
+      u[s] = C{0, 0};
+      if (!live) continue;
+      if (jb.psi0) u[s] = C{(R)jb.psi0[e].x, (R)jb.psi0[e].y};
+      else if (jb.psi_in) u[s] = ((const C*)jb.psi_in)[e];
+      else u[s] = C{(R)(e == 0 ? 1 : 0), 0};
+    }
+    {  // E_b, read back by this thread at each step
+      double v[A];
+#pragma unroll
+      for (int s = 0; s < A; ++s) v[s] = 0.0;
+#pragma unroll 1
+      for (int p = 1; p < N; ++p) {
+#pragma unroll 1
+        for (int q = 0; q < p; ++q) {
+          const double w = jb.ub[p * 32 + q];
+#pragma unroll
+          for (int s = 0; s < A; ++s) {
+            const uint32_t e = pos(tid, s);
+            v[s] += (e >> p) & (e >> q) & 1u ? w : 0.0;
+          }
+        }
+      }
+      if (live) {
+#pragma unroll
+        for (int s = 0; s < A; ++s) jb.diag[pos(tid, s)] = v[s];
+      }
+    }
+    const float log2_tol = (float)__builtin_amdgcn_frexp_exp(jb.tol);
+    if (tid == 0) sh.ba = -1.0;
+    __syncthreads();  // every thread has read the previous launch's results from out
+
+#pragma unroll 1
+    for (int64_t step = 0; step < jb.n_steps && status == RSV_OK; ++step) {
+      // coefficients of H_k by bit position p (atom n-1-p)
+      if (tid < (uint32_t)N) {
+        const size_t at = (jb.per_site ? (size_t)(N - 1 - tid) * jb.n_steps : 0) + step;
+        const double h = 0.5 * om[at], f = has_phi ? ph[at] : 0.0;
+        double re = h, im = 0.5 * f;
+        if (!jb.direct) {
+          const double2 w = unit_phase(f);
+          re = h * w.x;
+          im = -h * w.y;
+        }
+        cf[2 * tid] = (R)re;  // <1|h|0>
+        cf[2 * tid + 1] = (R)im;
+        sh.dl[tid] = de[at];
+      }
+      __syncthreads();
+      R dg[A];  // diagonal of H_k
+      {
+        double v[A];
+        const uint32_t t = fresh(tid);
+#pragma unroll
+        for (int s = 0; s < A; ++s) v[s] = live ? jb.diag[pos(t, s)] : 0.0;
+        if (jb.per_site) {
+#pragma unroll 1
+          for (int p = 0; p < N; ++p) {
+            const double d = sh.dl[p];
+#pragma unroll
+            for (int s = 0; s < A; ++s) v[s] -= (pos(t, s) >> p) & 1u ? d : 0.0;
+          }
+        } else {
+          const double d = sh.dl[0];
+#pragma unroll
+          for (int s = 0; s < A; ++s) v[s] -= d * (double)__popc(pos(t, s));
+        }
+#pragma unroll
+        for (int s = 0; s < A; ++s) dg[s] = (R)v[s];
+      }
+
+      double remaining = jb.tau;
+#pragma unroll 1
+      while (remaining > 0.0 && status == RSV_OK) {
+        C prev[A], z[A];
+#pragma unroll
+        for (int s = 0; s < A; ++s) prev[s] = z[s] = C{0, 0};
+        int m = 0;
+        // target: the part of the step this basis must resolve; shortened while the
+        // exponential of the growing T_m is too wide for one Chebyshev series
+        double target = remaining, sub = remaining;
+        double nrm = 0.0, lead = 0.0;         // |psi|, |psi| prod_{j<k} (tau beta_{j-1}) / (k-1)!
+        double s1 = 0.0, s2 = 0.0;            // scales of u_{k-1} and u_{k-2}
+        double glo = 1e300, ghi = -1e300, blast = 0.0;  // Gershgorin bounds of the rows before k-1
+        double2 nd = {0.0, 0.0};              // |u|^2 and <u, H u> of the newest vector
+        bool stop = false;
+        float off = -10.0f;                   // log2 of the estimate over its a-priori value
+        bool tested = false;
+#pragma unroll 1
+        for (int k = 0; !stop; ++k) {
+          const double alpha = s1 * s1 * nd.y;  // alpha_{k-1}
+          if (k > 0) {
+            // u_k = s z - alpha s u_{k-1} - (s_{k-2}/s_{k-1}) u_{k-2}, rounded once
+            const double ca = alpha * s1, cb = s2 * nd.x * s1;  // s2 / s1 = s2 |u_{k-1}|
+#pragma unroll
+            for (int s = 0; s < A; ++s) {
+              const double re = s1 * (double)z[s].x - ca * (double)u[s].x - cb * (double)prev[s].x;
+              const double im = s1 * (double)z[s].y - ca * (double)u[s].y - cb * (double)prev[s].y;
+              prev[s] = u[s];
+              u[s] = live ? C{(R)re, (R)im} : C{0, 0};
+            }
+          }
+          if (k < jb.kmax && live) {
+            const uint32_t t = fresh(tid);
+            C* b = basis + (size_t)k * dim;
+#pragma unroll
+            for (int s = 0; s < A; ++s) b[pos(t, s)] = u[s];
+          }
+          // z_k = H u_k and |u_k|^2 together: z_k is not needed where this dimension resolves
+          // the step, but its sum shares the exchange of |u_k|^2
+          nd = sweep(sh, tile, u, dg, cf, tid, live, z);
+          ++iters;
+          if (k == 0) {
+            nrm = sqrt(nd.x);
+            if (!(nrm > 0.0) || !isfinite(nrm)) {
+              status = RSV_ENUMERIC;
+              break;
+            }
+            s1 = rsqrt(nd.x);
+            lead = nrm;
+            if (tid == 0) sh.scale[0] = s1;
+            continue;
+          }
+          if (tid == 0) sh.alpha[k - 1] = alpha;
+          if (!isfinite(nd.x) || !isfinite(alpha)) {
+            status = RSV_ENUMERIC;
+            break;
+          }
+          const double sk = rsqrt(nd.x);
+          const double bk = nd.x > 0.0 ? nd.x * sk : 0.0;  // |u_k|
+          m = k;
+          const bool last = k == jb.kmax || bk == 0.0;
+          // the last row of T_k couples upwards only
+          const double half = 0.5 * (fmax(ghi, alpha + blast) - fmin(glo, alpha - blast));
+          const float guess = expected(lead * bk, target * half, k, tested);
+          if (last || !(guess + off > log2_tol)) {
+            // phase 0: the target, shortened while it is too wide; then, where this basis is the
+            // last and does not resolve it, the longest part that it does: 1 the first dyadic
+            // fraction that converges, 2 ten bisections above it, 3 the exponential of the result
+            int phase = 0, cnt = 0;
+            double tq = target, bad = target;
+#pragma unroll 1
+            for (;;) {
+              if (wave0) {
+                double yr, yi, ang;
+                const double e = cheb_rows(sh, m, tq, yr, yi, ang);
+                if (tid == 0) sh.est = e;
+                if ((int)tid < m && e >= 0.0 && bk * e * nrm <= jb.tol) {
+                  const double2 w = unit_phase(ang);
+                  const double sc = nrm * sh.scale[tid];
+                  sh.cre[tid] = sc * (w.x * yr - w.y * yi);
+                  sh.cim[tid] = jb.dir * sc * (w.x * yi + w.y * yr);
+                }
+              }
+              __syncthreads();
+              const double est = sh.est;  // < 0: too wide
+              __syncthreads();
+              // (met also at beta = 0, an invariant subspace)
+              const bool ok = est >= 0.0 && bk * est * nrm <= jb.tol;
+              if (phase == 0) {
+                if (est < 0.0 && ++cnt <= 64) {
+                  lead = ldexp(lead, 1 - k);  // target^(k-1) is a factor of it
+                  tq = target *= 0.5;
+                  continue;
+                }
+                if (ok) {
+                  sub = target;
+                  stop = true;
+                  break;
+                }
+                if (est >= 0.0 && !last) {
+                  off = (float)__builtin_amdgcn_frexp_exp(bk * est * nrm) -
+                        expected(lead * bk, target * half, k, true) - 2.0f;
+                  tested = true;
+                  break;
+                }
+                if (est < 0.0 || jb.max_depth < 1) {
+                  status = RSV_ENOTCONV;
+                  break;
+                }
+                phase = cnt = 1;
+                bad = target;
+                tq = ldexp(target, -1);
+              } else if (phase == 1) {
+                if (ok) {
+                  sub = tq;
+                  phase = 2;
+                  cnt = 0;
+                  tq = 0.5 * (sub + bad);
+                } else {
+                  bad = tq;
+                  if (++cnt > jb.max_depth) {
+                    status = RSV_ENOTCONV;
+                    break;
+                  }
+                  tq = ldexp(target, -cnt);
+                }
+              } else if (phase == 2) {
+                if (ok) sub = tq;
+                else bad = tq;
+                if (++cnt < 10) {
+                  tq = 0.5 * (sub + bad);
+                } else {
+                  phase = 3;
+                  tq = sub;
+                }
+              } else {
+                stop = true;
+                break;
+              }
+            }
+            if (stop || status != RSV_OK) break;
+          }
+          s2 = s1;
+          s1 = sk;
+          if (tid == 0) {
+            sh.beta[k - 1] = bk;
+            sh.scale[k] = s1;
+          }
+          lead *= target * bk * (double)__frcp_rn((float)k);
+          glo = fmin(glo, alpha - blast - bk);
+          ghi = fmax(ghi, alpha + blast + bk);
+          blast = bk;
+        }
+        if (status != RSV_OK) break;
+        kmax_used = kmax_used > m ? kmax_used : (int64_t)m;
+        // psi <- |psi| sum_l y_l s_l u_l over this thread's own amplitudes
+        double re[A], im[A];
+#pragma unroll
+        for (int s = 0; s < A; ++s) re[s] = im[s] = 0.0;
+        if (live) {
+          const uint32_t t = fresh(tid);
+          const C* b = basis;
+          // several vectors' loads in flight: the basis of a large job lives beyond the L2
+          constexpr int G = A >= 16 ? 4 : 32 / A > 8 ? 8 : 32 / A;
+          int l = 0;
+#pragma unroll 1
+          for (; l + G <= m; l += G, b += (size_t)G * dim) {
+            C x[G][A];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+              for (int s = 0; s < A; ++s) x[g][s] = b[(size_t)g * dim + pos(t, s)];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+              const double cr = sh.cre[l + g], ci = sh.cim[l + g];
+#pragma unroll
+              for (int s = 0; s < A; ++s) {
+                re[s] += cr * (double)x[g][s].x - ci * (double)x[g][s].y;
+                im[s] += cr * (double)x[g][s].y + ci * (double)x[g][s].x;
+              }
+            }
+          }
+#pragma unroll 1
+          for (; l < m; ++l, b += dim) {
+            const double cr = sh.cre[l], ci = sh.cim[l];
+#pragma unroll
+            for (int s = 0; s < A; ++s) {
+              const C x = b[pos(t, s)];
+              re[s] += cr * (double)x.x - ci * (double)x.y;
+              im[s] += cr * (double)x.y + ci * (double)x.x;
+            }
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < A; ++s) u[s] = C{(R)re[s], (R)im[s]};
+        __syncthreads();  // the coefficients are read before the next run writes its own
+        if (sub == remaining) {
+          remaining = 0.0;
+        } else {
+          remaining -= sub;
+          ++substeps;
+        }
+      }
+      const int64_t done = jb.obs_first + step + 1;
+      if (status == RSV_OK && jb.obs && done % jb.obs_every == 0)
+        occupations(sh, u, tid, jb.obs + (done / jb.obs_every - 1) * (N + 1));
+    }
+    // final state, occupations (FP64), bookkeeping
+    if (status == RSV_OK && live) {
+#pragma unroll
+      for (int s = 0; s < A; ++s) {
+        const uint32_t e = pos(tid, s);
+        if (jb.psi_out) ((C*)jb.psi_out)[e] = u[s];
+        if (jb.state) jb.state[e] = double2{(double)u[s].x, (double)u[s].y};
+      }
+    }
+    occupations(sh, u, tid, jb.out + kPackOccOffset - 1);
+    if (tid == 0) {
+      jb.out[4] = jb.out[kPackOccOffset - 1];
+      jb.out[0] = status;
+      jb.out[1] = (double)iters;
+      jb.out[2] = (double)kmax_used;
+      jb.out[3] = (double)substeps;
+    }
+  }
+};
+
+// The sizes of one launch: 2^TB threads, NLO..NHI atoms.
+template <class R, int TB, int NLO, int NHI>
+__device__ __forceinline__ void dispatch(const PackedJob& jb, const double* om, const double* de,
+                                         const double* ph, bool has_phi, Shared& sh, Cx<R>* tile,
+                                         R* cf) {
+  if constexpr (NLO <= NHI) {
+    if (jb.n == NLO && jb.real) Runner<R, NLO, TB, kCoefReal>::run(jb, om, de, ph, has_phi, sh, tile, cf);
+    else if (jb.n == NLO) Runner<R, NLO, TB, kCoefSite>::run(jb, om, de, ph, has_phi, sh, tile, cf);
+    else dispatch<R, TB, NLO + 1, NHI>(jb, om, de, ph, has_phi, sh, tile, cf);
+  }
+}
+
+template <class R> constexpr int max_bits() { return sizeof(R) == 8 ? 12 : 13; }
+constexpr int kSmallThreadBits = 8;
+// 13 atoms complex64: 36 Mcycles for a 115-step job on 1024 threads, 38 on 512; 12 atoms
+// complex128 spills its vectors on 1024.
+template <class R> constexpr int large_thread_bits() { return sizeof(R) == 8 ? 9 : 10; }
+
+template <class R, bool LARGE>
+__global__ __launch_bounds__(1 << (LARGE ? large_thread_bits<R>() : kSmallThreadBits)) void packed_kernel(const PackedJob* __restrict__ jobs) {
+  constexpr int HB = LARGE ? max_bits<R>() : kPackSmallBits;
+  __shared__ __align__(16) Cx<R> tile[1 << HB];
+  __shared__ Shared sh;
+  __shared__ R cf[2 * kMaxPackBits];
+  const PackedJob& jb = jobs[blockIdx.x];
+  if constexpr (LARGE)
+    dispatch<R, large_thread_bits<R>(), kPackSmallBits + 1, HB>(jb, jb.omega, jb.delta, jb.phi, jb.phi != nullptr, sh, tile, cf);
+  else
+    dispatch<R, kSmallThreadBits, 1, HB>(jb, jb.omega, jb.delta, jb.phi, jb.phi != nullptr, sh, tile, cf);
+}
+
+struct SmallArgs {
+  PackedJob job;
+  int with_phi;
+  double mid[kMidValues];
+};
+static_assert(sizeof(SmallArgs) <= 4096, "kernel argument size");
+
+template <class R, int N, int TB, int MODE>
+__global__ __launch_bounds__(1 << TB) void small_kernel(const SmallArgs a) {
+  __shared__ __align__(16) Cx<R> tile[N < TB ? (1 << TB) : (1 << N)];
+  __shared__ Shared sh;
+  __shared__ R cf[2 * kMaxPackBits];
+  __shared__ double mid[kMidValues];
+  for (int i = threadIdx.x; i < kMidValues; i += 1 << TB) mid[i] = a.mid[i];
   __syncthreads();
-  return K != -2;
+  const int cnt = (int)a.job.n_steps * (a.job.per_site ? N : 1);
+  Runner<R, N, TB, MODE>::run(a.job, mid, mid + cnt, mid + 2 * cnt, a.with_phi != 0, sh, tile, cf);
+}
+
+template <class R, int N>
+hipError_t small_launch(const SmallArgs& a, hipStream_t s) {
+  if constexpr (N > max_bits<R>()) {
+    return hipErrorInvalidValue;
+  } else {
+    if (a.job.n != N) return small_launch<R, N + 1>(a, s);
+    constexpr int TB = N > 11 ? large_thread_bits<R>() : (N > kPackSmallBits ? 9 : (N < 6 ? 6 : (N < 8 ? N : 8)));
+    if (a.job.real)
+      hipLaunchKernelGGL((small_kernel<R, N, TB, kCoefReal>), dim3(1), dim3(1 << TB), 0, s, a);
+    else
+      hipLaunchKernelGGL((small_kernel<R, N, TB, kCoefSite>), dim3(1), dim3(1 << TB), 0, s, a);
+    return hipGetLastError();
+  }
 }
 
 template <class R>
-__global__ __launch_bounds__(kThreads) void packed_evolve_kernel(const PackedJob* __restrict__ jobs) {
-  using C = Cx<R>;
-  constexpr int AMAX = PackGeo<R>::A;
-  __shared__ C tile[kThreads * AMAX];  // the current Krylov vector u (each thread owns tile[e])
-  __shared__ Shared sh;
-  __shared__ R cf[4 * kMaxPackBits];   // couplings of bit p: <1|h|0> re, im, <0|h|1> re, im
-  __shared__ R dg[kThreads * AMAX];    // diagonal of H_k
-  const PackedJob& jb = jobs[blockIdx.x];
-  const int n = jb.n;
-  const uint32_t dim = 1u << n;
-  const uint32_t tid = threadIdx.x;
-  const int A = dim >= (uint32_t)kThreads ? (int)(dim / kThreads) : 1;
-  C* psi = (C*)jb.psi;
-  C* basis = (C*)jb.basis;
-  const R* diag = (const R*)jb.diag;
-  auto mine = [&](int s) { return s < A && tid + kThreads * s < dim; };
-
-  C z[AMAX];  // H u of the newest Krylov vector
-  // the diagonal of H_k lives in LDS (dg[e], written and read by the thread that owns e)
-#pragma unroll
-  for (int s = 0; s < AMAX; ++s) {
-    z[s] = C{0, 0};
-    const uint32_t e = tid + kThreads * s;
-    if (mine(s)) tile[e] = jb.init_zero ? C{(R)(e == 0 ? 1 : 0), 0} : psi[e];
-  }
-  int64_t iters = 0, kmax_used = 0, substeps = 0;
-  int m_prev = 0;  // Krylov dimension of the previous Lanczos run of this job
-  int status = RSV_OK;
-  const double tau = jb.dt_ns * 1e-3;
-
-  // z = H u with u in the tile; returns Re<u, z>
-  // element s of this thread is e = tid | s << 9: bits below 9 are the thread's, the others
-  // are known at compile time in the unrolled loops
-  auto apply_h = [&]() -> double {
-    __syncthreads();
-    double dot = 0.0;
-    if (!jb.per_site) {
-      // one coupling for every atom: sum the neighbours with the bit set and all of them,
-      // then apply <1|h|0> and <0|h|1> once
-      const R ur = cf[0], ui = cf[1], dr = cf[2], di = cf[3];
-#pragma unroll
-      for (int s = 0; s < AMAX; ++s) {
-        const uint32_t e = tid | ((uint32_t)s << kThreadBits);
-        if (mine(s)) {
-          const C us = tile[e];
-          C all = {0, 0}, one = {0, 0};
-          for (int p = 0; p < n; ++p) {
-            const C nb = tile[e ^ (1u << p)];
-            all.x += nb.x;
-            all.y += nb.y;
-            if ((e >> p) & 1u) {
-              one.x += nb.x;
-              one.y += nb.y;
-            }
-          }
-          const C zr = {all.x - one.x, all.y - one.y};
-          C acc;
-          const R de = dg[e];
-          acc.x = de * us.x + (ur * one.x - ui * one.y) + (dr * zr.x - di * zr.y);
-          acc.y = de * us.y + (ur * one.y + ui * one.x) + (dr * zr.y + di * zr.x);
-          z[s] = acc;
-          dot += (double)us.x * (double)acc.x + (double)us.y * (double)acc.y;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < AMAX; ++s) {
-        const uint32_t e = tid | ((uint32_t)s << kThreadBits);
-        if (mine(s)) {
-          const C us = tile[e];
-          const R de = dg[e];
-          C acc = {de * us.x, de * us.y};
-          for (int p = 0; p < n; ++p) {
-            const C nb = tile[e ^ (1u << p)];
-            const int o = 4 * p + (((e >> p) & 1u) ? 0 : 2);
-            const R cr = cf[o], ci = cf[o + 1];
-            acc.x += cr * nb.x - ci * nb.y;
-            acc.y += cr * nb.y + ci * nb.x;
-          }
-          z[s] = acc;
-          dot += (double)us.x * (double)acc.x + (double)us.y * (double)acc.y;
-        }
-      }
-    }
-    return wg_sum(dot, sh.red);  // its barriers end every read of the tile
-  };
-  auto norm2 = [&]() -> double {
-    double acc = 0.0;
-#pragma unroll
-    for (int s = 0; s < AMAX; ++s) {
-      const uint32_t e = tid + kThreads * s;
-      if (mine(s)) acc = norm_add(acc, (double)tile[e].x, (double)tile[e].y);
-    }
-    return wg_sum(acc, sh.red);
-  };
-
-  for (int64_t step = jb.first_step; step < jb.first_step + jb.n_steps && status == RSV_OK; ++step) {
-    // coefficients of H_k by bit position p (atom n-1-p)
-    if (tid < (uint32_t)n) {
-      const int i = n - 1 - tid;
-      const size_t off = jb.per_site ? (size_t)i * jb.n_samples : 0;
-      const double om = midpoint(jb.omega + off, step, jb.dt_ns);
-      const double de = midpoint(jb.delta + off, step, jb.dt_ns);
-      const double ph = jb.phi ? midpoint(jb.phi + off, step, jb.dt_ns) : 0.0;
-      cf[4 * tid] = (R)(0.5 * om * cos(ph));
-      cf[4 * tid + 1] = (R)(-0.5 * om * sin(ph));
-      cf[4 * tid + 2] = (R)(0.5 * om * cos(ph));
-      cf[4 * tid + 3] = (R)(0.5 * om * sin(ph));
-      sh.dl[tid] = de;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < AMAX; ++s) {
-      const uint32_t e = tid + kThreads * s;
-      double v = 0.0;
-      if (mine(s)) {
-        v = (double)diag[e];
-        for (int p = 0; p < n; ++p)
-          if ((e >> p) & 1u) v -= sh.dl[p];
-      }
-      dg[e] = (R)v;
-    }
-
-    double remaining = tau;
-    while (remaining > 0.0 && status == RSV_OK) {
-      const double nrm = sqrt(norm2());
-      if (!(nrm > 0.0) || !isfinite(nrm)) {
-        status = RSV_ENUMERIC;
-        break;
-      }
-      if (tid == 0) sh.scale[0] = 1.0 / nrm;
-#pragma unroll
-      for (int s = 0; s < AMAX; ++s) {
-        const uint32_t e = tid + kThreads * s;
-        if (mine(s)) basis[e] = tile[e];
-      }
-      double dot = apply_h();  // z_0 = H u_0
-      ++iters;
-      int m = 0;
-      // target: the part of the step this basis must resolve; shortened while the
-      // exponential of the growing T_m is too wide for one Chebyshev series
-      double target = remaining, sub = remaining;
-      // the estimate is first tested two dimensions below the previous run's (every
-      // dimension on the first run): a larger m than the smallest converged one is as exact
-      const int k_test = m_prev > 3 ? m_prev - 2 : 1;
-      for (int k = 1; k <= jb.kmax; ++k) {
-        const double sk1 = sh.scale[k - 1];
-        const double alpha = sk1 * sk1 * dot;
-        const double c2 = k >= 2 ? -sh.scale[k - 2] / sk1 : 0.0;
-        // u_k = s z - alpha s u_{k-1} - (s_{k-2}/s_{k-1}) u_{k-2}, rounded once, in place
-#pragma unroll
-        for (int s = 0; s < AMAX; ++s) {
-          const uint32_t e = tid + kThreads * s;
-          if (mine(s)) {
-            const C u1 = tile[e];
-            const C u2 = k >= 2 ? basis[(size_t)(k - 2) * dim + e] : C{0, 0};
-            const double re = sk1 * (double)z[s].x - alpha * sk1 * (double)u1.x + c2 * (double)u2.x;
-            const double im = sk1 * (double)z[s].y - alpha * sk1 * (double)u1.y + c2 * (double)u2.y;
-            tile[e] = C{(R)re, (R)im};
-          }
-        }
-        const double b2 = norm2();
-        if (tid == 0) sh.alpha[k - 1] = alpha;
-        __syncthreads();
-        if (!isfinite(b2) || !isfinite(alpha)) {
-          status = RSV_ENUMERIC;
-          break;
-        }
-        const double bk = sqrt(b2);
-        m = k;
-        // the estimate meets the tolerance (always so at beta = 0, an invariant subspace)
-        auto resolved = [&]() { return bk * sh.est * nrm <= jb.tol; };
-        if (k >= k_test || k == jb.kmax || bk == 0.0) {
-          bool fits = cheb_expm(sh, m, target, false);
-          for (int h = 0; h < 64 && !fits; ++h) fits = cheb_expm(sh, m, target *= 0.5, false);
-          if (!fits) {
-            status = RSV_ENOTCONV;
-            break;
-          }
-          if (resolved()) {
-            sub = target;
-            break;
-          }
-          if (k == jb.kmax || bk == 0.0) {
-            // the longest part of the target this basis resolves: dyadic bracket, bisection
-            bool ok = false;
-            double bad = target;
-            for (int dd = 1; dd <= jb.max_depth && !ok; ++dd) {
-              sub = ldexp(target, -dd);
-              cheb_expm(sh, m, sub, false);
-              ok = resolved();
-              __syncthreads();
-              if (!ok) bad = sub;
-            }
-            if (!ok) {
-              status = RSV_ENOTCONV;
-              break;
-            }
-            for (int it = 0; it < 10; ++it) {
-              const double mid = 0.5 * (sub + bad);
-              cheb_expm(sh, m, mid, false);
-              if (resolved()) sub = mid;
-              else bad = mid;
-              __syncthreads();
-            }
-            break;
-          }
-        }
-        if (tid == 0) {
-          sh.beta[k - 1] = bk;
-          sh.scale[k] = 1.0 / bk;
-        }
-#pragma unroll
-        for (int s = 0; s < AMAX; ++s) {
-          const uint32_t e = tid + kThreads * s;
-          if (mine(s)) basis[(size_t)k * dim + e] = tile[e];
-        }
-        __syncthreads();
-        dot = apply_h();  // z_k = H u_k
-        ++iters;
-      }
-      if (status != RSV_OK) break;
-      kmax_used = max(kmax_used, (int64_t)m);
-      m_prev = m;
-      cheb_expm(sh, m, sub, true);
-      // psi <- |psi| sum_l y_l s_l u_l over this thread's own amplitudes
-#pragma unroll
-      for (int s = 0; s < AMAX; ++s) {
-        const uint32_t e = tid + kThreads * s;
-        if (mine(s)) {
-          double re = 0.0, im = 0.0;
-          for (int l = 0; l < m; ++l) {
-            const C x = basis[(size_t)l * dim + e];
-            const double cr = nrm * sh.yre[l] * sh.scale[l], ci = nrm * sh.yim[l] * sh.scale[l];
-            re += cr * (double)x.x - ci * (double)x.y;
-            im += cr * (double)x.y + ci * (double)x.x;
-          }
-          tile[e] = C{(R)re, (R)im};
-        }
-      }
-      __syncthreads();
-      if (sub == remaining) {
-        remaining = 0.0;
-      } else {
-        remaining -= sub;
-        ++substeps;
-      }
-    }
-  }
-  // final state, occupations (FP64), bookkeeping
-  double tot = 0.0, occ[kMaxPackBits];
-#pragma unroll
-  for (int p = 0; p < kMaxPackBits; ++p) occ[p] = 0.0;
-#pragma unroll
-  for (int s = 0; s < AMAX; ++s) {
-    const uint32_t e = tid + kThreads * s;
-    if (mine(s)) {
-      const C v = tile[e];
-      psi[e] = v;
-      const double pr = norm_add(0.0, (double)v.x, (double)v.y);
-      tot += pr;
-#pragma unroll
-      for (int p = 0; p < kMaxPackBits; ++p)
-        if ((e >> p) & 1u) occ[p] += pr;
-    }
-  }
-  const double total = wg_sum(tot, sh.red);
-  for (int p = 0; p < n; ++p) {
-    const double t = wg_sum(occ[p], sh.red);
-    if (tid == 0) jb.out[kPackOccOffset + p] = t;
-  }
-  if (tid == 0) {
-    jb.out[0] = status;
-    jb.out[1] = (double)iters;
-    jb.out[2] = (double)kmax_used;
-    jb.out[3] = (double)substeps;
-    jb.out[4] = total;
-  }
+hipError_t packed_r(const PackedJob* d_jobs, int n_small, int n_large, hipStream_t s_small,
+                    hipStream_t s_large) {
+  if (n_large > 0)
+    hipLaunchKernelGGL((packed_kernel<R, true>), dim3(n_large), dim3(1 << large_thread_bits<R>()), 0, s_large, d_jobs + n_small);
+  if (n_small > 0)
+    hipLaunchKernelGGL((packed_kernel<R, false>), dim3(n_small), dim3(1 << kSmallThreadBits), 0, s_small, d_jobs);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 int packed_max_atoms(int prec) { return prec == kC128 ? 12 : 13; }
 
-hipError_t packed_evolve(int prec, const PackedJob* d_jobs, int count, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  if (prec == kC128)
-    hipLaunchKernelGGL(packed_evolve_kernel<double>, dim3(count), dim3(kThreads), 0, s, d_jobs);
-  else
-    hipLaunchKernelGGL(packed_evolve_kernel<float>, dim3(count), dim3(kThreads), 0, s, d_jobs);
-  return hipGetLastError();
+bool packed_resolves(double tau, double half_width) {
+  // T_m's diagonal lies in H's spectrum and its couplings are at most the half-width, so its
+  // Gershgorin half-width is at most three times that
+  const double a = 3.0 * tau * half_width;
+  return a + 8.0 * std::cbrt(a) + 20.0 < kMaxBessel - 2;
+}
+
+hipError_t packed_evolve(int prec, const PackedJob* d_jobs, int n_small, int n_large,
+                         hipStream_t s_small, hipStream_t s_large) {
+  return prec == kC128 ? packed_r<double>(d_jobs, n_small, n_large, s_small, s_large)
+                       : packed_r<float>(d_jobs, n_small, n_large, s_small, s_large);
+}
+
+hipError_t small_evolve(int prec, const PackedJob& job, const double* mid, bool with_phi,
+                        hipStream_t s) {
+  SmallArgs a;
+  a.job = job;
+  a.with_phi = with_phi ? 1 : 0;
+  const int64_t cnt = job.n_steps * (job.per_site ? job.n : 1) * (with_phi ? 3 : 2);
+  if (job.n_steps < 1 || cnt > kMidValues) return hipErrorInvalidValue;
+  std::memcpy(a.mid, mid, (size_t)cnt * sizeof(double));
+  std::memset(a.mid + cnt, 0, (kMidValues - (size_t)cnt) * sizeof(double));
+  return prec == kC128 ? small_launch<double, 1>(a, s) : small_launch<float, 1>(a, s);
 }
 
 }  // namespace rsv

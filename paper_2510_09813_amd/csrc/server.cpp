@@ -10,8 +10,8 @@
 //
 // Small jobs are packed: a lane takes every queued small job of one precision (up to the
 // batch limit and its pinned staging size) as one arena block, uploads all their inputs
-// with one copy, builds each diagonal, runs them in one launch of the packed kernel (one
-// workgroup per job) and downloads all outputs with one copy.  With packing on, one lane
+// with one copy, runs them in one launch of the packed kernel per size class (one workgroup per
+// job) and downloads all outputs with one copy.  With packing on, one lane
 // beyond n_lanes takes only packed batches, so small jobs never queue behind long jobs that
 // hold every regular lane.
 #include <hip/hip_runtime.h>
@@ -249,20 +249,19 @@ void free_completion(rsv_completion& c) {
 
 // ---------------------------------------------------------------------- packed batches
 
-size_t pulse_count(const Job& j) {
-  return (size_t)j.pulses.n_samples * (j.pulses.per_site ? (size_t)j.n : 1);
-}
+// Midpoint values a packed job uploads per pulse array.
+size_t step_count(const Job& j) { return (size_t)j.n_steps * (j.pulses.per_site ? (size_t)j.n : 1); }
 
-// Footprint of a packed job: uploaded (U, pulses, initial state), downloaded (status and
-// occupations, samples, final state) and device-only (diagonal, state, Krylov basis,
+// Footprint of a packed job: uploaded (U, midpoint values, initial state), downloaded (status
+// and occupations, samples, final state) and device-only (diagonal, state, Krylov basis,
 // sampling scratch).
 void packed_sizes(Job& j) {
-  const size_t dim = size_t(1) << j.n, cnt = pulse_count(j);
+  const size_t dim = size_t(1) << j.n, cnt = step_count(j);
   j.up = granule(32 * 32 * 8) + 2 * granule(cnt * 8) + (j.phi.empty() ? 0 : granule(cnt * 8)) +
          (j.psi0.empty() ? 0 : granule(dim * 16));
   j.down = granule(kPackOutDoubles * 8) + granule((size_t)j.shots * 8) +
            (j.return_state ? granule(dim * 16) : 0);
-  j.work = granule(dim * (j.prec == kC128 ? 8 : 4)) + granule(vec_bytes(j.n, j.prec)) +
+  j.work = granule(dim * 8) + granule(vec_bytes(j.n, j.prec)) +
            granule((size_t)j.opts.kmax * vec_bytes(j.n, j.prec)) +
            (j.shots > 0 ? granule((size_t)sample_scratch_doubles(j.n) * 8) : 0);
 }
@@ -347,6 +346,8 @@ bool take_work(rsv_server* srv, std::unique_lock<std::mutex>& lk, Work& w, bool 
 
 struct LaneBuffers {
   hipStream_t stream = nullptr;
+  hipStream_t side = nullptr;  // a packed batch's smaller jobs, beside its larger ones
+  hipEvent_t fork = nullptr, join = nullptr;
   double* h_pinned = nullptr;  // 512 doubles of per-iteration scalars
   char* h_up = nullptr;        // packed staging, kPackStage bytes each
   char* h_down = nullptr;
@@ -365,8 +366,9 @@ struct PackedSlot {
   int status;  // RSV_OK, or an input error found on the host
 };
 
-// Runs a packed batch: one upload, per-job diagonal builds, one packed launch, per-job
-// samples and state exports, one download.  Completions are appended to `out`.
+// Runs a packed batch: one upload, one launch for its larger and one for its smaller jobs (on
+// two streams, so that they overlap), per-job samples, one download.  Completions are appended
+// to `out`.
 int run_batch(rsv_server* srv, Work& w, LaneBuffers& lb, std::vector<rsv_completion>& out,
               double t_start) {
   const size_t count = w.jobs.size();
@@ -382,13 +384,24 @@ int run_batch(rsv_server* srv, Work& w, LaneBuffers& lb, std::vector<rsv_complet
   char* down_base = up_base + up_total;
   char* work_base = down_base + down_total;
   std::vector<PackedSlot> slot(count);
-  PackedJob* desc = (PackedJob*)lb.h_up;
+  PackedJob* desc = (PackedJob*)lb.h_up;  // small jobs first (see packed_evolve)
   size_t uo = granule(count * sizeof(PackedJob)), dw = 0, wo = 0;
-  int launched = 0;
+  std::vector<PackedJob> large;
+  int n_small = 0;
   for (size_t i = 0; i < count; ++i) {
     Job* j = w.jobs[i];
     PackedSlot& sl = slot[i];
-    const size_t dim = size_t(1) << j->n, cnt = pulse_count(*j);
+    const size_t dim = size_t(1) << j->n, cnt = step_count(*j);
+    auto take_mid = [&](const double* x) {
+      double* dst = (double*)(lb.h_up + uo);
+      const size_t rows = j->pulses.per_site ? (size_t)j->n : 1;
+      for (size_t r = 0; r < rows; ++r)
+        step_midpoints(x + r * j->pulses.n_samples, j->first_step, j->n_steps, j->opts.dt_ns,
+                       dst + r * j->n_steps);
+      double* dev = (double*)(up_base + uo);
+      uo += granule(cnt * 8);
+      return dev;
+    };
     auto take_up = [&](size_t bytes, const void* src) {
       std::memcpy(lb.h_up + uo, src, bytes);
       void* dev = up_base + uo;
@@ -399,9 +412,9 @@ int run_batch(rsv_server* srv, Work& w, LaneBuffers& lb, std::vector<rsv_complet
     sl.status = build_interactions(j->n, j->xyz.data(), j->c6, (double*)(lb.h_up + uo));
     sl.ub = (double*)(up_base + uo);
     uo += granule(32 * 32 * 8);
-    sl.omega = (double*)take_up(cnt * 8, j->omega.data());
-    sl.delta = (double*)take_up(cnt * 8, j->delta.data());
-    sl.phi = j->phi.empty() ? nullptr : (double*)take_up(cnt * 8, j->phi.data());
+    sl.omega = take_mid(j->omega.data());
+    sl.delta = take_mid(j->delta.data());
+    sl.phi = j->phi.empty() ? nullptr : take_mid(j->phi.data());
     sl.psi0 = j->psi0.empty() ? nullptr : take_up(dim * 16, j->psi0.data());
     sl.down_off = dw;
     sl.out = (double*)(down_base + dw);
@@ -411,7 +424,7 @@ int run_batch(rsv_server* srv, Work& w, LaneBuffers& lb, std::vector<rsv_complet
     sl.state = j->return_state ? down_base + dw : nullptr;
     dw += j->return_state ? granule(dim * 16) : 0;
     sl.diag = work_base + wo;
-    wo += granule(dim * (prec == kC128 ? 8 : 4));
+    wo += granule(dim * 8);
     sl.psi = work_base + wo;
     wo += granule(vec_bytes(j->n, prec));
     sl.basis = work_base + wo;
@@ -419,50 +432,47 @@ int run_batch(rsv_server* srv, Work& w, LaneBuffers& lb, std::vector<rsv_complet
     sl.scratch = (double*)(work_base + wo);
     wo += j->shots > 0 ? granule((size_t)sample_scratch_doubles(j->n) * 8) : 0;
     if (sl.status != RSV_OK) continue;
-    PackedJob& d = desc[launched++];
+    PackedJob d{};
     d.n = j->n;
-    d.dt_ns = j->opts.dt_ns;
     d.kmax = j->opts.kmax;
     d.max_depth = j->opts.max_substep_depth;
     d.per_site = j->pulses.per_site;
-    d.init_zero = j->psi0.empty() ? 1 : 0;
-    d.first_step = j->first_step;
+    d.real = !d.per_site && j->phi.empty();
+    d.dir = 1.0;
     d.n_steps = j->n_steps;
-    d.n_samples = j->pulses.n_samples;
+    d.tau = j->opts.dt_ns * 1e-3;
     d.tol = j->opts.tol;
     d.omega = sl.omega;
     d.delta = sl.delta;
     d.phi = sl.phi;
-    d.diag = sl.diag;
-    d.psi = sl.psi;
+    d.ub = sl.ub;
+    d.diag = (double*)sl.diag;
+    d.psi0 = (const double2*)sl.psi0;
+    d.psi_out = j->shots > 0 ? sl.psi : nullptr;
+    d.state = (double2*)sl.state;
     d.basis = sl.basis;
     d.out = sl.out;
+    if (d.n <= kPackSmallBits) desc[n_small++] = d;
+    else large.push_back(d);
   }
+  const int n_large = (int)large.size();
+  for (int i = 0; i < n_large; ++i) desc[n_small + i] = large[i];
   HIP_TRY(hipMemcpyAsync(up_base, lb.h_up, up_total, hipMemcpyHostToDevice, s));
-  for (size_t i = 0; i < count; ++i) {
-    const PackedSlot& sl = slot[i];
-    const Job* j = w.jobs[i];
-    if (sl.status != RSV_OK) continue;
-    HIP_TRY(diag_build(prec, j->n, sl.ub, sl.diag, s));
-    if (sl.psi0) {
-      if (prec == kC128)
-        HIP_TRY(hipMemcpyAsync(sl.psi, sl.psi0, (size_t(1) << j->n) * 16, hipMemcpyDeviceToDevice, s));
-      else
-        HIP_TRY(convert_from_c128(prec, j->n, sl.psi0, sl.psi, s));
-    }
+  const bool both = n_small > 0 && n_large > 0;
+  if (both) {
+    HIP_TRY(hipEventRecord(lb.fork, s));
+    HIP_TRY(hipStreamWaitEvent(lb.side, lb.fork, 0));
   }
-  HIP_TRY(packed_evolve(prec, (const PackedJob*)up_base, launched, s));
+  HIP_TRY(packed_evolve(prec, (const PackedJob*)up_base, n_small, n_large, both ? lb.side : s, s));
+  if (both) {
+    HIP_TRY(hipEventRecord(lb.join, lb.side));
+    HIP_TRY(hipStreamWaitEvent(s, lb.join, 0));
+  }
   for (size_t i = 0; i < count; ++i) {
     const PackedSlot& sl = slot[i];
     const Job* j = w.jobs[i];
     if (sl.status != RSV_OK) continue;
     if (j->shots > 0) HIP_TRY(sample(prec, j->n, sl.psi, j->seed, j->shots, sl.scratch, sl.idx, s));
-    if (sl.state) {
-      if (prec == kC128)
-        HIP_TRY(hipMemcpyAsync(sl.state, sl.psi, (size_t(1) << j->n) * 16, hipMemcpyDeviceToDevice, s));
-      else
-        HIP_TRY(convert_to_c128(prec, j->n, sl.psi, sl.state, s));
-    }
   }
   if (down_total) HIP_TRY(hipMemcpyAsync(lb.h_down, down_base, down_total, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -525,7 +535,10 @@ void lane_main(rsv_server* srv, bool packed_only) {
             hipHostMalloc((void**)&lb.h_pinned, 512 * sizeof(double), hipHostMallocDefault) ==
                 hipSuccess;
   if (ok && srv->opts.pack_max_atoms > 0)
-    ok = hipHostMalloc((void**)&lb.h_up, kPackStage, hipHostMallocDefault) == hipSuccess &&
+    ok = hipStreamCreateWithFlags(&lb.side, hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&lb.fork, hipEventDisableTiming) == hipSuccess &&
+         hipEventCreateWithFlags(&lb.join, hipEventDisableTiming) == hipSuccess &&
+         hipHostMalloc((void**)&lb.h_up, kPackStage, hipHostMallocDefault) == hipSuccess &&
          hipHostMalloc((void**)&lb.h_down, kPackStage, hipHostMallocDefault) == hipSuccess;
   for (;;) {
     Work w;
@@ -576,6 +589,7 @@ void lane_main(rsv_server* srv, bool packed_only) {
     // drain before its memory goes back to the arena
     bool failed = false;
     for (const rsv_completion& c : comps) failed |= c.status != RSV_OK;
+    if (failed && lb.side) (void)hipStreamSynchronize(lb.side);
     if (failed && lb.stream) (void)hipStreamSynchronize(lb.stream);
     srv->arena.release(w.block, w.bytes);
     for (Job* j : w.jobs) delete j;
@@ -587,6 +601,9 @@ void lane_main(rsv_server* srv, bool packed_only) {
     srv->cv_done.notify_all();
     srv->cv_work.notify_all();  // memory was released: queued jobs may fit now
   }
+  if (lb.side) (void)hipStreamDestroy(lb.side);
+  if (lb.fork) (void)hipEventDestroy(lb.fork);
+  if (lb.join) (void)hipEventDestroy(lb.join);
   if (lb.stream) (void)hipStreamDestroy(lb.stream);
   if (lb.h_pinned) (void)hipHostFree(lb.h_pinned);
   if (lb.h_up) (void)hipHostFree(lb.h_up);
