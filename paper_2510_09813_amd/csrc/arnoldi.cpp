@@ -1,4 +1,10 @@
 // Arnoldi Krylov exponential on device vectors, driven from the host (see arnoldi.h).
+//
+// Iterations are queued several at a time (as many as the previous run took, or as the decay of
+// the a-priori estimate suggests) and their Hessenberg columns fetched together; the host then
+// goes through them in order.  What it decides (a second Gram-Schmidt pass, the dimension that
+// meets the tolerance) depends on the columns alone, not on how they were queued: columns after a
+// vector that needs a second pass are computed again, columns beyond the final dimension ignored.
 #include "arnoldi.h"
 
 #include <algorithm>
@@ -11,165 +17,260 @@ namespace {
 
 using cd = std::complex<double>;
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
-constexpr int kScal = 2 * kMaxKrylov + 8;
 
-int fetch(ArnoldiSpace& sp, int count, hipStream_t s, double* out) {
-  HIP_TRY(hipMemcpyAsync(sp.h_scal, sp.dscal, count * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  std::memcpy(out, sp.h_scal, count * sizeof(double));
-  return RSV_OK;
-}
+// dscal: |u_i|^2, the second pass's inner products, then column j's 2 (j + 2) values.
+constexpr size_t kNorms = kMaxKrylov + 2, kAgain = kNorms, kCols = kNorms + 2 * (kMaxKrylov + 2);
+inline size_t col_off(int j) { return kCols + (size_t)j * j + 3 * (size_t)j; }
 
-// |x|^2 of a vector of the space.
-int norm2(ArnoldiSpace& sp, const void* x, hipStream_t s, double* out) {
-  HIP_TRY(norm2_partial(sp.prec, sp.nb, x, sp.partial, s));
-  HIP_TRY(finalize_sum(sp.partial, vec_num_partials(sp.prec, sp.nb), sp.dscal, s));
-  return fetch(sp, 1, s, out);
-}
+struct Run {
+  const OpFn& op;
+  ArnoldiSpace& sp;
+  void* d_x;
+  hipStream_t s;
+  rsv_stats* st;
+  size_t count;
+  bool small;
+  int parts;
 
-// <u_i, y> for i < k (Re, Im interleaved into dots[2 i], dots[2 i + 1]).
-// <u_i, y> for i < k, and <y, y> after them when self_dot (in the same sweeps over y).
-int dots_against(ArnoldiSpace& sp, int k, const void* y, hipStream_t s, double* dots,
-                 bool self_dot = false) {
-  const int64_t nw = vec_num_partials(sp.prec, sp.nb);
-  const int total = k + (self_dot ? 1 : 0);
-  for (int i0 = 0; i0 < total; i0 += kDotGroup) {
-    DotGroup d{};
-    d.g = std::min(kDotGroup, total - i0);
-    for (int g = 0; g < d.g; ++g) d.x[g] = i0 + g < k ? sp.vec[i0 + g] : y;
-    HIP_TRY(multi_dot(sp.prec, sp.nb, d, y, sp.partial, s));
-    HIP_TRY(finalize_rows(sp.partial, nw, 2 * d.g, sp.dscal + 2 * i0, s));
+  void* vec(int i) const { return i == 0 ? d_x : (void*)(sp.base + (size_t)i * sp.vb); }
+
+  ArnoldiStep step(int j, bool again) const {
+    ArnoldiStep a{};
+    a.j = j;
+    a.again = again;
+    a.v0 = d_x;
+    a.base = sp.base;
+    a.stride = sp.vb / amp_bytes(sp.prec);
+    a.count = count;
+    a.w = again ? vec(j + 1) : (void*)sp.base;
+    a.nrm2 = sp.dscal;
+    a.npart = sp.npart;
+    a.nparts = !again && small && j > 0 ? parts : 0;
+    a.part = sp.part;
+    a.dparts = small ? parts : 0;
+    a.dots = sp.dscal + (again ? kAgain : col_off(j));
+    a.npart_out = sp.npart;
+    return a;
   }
-  return fetch(sp, 2 * total, s, dots);
-}
-
-int expm_once(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol, hipStream_t s,
-              rsv_stats* st, bool* converged) {
-  const int kmax = sp.kmax;
-  std::vector<void*>& v = sp.vec;
-  void* w = v[kmax + 1];
-  void* t = v[kmax + 2];
-  const size_t vb = (size_t(1) << sp.nb) * amp_bytes(sp.prec);
-  double nx2 = 0.0;
-  RSV_TRY(norm2(sp, d_x, s, &nx2));
-  const double nx = std::sqrt(nx2);
-  *converged = true;
-  if (!std::isfinite(nx)) return fail(RSV_ENUMERIC, "state norm is not finite");
-  if (nx == 0.0) return RSV_OK;
-  HIP_TRY(hipMemcpyAsync(v[0], d_x, vb, hipMemcpyDeviceToDevice, s));
-  std::vector<double> scale(kmax + 2, 0.0);
-  scale[0] = 1.0 / nx;
-  std::vector<cd> h((size_t)(kmax + 1) * kmax, 0.0);  // h[i * kmax + j], i <= j + 1
-  auto H = [&](int i, int j) -> cd& { return h[(size_t)i * kmax + j]; };
-  std::vector<cd> hm, e;
-  std::vector<double> dots(2 * kMaxKrylov + 2);
-  int m = 0;
-  for (int j = 0; j < kmax; ++j) {
-    RSV_TRY(op(v[j], w, s));  // w = Op u_j, v_j = s_j u_j
+  // One Gram-Schmidt pass; long vectors sum their partials in launches of their own.
+  int orthogonalise(int j, bool again) {
+    const ArnoldiStep a = step(j, again);
+    HIP_TRY(arnoldi_dots(sp.prec, a, s));
+    if (!small) HIP_TRY(finalize_rows(sp.part, parts, 2 * (j + 2), a.dots, s));
+    HIP_TRY(arnoldi_update(sp.prec, a, s));
+    if (!small) HIP_TRY(finalize_sum(sp.npart, parts, sp.dscal + j + 1, s));
+    return RSV_OK;
+  }
+  int iterate(int j) {
+    RSV_TRY(op(vec(j), sp.base, s));
     st->krylov_iters += 1;
-    // y = Op v_j = s_j w, orthogonalised against v_0..v_j by classical Gram-Schmidt; the first
-    // pass applies s_j, so every stored vector has the size of a Hessenberg entry (no growth
-    // by |Op|^j, which would overflow complex64 storage).  A second pass runs only when the
-    // first removed most of y: |y'| < |y| / sqrt(2) (the criterion of Daniel, Gragg, Kaufman
-    // and Stewart, 1976), the case where rounding in y' is no longer small against y'.
-    double y2 = 0.0, beta2 = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-      const double f = pass == 0 ? scale[j] : 1.0;
-      RSV_TRY(dots_against(sp, j + 1, w, s, dots.data(), pass == 0));
-      if (pass == 0) y2 = f * f * dots[2 * (j + 1)];
-      CombineCoef cc;
-      std::memset(&cc, 0, sizeof cc);
-      cc.m = j + 2;
-      cc.re[0] = f;
-      cc.x[0] = w;
-      for (int i = 0; i <= j; ++i) {
-        const cd d(dots[2 * i], dots[2 * i + 1]);
-        if (!std::isfinite(d.real()) || !std::isfinite(d.imag()))
-          return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
-        H(i, j) += f * scale[i] * d;           // <v_i, y>
-        const cd c = -f * scale[i] * scale[i] * d;  // y - v_i <v_i, y>
-        cc.re[i + 1] = c.real();
-        cc.im[i + 1] = c.imag();
-        cc.x[i + 1] = v[i];
-      }
-      HIP_TRY(krylov_combine(sp.prec, sp.nb, cc, t, sp.partial, s));
-      std::swap(w, t);
-      HIP_TRY(finalize_sum(sp.partial, vec_num_partials(sp.prec, sp.nb), sp.dscal, s));
-      RSV_TRY(fetch(sp, 1, s, &beta2));
-      if (!std::isfinite(beta2)) return fail(RSV_ENUMERIC, "Arnoldi residual not finite");
-      if (pass == 0 && beta2 >= 0.5 * y2) break;
-    }
-    // the scratch slots keep naming the two buffers that are not basis vectors, whichever
-    // way the passes swapped them (the next call takes its scratch from these slots)
-    v[kmax + 1] = w;
-    v[kmax + 2] = t;
-    const double beta = std::sqrt(std::max(beta2, 0.0));
-    H(j + 1, j) = beta;  // h_{j+1,j} = |y - sum_i v_i <v_i, y>|
-    m = j + 1;
-    hm.assign((size_t)m * m, 0.0);
-    for (int r = 0; r < m; ++r)
-      for (int c = 0; c < m; ++c) hm[(size_t)r * m + c] = tau * H(r, c);
-    e.assign((size_t)m * m, 0.0);
-    if (dense_expm(m, hm.data(), e.data()) != 0)
-      return fail(RSV_ENUMERIC, "Hessenberg exponential failed (m = %d)", m);
-    const double est = nx * std::abs(H(j + 1, j)) * std::abs(e[(size_t)(m - 1) * m]);
-    const bool done = !(est > tol) || beta == 0.0;
-    if (done || j + 1 == kmax) {
-      if (!done) {
-        *converged = false;
-        return RSV_OK;
-      }
-      st->krylov_max = std::max<int64_t>(st->krylov_max, m);
-      CombineCoef cc;
-      std::memset(&cc, 0, sizeof cc);
-      cc.m = m;
-      for (int l = 0; l < m; ++l) {
-        const cd y = nx * scale[l] * e[(size_t)l * m];
-        cc.re[l] = y.real();
-        cc.im[l] = y.imag();
-        cc.x[l] = v[l];
-      }
-      HIP_TRY(krylov_combine(sp.prec, sp.nb, cc, d_x, sp.partial, s));
-      return RSV_OK;
-    }
-    scale[j + 1] = 1.0 / beta;
-    std::swap(v[j + 1], v[kmax + 1]);  // the orthogonalised residual becomes u_{j+1}
-    w = v[kmax + 1];
+    return orthogonalise(j, false);
   }
-  *converged = false;
-  return RSV_OK;
-}
+  // |u_upto|^2 and everything up to column upto - 1 (or the second pass's inner products).
+  int fetch(int upto) {
+    if (small) HIP_TRY(finalize_sum(sp.npart, parts, sp.dscal + upto, s));
+    HIP_TRY(hipMemcpyAsync(sp.h_scal, sp.dscal, col_off(upto) * sizeof(double),
+                           hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    return RSV_OK;
+  }
+};
 
-int expm_depth(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol, int depth,
-               int max_depth, hipStream_t s, rsv_stats* st) {
-  bool ok = false;
-  RSV_TRY(expm_once(op, sp, d_x, tau, tol, s, st, &ok));
-  if (ok) return RSV_OK;
-  if (depth >= max_depth)
-    return fail(RSV_ENOTCONV, "Arnoldi exponential not converged with kmax = %d", sp.kmax);
-  st->substeps += 1;
-  RSV_TRY(expm_depth(op, sp, d_x, 0.5 * tau, tol, depth + 1, max_depth, s, st));
-  return expm_depth(op, sp, d_x, 0.5 * tau, tol, depth + 1, max_depth, s, st);
+// The a-priori course of the estimate |x| h_{k+1,k} |[exp(tau H_k) e_1]_k|, in log2: at most
+// lead_k = |x| h_{k+1,k} prod_{i<k} tau h_{i+1,i} / (k-1)!, and for a spectrum of half-width a /
+// tau below that by about exp(-a^2 / 4k).  The first test takes the Gershgorin half-width (up to
+// twice the true one), later ones half of it, relative to the last value found.
+struct Course {
+  double tau, lead = 0.0, lo = 1e300, hi = -1e300, below = 0.0, last = 0.0, off = -10.0;
+  bool tested = false;
+  int k = 0;
+  void start(double t, double nx) {
+    *this = Course{};
+    tau = t;
+    lead = std::log2(nx);
+  }
+  // row k - 1 of H_k: its diagonal entry and the entry below it
+  void add(const cd& diag, double beta) {
+    ++k;
+    lo = std::min(lo, diag.imag() - below - beta);
+    hi = std::max(hi, diag.imag() + below + beta);
+    if (k > 1) lead += std::log2(tau * below / (k - 1));
+    below = beta;
+  }
+  double value(bool tight, int at, double l) const {
+    const double a = 0.5 * tau * (hi - lo) * (tight ? 0.5 : 1.0);
+    return l + std::log2(std::max(below, 1e-300)) - 0.3607 * a * a / at;
+  }
+  bool due(double log2_tol) const { return !(value(tested, k, lead) + off > log2_tol); }
+  void found(double est) {
+    off = std::log2(std::max(est, 1e-300)) - value(true, k, lead) - 2.0;
+    tested = true;
+  }
+  // iterations until a test is due, were the couplings to stay as they are
+  int ahead(double log2_tol, int most) const {
+    double l = lead;
+    for (int n = 1; n < most; ++n) {
+      l += std::log2(std::max(tau * below / (k + n - 1), 1e-300));
+      if (!(value(tested, k + n, l) + off > log2_tol)) return n;
+    }
+    return std::max(1, most);
+  }
+};
+
+// x <- exp(sub Op) x for the largest sub <= tau found that kmax vectors resolve.
+int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol, int max_depth,
+              hipStream_t s, rsv_stats* st, double* sub) {
+  const int kmax = sp.kmax;
+  const size_t count = size_t(1) << sp.nb;
+  Run run{op, sp, d_x, s, st, count, count <= (size_t(1) << kSmallBits), arnoldi_parts(count)};
+  *sub = tau;
+  HIP_TRY(norm2_partial(sp.prec, sp.nb, d_x, sp.part, s));
+  HIP_TRY(finalize_sum(sp.part, vec_num_partials(sp.prec, sp.nb), sp.dscal, s));
+  std::vector<cd> h((size_t)(kmax + 1) * kmax, 0.0), y(kmax);  // h[i * kmax + j], i <= j + 1
+  auto H = [&](int i, int j) -> cd& { return h[(size_t)i * kmax + j]; };
+  std::vector<double> scale(kmax + 1, 0.0);
+  const double* sc = sp.h_scal;
+  const double log2_tol = std::log2(tol);
+  Course course;
+  double nx = 0.0;
+  // an iteration too many costs a long vector more than a round trip
+  int next = sp.hint > 0 ? (run.small ? sp.hint : sp.hint - 1) : 6;
+  int m = 0;            // columns gone through
+  bool careful = false;  // a second pass was needed: go on one iteration at a time
+  auto finish = [&](int dim, double part) -> int {
+    sp.hint = dim;
+    st->krylov_max = std::max<int64_t>(st->krylov_max, dim);
+    CombineCoef cc;
+    std::memset(&cc, 0, sizeof cc);
+    cc.m = dim;
+    for (int l = 0; l < dim; ++l) {
+      const cd c = nx * scale[l] * y[l];
+      cc.re[l] = c.real();
+      cc.im[l] = c.imag();
+      cc.x[l] = run.vec(l);
+    }
+    *sub = part;
+    HIP_TRY(krylov_combine(sp.prec, sp.nb, cc, d_x, sp.part, s));
+    return RSV_OK;
+  };
+  for (;;) {
+    const int upto = std::min(kmax, m + std::max(1, careful ? 1 : next));
+    for (int j = m; j < upto; ++j) RSV_TRY(run.iterate(j));
+    RSV_TRY(run.fetch(upto));
+    if (m == 0) {
+      nx = std::sqrt(sc[0]);
+      if (!std::isfinite(nx)) return fail(RSV_ENUMERIC, "state norm is not finite");
+      if (nx == 0.0) return RSV_OK;
+      scale[0] = 1.0 / nx;
+      course.start(tau, nx);
+    }
+    for (int j = m; j < upto; ++j) {
+      const double* d = sc + col_off(j);
+      const double y2 = d[2 * (j + 1)];
+      double beta2 = sc[j + 1];
+      for (int i = 0; i <= j; ++i) {
+        if (!std::isfinite(d[2 * i]) || !std::isfinite(d[2 * i + 1]))
+          return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
+        H(i, j) = scale[i] * cd(d[2 * i], d[2 * i + 1]);  // <v_i, y1>
+      }
+      if (j > 0) H(j - 1, j) -= 1.0 / scale[j];  // y = y1 - beta_{j-1} v_{j-1}
+      if (!std::isfinite(beta2)) return fail(RSV_ENUMERIC, "Arnoldi residual not finite");
+      bool again = false;
+      if (!(beta2 >= 0.5 * y2)) {
+        // the first pass removed most of the vector (|y'| < |y1| / sqrt(2), the criterion of
+        // Daniel, Gragg, Kaufman and Stewart, 1976): rounding in what is left is no longer small
+        // against it, so orthogonalise it once more
+        again = careful = true;
+        RSV_TRY(run.orthogonalise(j, true));
+        RSV_TRY(run.fetch(j + 1));
+        for (int i = 0; i <= j; ++i) {
+          const cd d2(sc[kAgain + 2 * i], sc[kAgain + 2 * i + 1]);
+          if (!std::isfinite(d2.real()) || !std::isfinite(d2.imag()))
+            return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
+          H(i, j) += scale[i] * d2;
+        }
+        beta2 = sc[j + 1];
+        if (!std::isfinite(beta2)) return fail(RSV_ENUMERIC, "Arnoldi residual not finite");
+      }
+      const double beta = std::sqrt(std::max(beta2, 0.0));
+      H(j + 1, j) = beta;  // h_{j+1,j} = |y - sum_i v_i <v_i, y>|
+      m = j + 1;
+      scale[m] = 1.0 / beta;
+      course.add(H(j, j), beta);
+      if (m == kmax || beta == 0.0 || course.due(log2_tol)) {
+        auto estimate = [&](double t, double* est) -> int {
+          if (hess_expm_e1(m, h.data(), kmax, t, y.data()) != 0)
+            return fail(RSV_ENUMERIC, "Hessenberg exponential failed (m = %d)", m);
+          *est = nx * beta * std::abs(y[m - 1]);
+          return RSV_OK;
+        };
+        double est = 0.0;
+        RSV_TRY(estimate(tau, &est));
+        if (!(est > tol) || beta == 0.0) return finish(m, tau);
+        course.found(est);
+        if (m == kmax) {
+          // the longest part of the step this basis resolves (same operator, so the split is
+          // exact): the estimate grows like the m-th power of the time
+          const double least = std::ldexp(tau, -max_depth);
+          double t = tau;
+          while (est > tol) {
+            if (!(t > least))
+              return fail(RSV_ENOTCONV, "Arnoldi exponential not converged with kmax = %d", kmax);
+            const double r = std::pow(0.5 * tol / est, 1.0 / m);
+            t = std::max(least, t * std::min(0.95, std::max(0.5, r)));
+            RSV_TRY(estimate(t, &est));
+          }
+          st->substeps += 1;
+          return finish(m, t);
+        }
+      }
+      if (again) break;  // what was queued after this vector used its first form
+    }
+    next = course.ahead(log2_tol, kmax - m);
+    if (!course.tested && !run.small) next = std::max(1, next - 2);
+  }
 }
 
 }  // namespace
 
+size_t arnoldi_host_doubles() { return col_off(kMaxKrylov); }
+
+int arnoldi_host(rsv_register* reg, double** out) {
+  if (!reg->h_arnoldi) {
+    const hipError_t e = hipHostMalloc((void**)&reg->h_arnoldi, arnoldi_host_doubles() * sizeof(double),
+                                       hipHostMallocDefault);
+    if (e != hipSuccess) {
+      reg->h_arnoldi = nullptr;
+      return fail(RSV_EDEVICE, "hipHostMalloc failed: %s", hipGetErrorString(e));
+    }
+  }
+  *out = reg->h_arnoldi;
+  return RSV_OK;
+}
+
+static size_t part_doubles(int prec, int nb, int kmax) {
+  const size_t rows = (size_t)2 * (kmax + 2) * arnoldi_parts(size_t(1) << nb);
+  return std::max(rows, (size_t)vec_num_partials(prec, nb));
+}
+
 size_t arnoldi_device_bytes(int prec, int nb, int kmax) {
   const size_t vb = up256((size_t(1) << nb) * amp_bytes(prec));
-  const size_t part = up256((size_t)2 * kDotGroup * vec_num_partials(prec, nb) * sizeof(double));
-  return (size_t)(kmax + 3) * vb + part + up256(kScal * sizeof(double));
+  return (size_t)(kmax + 1) * vb + up256(part_doubles(prec, nb, kmax) * sizeof(double)) +
+         up256(arnoldi_parts(size_t(1) << nb) * sizeof(double)) +
+         up256(arnoldi_host_doubles() * sizeof(double));
 }
 
 void arnoldi_carve(void* block, double* h_scal, int prec, int nb, int kmax, ArnoldiSpace* sp) {
-  const size_t vb = up256((size_t(1) << nb) * amp_bytes(prec));
-  char* p = (char*)block;
   sp->prec = prec;
   sp->nb = nb;
   sp->kmax = kmax;
-  sp->vec.assign(kmax + 3, nullptr);
-  for (int i = 0; i < kmax + 3; ++i, p += vb) sp->vec[i] = p;
-  sp->partial = (double*)p;
-  p += up256((size_t)2 * kDotGroup * vec_num_partials(prec, nb) * sizeof(double));
+  sp->vb = up256((size_t(1) << nb) * amp_bytes(prec));
+  sp->base = (char*)block;
+  char* p = (char*)block + (size_t)(kmax + 1) * sp->vb;
+  sp->part = (double*)p;
+  p += up256(part_doubles(prec, nb, kmax) * sizeof(double));
+  sp->npart = (double*)p;
+  p += up256(arnoldi_parts(size_t(1) << nb) * sizeof(double));
   sp->dscal = (double*)p;
   sp->h_scal = h_scal;
 }
@@ -177,7 +278,12 @@ void arnoldi_carve(void* block, double* h_scal, int prec, int nb, int kmax, Arno
 int arnoldi_expm(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol,
                  int max_depth, hipStream_t s, rsv_stats* st) {
   if (sp.kmax < 2 || sp.kmax > kMaxKrylov - 1) return fail(RSV_EINVAL, "kmax must be in 2..%d", kMaxKrylov - 1);
-  return expm_depth(op, sp, d_x, tau, tol, 0, max_depth, s, st);
+  for (double remaining = tau; remaining > 0.0;) {
+    double sub = 0.0;
+    RSV_TRY(expm_part(op, sp, d_x, remaining, tol, max_depth, s, st, &sub));
+    remaining = sub >= remaining ? 0.0 : remaining - sub;
+  }
+  return RSV_OK;
 }
 
 }  // namespace rsv

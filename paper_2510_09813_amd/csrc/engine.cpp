@@ -388,6 +388,7 @@ void register_destroy(rsv_register* reg, hipStream_t stream) {
   if (reg->d_efull) reg->alloc->release(reg->d_efull, (size_t(1) << reg->n) * sizeof(double));
   if (reg->d_ub) reg->alloc->release(reg->d_ub, reg->bytes);
   if (reg->own_h_scal && reg->h_scal) (void)hipHostFree(reg->h_scal);
+  if (reg->h_arnoldi) (void)hipHostFree(reg->h_arnoldi);
   if (reg->have_ev)
     for (hipEvent_t e : reg->ev) (void)hipEventDestroy(e);
   delete reg;

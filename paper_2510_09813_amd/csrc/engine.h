@@ -146,6 +146,7 @@ struct rsv_register {
   rsv::Workspace ws;
   double* h_scal = nullptr;  // pinned host scalars of the per-iteration exchange
   bool own_h_scal = false;
+  double* h_arnoldi = nullptr;  // pinned scalars of the Arnoldi process (arnoldi_host)
   hipEvent_t ev[rsv::kMaxKrylov + 1] = {};  // iteration k's scalars have reached h_scal
   bool have_ev = false;
 };

@@ -109,8 +109,10 @@ int rsv_gradient_occupations(rsv_register* reg, const rsv_pulses* pl, const rsv_
   double* part = (double*)(p + 4 * vb + tabs);
   double* res = part + npd + 2 * kDotGroup * npv;
   char* aug = p + 4 * vb + tabs + parts;  // [a | b], each 2^n amplitudes
+  double* h_scal = nullptr;
+  RSV_TRY(arnoldi_host(reg, &h_scal));
   ArnoldiSpace sp;
-  arnoldi_carve(p + fixed, reg->h_scal, prec, n + 1, o->kmax, &sp);
+  arnoldi_carve(p + fixed, h_scal, prec, n + 1, o->kmax, &sp);
   HIP_TRY(hipMemsetAsync(zt, 0, tabs, s));
   if (psi0_host) {
     if (prec == kC128) {

@@ -1,0 +1,190 @@
+// Gram-Schmidt kernels of the Arnoldi process (see arnoldi.h): the inner products of a new vector
+// with the whole basis, and its update.
+//
+// Both are streams over the basis (HBM-bound for density matrices of 11 atoms and more,
+// launch-bound for small ones).  The Gram-Schmidt coefficients never leave the device: the update
+// takes them from the inner products in device memory, so a run of iterations is queued without a
+// host round trip.  For vectors of up to 2^kSmallBits elements every workgroup sums the (at most
+// kSmallParts) partial sums it needs itself, which makes an iteration two launches besides the
+// operator; longer vectors take a second-stage launch each (2048 partials per value).
+//
+// y = s_j Op u_j is not orthogonalised as it is: for a skew-Hermitian operator it holds
+// -beta_{j-1} v_{j-1} (the Lanczos coupling), usually its largest part, and where the next beta
+// is smaller its removal cancels digits, so that the criterion for a second pass was met in
+// every second iteration (12 atoms: 12 of 28) by that one known component.  So both kernels
+// work on y1 = y + beta_{j-1} v_{j-1}; the inner products then measure what is left, the
+// coefficient of v_{j-1} is the sum of both parts, and the criterion compares with |y1|.  For
+// another operator the guess is merely a poor one: the result is the same, with more second passes.
+//
+// Measured, with the host part of arnoldi.cpp, against inner products and coefficients that went
+// through the host, a second pass by |y| and the whole exponential of H_m at every dimension: a
+// Lindblad step of 12 atoms (28 vectors of 256 MiB) 109 -> 72 ms, 20 steps of 6 atoms (12 vectors
+// of 64 KiB each) 40 -> 8.7 ms.
+#include "arnoldi.h"
+#include "device_common.h"
+
+namespace rsv {
+namespace {
+
+template <class R>
+__device__ __forceinline__ const Cx<R>* basis_vec(const ArnoldiStep& a, int i) {
+  return i == 0 ? (const Cx<R>*)a.v0 : (const Cx<R>*)a.base + (size_t)i * a.stride;
+}
+
+// Sum of p[0..n), n <= kSmallParts, by every wave for itself (fixed order).
+__device__ __forceinline__ double wave_parts(const double* p, int n) {
+  const int lane = threadIdx.x & 63;
+  double v = lane < n ? p[lane] : 0.0;
+  if (lane + 64 < n) v += p[lane + 64];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+struct Scales {
+  double f, g;  // y1 = f w + g u_{j-1}
+};
+
+// The coefficients of y1, with |u_j|^2 from its partial sums where they are not summed yet.
+__device__ __forceinline__ Scales scales(const ArnoldiStep& a, double n2) {
+  if (a.again) return Scales{1.0, 0.0};
+  const double s = 1.0 / sqrt(n2);
+  return Scales{s, a.j > 0 ? sqrt(n2) / sqrt(a.nrm2[a.j - 1]) : 0.0};
+}
+
+// Partial inner products <u_i, y1> (i <= j) and <y1, y1> (i = j + 1) of group blockIdx.y.
+template <class R>
+__global__ __launch_bounds__(kBlock) void arnoldi_dots_kernel(const ArnoldiStep a) {
+  constexpr int G = kArnoldiGroup;
+  __shared__ double red[4][2 * G];
+  double n2;
+  if (!a.again && a.nparts > 0) {
+    n2 = wave_parts(a.npart, a.nparts);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.nrm2[a.j] = n2;
+  } else {
+    n2 = a.nrm2[a.j];
+  }
+  const Scales sc = scales(a, n2);
+  const Cx<R>* w = (const Cx<R>*)a.w;
+  const Cx<R>* prev = sc.g != 0.0 ? basis_vec<R>(a, a.j - 1) : nullptr;
+  const int i0 = blockIdx.y * G, total = a.j + 2;
+  const Cx<R>* x[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) x[g] = i0 + g <= a.j ? basis_vec<R>(a, i0 + g) : nullptr;
+  double acc[2 * G];
+#pragma unroll
+  for (int q = 0; q < 2 * G; ++q) acc[q] = 0.0;
+  const size_t stride = (size_t)gridDim.x * kBlock;
+  for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < a.count; e += stride) {
+    const Cx<R> we = w[e];
+    double yr = sc.f * (double)we.x, yi = sc.f * (double)we.y;
+    if (prev) {
+      const Cx<R> pe = prev[e];
+      yr += sc.g * (double)pe.x;
+      yi += sc.g * (double)pe.y;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (x[g]) {
+        const Cx<R> xe = x[g][e];
+        acc[2 * g] += (double)xe.x * yr + (double)xe.y * yi;
+        acc[2 * g + 1] += (double)xe.x * yi - (double)xe.y * yr;
+      } else if (i0 + g == a.j + 1) {
+        acc[2 * g] += yr * yr + yi * yi;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2 * G; ++q) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = acc[q];
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * G && i0 + (int)(threadIdx.x >> 1) < total) {
+    const int q = threadIdx.x;
+    a.part[(size_t)(2 * i0 + q) * gridDim.x + blockIdx.x] =
+        (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
+  }
+}
+
+// u_{j+1} = y1 - sum_i v_i <v_i, y1>, rounded once, and the partials of |u_{j+1}|^2 (again: in
+// place on u_{j+1}, with the inner products of the second pass).
+template <class R>
+__global__ __launch_bounds__(kBlock) void arnoldi_update_kernel(const ArnoldiStep a) {
+  __shared__ double cr[kMaxKrylov + 2], ci[kMaxKrylov + 2], red[4];
+  const int rows = 2 * (a.j + 2), tid = threadIdx.x;
+  if (a.dparts > 0) {  // sum the partial inner products, one wave per value
+    for (int r = tid >> 6; r < rows; r += kBlock / 64) {
+      const double v = wave_parts(a.part + (size_t)r * a.dparts, a.dparts);
+      if ((tid & 63) == 0) ((r & 1) ? ci : cr)[r >> 1] = v;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid < kBlock)
+      for (int r = tid; r < rows; r += kBlock) a.dots[r] = (r & 1) ? ci[r >> 1] : cr[r >> 1];
+  } else {
+    for (int r = tid; r < rows; r += kBlock) ((r & 1) ? ci : cr)[r >> 1] = a.dots[r];
+    __syncthreads();
+  }
+  const Scales sc = scales(a, a.nrm2[a.j]);
+  if (tid <= a.j) {
+    const double s2 = 1.0 / a.nrm2[tid];  // v_i = u_i / |u_i|
+    cr[tid] = -s2 * cr[tid] + (tid == a.j - 1 ? sc.g : 0.0);
+    ci[tid] = -s2 * ci[tid];
+  }
+  __syncthreads();
+  const Cx<R>* w = (const Cx<R>*)a.w;
+  Cx<R>* out = (Cx<R>*)a.base + (size_t)(a.j + 1) * a.stride;
+  double acc = 0.0;
+  const size_t stride = (size_t)gridDim.x * kBlock;
+  for (size_t e = (size_t)blockIdx.x * kBlock + tid; e < a.count; e += stride) {
+    const Cx<R> we = w[e], x0 = ((const Cx<R>*)a.v0)[e];
+    double re = sc.f * (double)we.x + (cr[0] * (double)x0.x - ci[0] * (double)x0.y);
+    double im = sc.f * (double)we.y + (cr[0] * (double)x0.y + ci[0] * (double)x0.x);
+    const Cx<R>* x = (const Cx<R>*)a.base + a.stride + e;
+#pragma unroll 4
+    for (int i = 1; i <= a.j; ++i, x += a.stride) {
+      const Cx<R> xe = *x;
+      re += cr[i] * (double)xe.x - ci[i] * (double)xe.y;
+      im += cr[i] * (double)xe.y + ci[i] * (double)xe.x;
+    }
+    Cx<R> r;
+    r.x = (R)re;
+    r.y = (R)im;
+    out[e] = r;
+    acc = norm_add(acc, (double)r.x, (double)r.y);
+  }
+  const double t = block_sum_256(acc, red);
+  if (tid == 0) a.npart_out[blockIdx.x] = t;
+}
+
+}  // namespace
+
+int arnoldi_parts(size_t count) {
+  if (count <= (size_t(1) << kSmallBits)) {
+    // 512 elements per workgroup, 4 to kSmallParts of them
+    size_t g = count / 512;
+    return (int)(g < 4 ? 4 : g > kSmallParts ? kSmallParts : g);
+  }
+  return (int)stream_grid(count, 8);
+}
+
+hipError_t arnoldi_dots(int prec, const ArnoldiStep& a, hipStream_t s) {
+  const dim3 grid(arnoldi_parts(a.count), (a.j + 2 + kArnoldiGroup - 1) / kArnoldiGroup);
+  if (prec == kC128)
+    hipLaunchKernelGGL(arnoldi_dots_kernel<double>, grid, dim3(kBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL(arnoldi_dots_kernel<float>, grid, dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t arnoldi_update(int prec, const ArnoldiStep& a, hipStream_t s) {
+  const dim3 grid(arnoldi_parts(a.count));
+  if (prec == kC128)
+    hipLaunchKernelGGL(arnoldi_update_kernel<double>, grid, dim3(kBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL(arnoldi_update_kernel<float>, grid, dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace rsv

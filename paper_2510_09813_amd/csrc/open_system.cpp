@@ -126,8 +126,10 @@ int rsv_lindblad_evolve_device(rsv_register* reg, const rsv_pulses* pl, const rs
   RSV_TRY(energies(reg, s, &e));
   Block blk(reg->alloc, s);
   RSV_TRY(blk.get(arnoldi_device_bytes(prec, 2 * n, o->kmax)));
+  double* h_scal = nullptr;
+  RSV_TRY(arnoldi_host(reg, &h_scal));
   ArnoldiSpace sp;
-  arnoldi_carve(blk.p, reg->h_scal, prec, 2 * n, o->kmax, &sp);
+  arnoldi_carve(blk.p, h_scal, prec, 2 * n, o->kmax, &sp);
   rsv_stats st{};
   const double tau = o->dt_ns * 1e-3;
   for (int64_t k = first; k < first + count; ++k) {
@@ -143,8 +145,8 @@ int rsv_lindblad_evolve_device(rsv_register* reg, const rsv_pulses* pl, const rs
     }
     st.steps += 1;
   }
-  HIP_TRY(norm2_partial(prec, 2 * n, d_rho, sp.partial, s));
-  HIP_TRY(finalize_sum(sp.partial, vec_num_partials(prec, 2 * n), sp.dscal, s));
+  HIP_TRY(norm2_partial(prec, 2 * n, d_rho, sp.part, s));
+  HIP_TRY(finalize_sum(sp.part, vec_num_partials(prec, 2 * n), sp.dscal, s));
   double nrm2 = 0.0;
   HIP_TRY(hipMemcpyAsync(sp.h_scal, sp.dscal, sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
