@@ -76,47 +76,6 @@ struct Run {
   }
 };
 
-// The a-priori course of the estimate |x| h_{k+1,k} |[exp(tau H_k) e_1]_k|, in log2: at most
-// lead_k = |x| h_{k+1,k} prod_{i<k} tau h_{i+1,i} / (k-1)!, and for a spectrum of half-width a /
-// tau below that by about exp(-a^2 / 4k).  The first test takes the Gershgorin half-width (up to
-// twice the true one), later ones half of it, relative to the last value found.
-struct Course {
-  double tau, lead = 0.0, lo = 1e300, hi = -1e300, below = 0.0, last = 0.0, off = -10.0;
-  bool tested = false;
-  int k = 0;
-  void start(double t, double nx) {
-    *this = Course{};
-    tau = t;
-    lead = std::log2(nx);
-  }
-  // row k - 1 of H_k: its diagonal entry and the entry below it
-  void add(const cd& diag, double beta) {
-    ++k;
-    lo = std::min(lo, diag.imag() - below - beta);
-    hi = std::max(hi, diag.imag() + below + beta);
-    if (k > 1) lead += std::log2(tau * below / (k - 1));
-    below = beta;
-  }
-  double value(bool tight, int at, double l) const {
-    const double a = 0.5 * tau * (hi - lo) * (tight ? 0.5 : 1.0);
-    return l + std::log2(std::max(below, 1e-300)) - 0.3607 * a * a / at;
-  }
-  bool due(double log2_tol) const { return !(value(tested, k, lead) + off > log2_tol); }
-  void found(double est) {
-    off = std::log2(std::max(est, 1e-300)) - value(true, k, lead) - 2.0;
-    tested = true;
-  }
-  // iterations until a test is due, were the couplings to stay as they are
-  int ahead(double log2_tol, int most) const {
-    double l = lead;
-    for (int n = 1; n < most; ++n) {
-      l += std::log2(std::max(tau * below / (k + n - 1), 1e-300));
-      if (!(value(tested, k + n, l) + off > log2_tol)) return n;
-    }
-    return std::max(1, most);
-  }
-};
-
 // x <- exp(sub Op) x for the largest sub <= tau found that kmax vectors resolve.
 int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol, int max_depth,
               hipStream_t s, rsv_stats* st, double* sub) {
@@ -131,7 +90,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
   std::vector<double> scale(kmax + 1, 0.0);
   const double* sc = sp.h_scal;
   const double log2_tol = std::log2(tol);
-  Course course;
+  KrylovCourse course;
   double nx = 0.0;
   // an iteration too many costs a long vector more than a round trip
   int next = sp.hint > 0 ? (run.small ? sp.hint : sp.hint - 1) : 6;
@@ -196,7 +155,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
       H(j + 1, j) = beta;  // h_{j+1,j} = |y - sum_i v_i <v_i, y>|
       m = j + 1;
       scale[m] = 1.0 / beta;
-      course.add(H(j, j), beta);
+      course.add(H(j, j).imag(), beta);
       if (m == kmax || beta == 0.0 || course.due(log2_tol)) {
         auto estimate = [&](double t, double* est) -> int {
           if (hess_expm_e1(m, h.data(), kmax, t, y.data()) != 0)

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "engine.h"
+#include "krylov_course.h"
 
 namespace rsv {
 

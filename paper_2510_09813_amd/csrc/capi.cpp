@@ -145,7 +145,7 @@ int rsv_apply_hamiltonian(rsv_register* reg, const rsv_pulses* pl, int64_t step,
     return fail(RSV_EINVAL, "step %lld outside the pulse (%lld steps)", (long long)step,
                 (long long)K);
   HIP_TRY(hipSetDevice(reg->ctx->device));
-  const TilePlan plan = make_tile_plan(reg->prec, reg->n);
+  const TilePlan plan = sweep_plan(reg->prec, reg->n, true);
   if (plan.n_hi_passes > 0 && !reg->d_hbuf)
     RSV_TRY(reg->alloc->alloc(vec_bytes(reg->n, reg->prec), &reg->d_hbuf));
   const StepCoef c = step_coef(pl, reg->n, step, dt_ns);
@@ -186,7 +186,7 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
                 (long long)K);
   HIP_TRY(hipSetDevice(reg->ctx->device));
   const int n = reg->n, prec = reg->prec;
-  const TilePlan plan = make_tile_plan(prec, n);
+  const TilePlan plan = sweep_plan(prec, n, false);
   if (plan.n_hi_passes > 0 && !reg->d_hbuf)
     RSV_TRY(reg->alloc->alloc(vec_bytes(n, prec), &reg->d_hbuf));
   // H psi, the partial sums of Re<psi, H psi> and of |psi|^2 (both from the same sweep: the

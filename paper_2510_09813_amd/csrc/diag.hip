@@ -108,12 +108,12 @@ __global__ __launch_bounds__(kBlock) void diag_tables_kernel(const int n, const 
 }  // namespace
 
 size_t diag_table_doubles(int prec, int n) {
-  const int L = make_tile_plan(prec, n).lo_bits;
+  const int L = sweep_plan(prec, n, true).lo_bits;
   return (size_t(1) << L) + (size_t(1) << (n - L)) * (size_t)(L + 1);
 }
 
 hipError_t diag_tables_build(int prec, int n, const double* d_ub, double* dtab, hipStream_t s) {
-  const int L = make_tile_plan(prec, n).lo_bits;
+  const int L = sweep_plan(prec, n, true).lo_bits;
   const int64_t count = (int64_t)diag_table_doubles(prec, n);
   const uint32_t nblk = (uint32_t)((count + kBlock - 1) / kBlock);
   hipLaunchKernelGGL(diag_tables_kernel, dim3(nblk), dim3(kBlock), 0, s, n, L, d_ub, dtab, count);

@@ -3,9 +3,9 @@
 // Stepper (Sec. III): step k holds the pulse at its midpoint sample value and advances psi
 // by exp(-i H_k dt) (eq. 6).  Lanczos driver (Sec. III.A): each iteration is one H sweep
 // whose first pass also forms the next Krylov vector from the three-term recurrence (alpha
-// read from device memory) and whose last pass returns <u, H u>.  After the forming pass
-// one device-to-host copy brings (alpha_{k-1}, beta_{k-1}^2) to the host, which
-// diagonalises the tridiagonal T_k in FP64 and stops when the a-posteriori estimate
+// read from device memory) and whose last pass returns <u, H u>.  After a run of iterations
+// one device-to-host copy brings their (alpha_{k-1}, beta_{k-1}^2) to the host, which evaluates
+// the exponential of the tridiagonal T_k in FP64 and stops when the a-posteriori estimate
 // beta_{k-1} |[exp(-i dt T_k) e_1]_k| |psi| is at most tol.  Then
 // psi_{k+1} = |psi_k| sum_l y_l v_l (one combine sweep, which also returns |psi_{k+1}|^2).
 //
@@ -13,6 +13,7 @@
 // the kernel of packed jobs: see evolve_small.
 #include "engine.h"
 
+#include "krylov_course.h"
 #include "packed.h"
 
 #include <algorithm>
@@ -35,6 +36,9 @@ bool finite_all(const double* p, size_t n) {
 }
 
 constexpr size_t kScalarBytes = 4096;
+// Most partials that every workgroup of the forming pass sums for itself.  At most one norm
+// partial per thread, so that the sum's order is also finalize_sum's.
+constexpr int64_t kFusedParts = 1024;
 constexpr size_t kGranule = 256;
 inline size_t round_up(size_t b) { return (b + kGranule - 1) / kGranule * kGranule; }
 }  // namespace
@@ -217,7 +221,9 @@ size_t partial_doubles(int n, int prec) {
   // the two partial arrays are adjacent: together they hold a group of re-orthogonalisation
   // inner products (2 kDotGroup rows of vec_num_partials)
   const int64_t e = (int64_t)kDotGroup * b;
-  return (size_t)std::max(std::max(std::max(a, b), std::max(c, d)), e);
+  // and the norm partials of two iterations where the forming pass sums them
+  const int64_t f = a <= kFusedParts ? 2 * a : a;
+  return (size_t)std::max(std::max(std::max(f, b), std::max(c, d)), e);
 }
 
 size_t workspace_bytes(int n, int kmax, int prec) {
@@ -389,8 +395,6 @@ void register_destroy(rsv_register* reg, hipStream_t stream) {
   if (reg->d_ub) reg->alloc->release(reg->d_ub, reg->bytes);
   if (reg->own_h_scal && reg->h_scal) (void)hipHostFree(reg->h_scal);
   if (reg->h_arnoldi) (void)hipHostFree(reg->h_arnoldi);
-  if (reg->have_ev)
-    for (hipEvent_t e : reg->ev) (void)hipEventDestroy(e);
   delete reg;
 }
 
@@ -412,6 +416,7 @@ int workspace_acquire(rsv_register* reg, int kmax) {
   ws.z = p + (size_t)(kmax + 1) * vb;
   ws.t = p + (size_t)(kmax + 2) * vb;
   ws.pnorm = (double*)(p + (size_t)(kmax + 3) * vb);
+  ws.pnorm2 = ws.pnorm + sweep_num_partials(reg->prec, reg->n);
   ws.pdot = (double*)(p + (size_t)(kmax + 3) * vb + pb);
   ws.dscal = (double*)(p + (size_t)(kmax + 3) * vb + 2 * pb);
   return RSV_OK;
@@ -430,12 +435,15 @@ struct Lanczos {
   rsv_register* reg;
   hipStream_t s;
   rsv_stats* st;
-  double norm2;  // |psi|^2 of the state in basis[0]
+  double norm2 = 0.0;  // |psi|^2 of the state the last step began with
   double alpha[kMaxKrylov + 1], beta[kMaxKrylov + 1], scale[kMaxKrylov + 1];
   double yre[kMaxKrylov], yim[kMaxKrylov];
   std::vector<double> work;
   double* occ_partial = nullptr;  // fused occupation sums of an observed step's combination
   double dir = 1.0;               // -1: exp(+i tau H), the step backwards in time
+  // dimensions of the previous step's runs (its sub-steps): how many iterations to queue first
+  static constexpr int kHints = 8;
+  int hint[kHints] = {};
 };
 
 // Device scalar slots [first_slot, first_slot + count) through the same slots of h_scal.
@@ -445,15 +453,6 @@ int fetch_scalars(Lanczos& L, int first_slot, int count, double* out) {
                          hipMemcpyDeviceToHost, L.s));
   HIP_TRY(hipStreamSynchronize(L.s));
   for (int i = 0; i < count; ++i) out[i] = h[i];
-  return RSV_OK;
-}
-
-// Events marking the per-iteration scalar copies, created once per register.
-int ensure_events(rsv_register* reg) {
-  if (reg->have_ev) return RSV_OK;
-  for (int k = 0; k <= kMaxKrylov; ++k)
-    HIP_TRY(hipEventCreateWithFlags(&reg->ev[k], hipEventDisableTiming));
-  reg->have_ev = true;
   return RSV_OK;
 }
 
@@ -498,23 +497,27 @@ int reorthogonalise(Lanczos& L, int k, double* b2) {
   return RSV_OK;
 }
 
-// |[exp(-i h T_m) e_1]_{m-1}| for the current T_m.
-int last_component(Lanczos& L, int m, double h, double* out) {
-  if (tridiag_expm_last(m, L.alpha, L.beta, h, out, L.work.data()) != 0)
+// y = exp(-i h T_m) e_1 (into L.yre, L.yim) and |y_{m-1}| for the current T_m.
+int small_exponential(Lanczos& L, int m, double h, double* last) {
+  if (tridiag_expm_series(m, L.alpha, L.beta, h, L.yre, L.yim, L.work.data()) != 0)
     return fail(RSV_ENUMERIC, "tridiagonal eigensolver failed (m = %d)", m);
+  *last = std::hypot(L.yre[m - 1], L.yim[m - 1]);
   return RSV_OK;
 }
 
-// psi <- exp(-i tau H) psi with psi in basis[0] (|psi|^2 = L.norm2).
+// psi <- exp(-i tau H) psi with psi in basis[0] (|psi|^2 = dscal[kNormSlot]).
 //
 // Krylov vectors are kept unnormalised: v_k = s_k u_k with s_0 = 1/|psi| and
 // s_k = 1/beta_{k-1}.  Sweep k >= 1 forms
 //   u_k = s_{k-1} z_{k-1} - s_{k-1}^3 <u_{k-1}, z_{k-1}> u_{k-1} - (s_{k-2}/s_{k-1}) u_{k-2}
-// (= H v_{k-1} - alpha_{k-1} v_{k-1} - beta_{k-2} v_{k-2}) in its first pass, stores it,
-// and returns |u_k|^2 = beta_{k-1}^2; the host then tests convergence of the m = k
-// dimensional Krylov approximation before the later passes compute z_k = H u_k.
-// With obs set, the combination that completes the step also writes the occupation sums of
-// the new state to obs (device, n + 1 doubles).
+// (= H v_{k-1} - alpha_{k-1} v_{k-1} - beta_{k-2} v_{k-2}) in its first pass, from scalars in
+// device memory, stores it and returns the partials of |u_k|^2 = beta_{k-1}^2; the later passes
+// compute z_k = H u_k.  Iterations are queued several at a time (as many as the previous step took,
+// or as the a-priori course of the estimate suggests) and their scalars fetched together; the
+// host then goes through the dimensions in order and takes the smallest that meets the tolerance
+// (reorth: one iteration at a time, since the host forms its coefficients).  With obs set, the
+// combination that completes the step also writes the occupation sums of the new state to obs
+// (device, n + 1 doubles).
 int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, int max_depth,
               bool reorth, double* obs = nullptr) {
   rsv_register* reg = L.reg;
@@ -522,118 +525,145 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
   const int n = reg->n, prec = reg->prec;
   const int64_t np_norm = sweep_norm_partials(prec, n), np_dot = sweep_dot_partials(prec, n);
   const bool single = sweep_passes(prec, n) == 1;
+  // few enough partials: the forming pass sums them (the two norms alternate between buffers,
+  // since its workgroups read one while they write the other)
+  const bool fused = !single && !reorth && np_dot <= kFusedParts && np_norm <= kFusedParts;
+  auto norm_parts = [&](int k) { return fused && (k & 1) ? ws.pnorm2 : ws.pnorm; };
+  // an iteration too many costs large vectors (from about 40 us per iteration) more than a round trip
+  const bool large = vec_bytes(n, prec) >= (size_t(16) << 20);
   const double hbytes = (double)(size_t(1) << n) * (prec == kC128 ? 40.0 : 20.0);
-  // below 256 MiB per vector an iteration's kernels are short and the host round trip would
-  // leave the device idle: queue one iteration ahead (re-orthogonalisation needs the host)
-  const bool ahead = !reorth && vec_bytes(n, prec) < (size_t(256) << 20);
-  RSV_TRY(ensure_events(reg));
+  const double log2_tol = std::log2(tol);
   double remaining = tau;
-  while (remaining > 0.0) {
-    const double nrm = std::sqrt(L.norm2);
-    if (!(nrm > 0.0) || !std::isfinite(nrm)) return fail(RSV_ENUMERIC, "state norm is %g", nrm);
-    L.scale[0] = 1.0 / nrm;
+  for (int run = 0; remaining > 0.0; ++run) {
+    int& hint = L.hint[run < Lanczos::kHints ? run : Lanczos::kHints - 1];
     // sweep 0: z_0 = H u_0 and <u_0, z_0>
     {
       const SweepIn in{ws.basis[0], nullptr, nullptr, 1.0, 0.0, 0.0, nullptr, 0.0};
       const SweepOut so{nullptr, nullptr, ws.pdot};
       HIP_TRY(hpsi_sweep(prec, n, c, reg->d_dtab, in, ws.z, ws.t, so, kAllPasses, L.s));
-      HIP_TRY(finalize_sum(ws.pdot, np_dot, ws.dscal + 1, L.s));
+      if (!fused) HIP_TRY(finalize_sum(ws.pdot, np_dot, ws.dscal + 1, L.s));
       L.st->krylov_iters += 1;
       L.st->bytes_hpsi += hbytes;
     }
-    int m = 0;
-    double sub = remaining;
     // device address of |u_k|^2 (|psi|^2 for k = 0): the forming pass takes s_k from it
     auto dev_norm = [&](int k) { return ws.dscal + (k == 0 ? kNormSlot : 2 * k); };
-    // u_k from z_{k-1}, u_{k-1}, u_{k-2} with device-side coefficients, |u_k|^2, and the
-    // copy of (<u_{k-1}, z_{k-1}>, |u_k|^2) to the pinned host scalars, marked by ev[k]
+    // u_k from z_{k-1}, u_{k-1}, u_{k-2} with device-side coefficients, and |u_k|^2
     auto form = [&](int k) -> int {
       SweepIn in{ws.z, ws.basis[k - 1], k >= 2 ? ws.basis[k - 2] : nullptr, 0.0, 0.0, 0.0,
                  ws.dscal + (2 * (k - 1) + 1), 0.0};
       in.nrm1 = dev_norm(k - 1);
       in.nrm2 = k >= 2 ? dev_norm(k - 2) : nullptr;
-      const SweepOut so{ws.basis[k], ws.pnorm, ws.pdot};
+      if (fused) {
+        in.part_dot = ws.pdot;
+        in.n_dot = (int)np_dot;
+        in.part_nrm = norm_parts(k - 1);
+        in.n_nrm = k >= 2 ? (int)np_norm : 0;
+      }
+      const SweepOut so{ws.basis[k], norm_parts(k), ws.pdot};
       // single-pass sizes compute z_k in the same pass; otherwise only the forming pass
       HIP_TRY(hpsi_sweep(prec, n, c, reg->d_dtab, in, ws.z, ws.t, so, kFirstPass, L.s));
-      HIP_TRY(finalize_sum(ws.pnorm, np_norm, ws.dscal + 2 * k, L.s));
+      if (!fused) HIP_TRY(finalize_sum(ws.pnorm, np_norm, ws.dscal + 2 * k, L.s));
       if (single) HIP_TRY(finalize_sum(ws.pdot, np_dot, ws.dscal + 2 * k + 1, L.s));
-      HIP_TRY(hipMemcpyAsync(reg->h_scal + 2 * k - 1, ws.dscal + 2 * k - 1, 2 * sizeof(double),
-                             hipMemcpyDeviceToHost, L.s));
-      HIP_TRY(hipEventRecord(reg->ev[k], L.s));
       return RSV_OK;
     };
     // z_k = H u_k: the remaining passes, or all of them when u_k was re-orthogonalised
     // after the forming pass
     auto later = [&](int k) -> int {
+      L.st->krylov_iters += 1;
+      L.st->bytes_hpsi += hbytes;
       if (single && !reorth) return RSV_OK;
       const SweepIn in2{ws.basis[k], nullptr, nullptr, 1.0, 0.0, 0.0, nullptr, 0.0};
       const SweepOut so2{nullptr, nullptr, ws.pdot};
       HIP_TRY(hpsi_sweep(prec, n, c, reg->d_dtab, in2, ws.z, ws.t, so2,
                          reorth ? kAllPasses : kLaterPasses, L.s));
-      HIP_TRY(finalize_sum(ws.pdot, np_dot, ws.dscal + 2 * k + 1, L.s));
+      if (!fused) HIP_TRY(finalize_sum(ws.pdot, np_dot, ws.dscal + 2 * k + 1, L.s));
       return RSV_OK;
     };
-    RSV_TRY(form(1));
-    for (int k = 1; k <= kmax; ++k) {
-      // run ahead: queue iteration k+1 before reading iteration k's scalars, so the device
-      // never waits for the host (one iteration is wasted when k converges)
-      const bool speculate = ahead && k < kmax;
-      if (speculate) {
-        RSV_TRY(later(k));
-        RSV_TRY(form(k + 1));
-        L.st->krylov_iters += 1;
-        L.st->bytes_hpsi += hbytes;
+    int m = 0;  // dimensions gone through
+    double nrm = 0.0, sub = remaining;
+    bool done = false;
+    int next = reorth ? 1 : hint <= 0 ? 6 : large ? hint - 1 : hint;
+    KrylovCourse course;
+    double bks[kMaxKrylov + 1];  // |u_k|
+    while (!done) {
+      const int upto = std::min(kmax, m + std::max(1, next));
+      for (int k = m + 1; k <= upto; ++k) {
+        if (k > 1) RSV_TRY(later(k - 1));
+        RSV_TRY(form(k));
       }
-      HIP_TRY(hipEventSynchronize(reg->ev[k]));
-      double ab[2] = {reg->h_scal[2 * k - 1], reg->h_scal[2 * k]};  // <u_{k-1}, z_{k-1}>, |u_k|^2
-      if (!std::isfinite(ab[0]) || !std::isfinite(ab[1]))
-        return fail(RSV_ENUMERIC, "Lanczos coefficient not finite at iteration %d", k);
-      const double sk1 = L.scale[k - 1];
-      L.alpha[k - 1] = sk1 * sk1 * ab[0];
-      if (reorth) {
-        RSV_TRY(reorthogonalise(L, k, &ab[1]));
-        if (!std::isfinite(ab[1]))
+      if (fused) HIP_TRY(finalize_sum(norm_parts(upto), np_norm, ws.dscal + 2 * upto, L.s));
+      double scal[kNormSlot + 1];
+      RSV_TRY(fetch_scalars(L, 0, kNormSlot + 1, scal));
+      if (m == 0) {
+        L.norm2 = scal[kNormSlot];
+        nrm = std::sqrt(L.norm2);
+        if (!(nrm > 0.0) || !std::isfinite(nrm)) return fail(RSV_ENUMERIC, "state norm is %g", nrm);
+        L.scale[0] = 1.0 / nrm;
+        course.start(remaining, nrm);
+      }
+      for (int k = m + 1; k <= upto && !done; ++k) {
+        double ab[2] = {scal[2 * k - 1], scal[2 * k]};  // <u_{k-1}, z_{k-1}>, |u_k|^2
+        if (!std::isfinite(ab[0]) || !std::isfinite(ab[1]))
           return fail(RSV_ENUMERIC, "Lanczos coefficient not finite at iteration %d", k);
-      }
-      const double bk = std::sqrt(std::max(ab[1], 0.0));  // beta_{k-1}
-      m = k;
-      double ylast = 0.0;
-      RSV_TRY(last_component(L, m, remaining, &ylast));
-      if (bk * ylast * nrm <= tol || bk == 0.0) break;
-      if (k == kmax) {
-        // Not converged: advance by the longest part of the step that this basis already
-        // resolves (same H_k, so the split is exact), then restart from the new state.
-        // The first dyadic fraction that converges brackets it; bisection refines it.
-        bool ok = false;
-        double bad = remaining;
-        for (int d = 1; d <= max_depth && !ok; ++d) {
-          sub = std::ldexp(remaining, -d);
-          RSV_TRY(last_component(L, m, sub, &ylast));
-          ok = bk * ylast * nrm <= tol;
-          if (!ok) bad = sub;
+        const double sk1 = L.scale[k - 1];
+        L.alpha[k - 1] = sk1 * sk1 * ab[0];
+        if (reorth) {
+          RSV_TRY(reorthogonalise(L, k, &ab[1]));
+          if (!std::isfinite(ab[1]))
+            return fail(RSV_ENUMERIC, "Lanczos coefficient not finite at iteration %d", k);
         }
-        if (!ok) return fail(RSV_ENOTCONV, "Krylov exponential not converged with kmax = %d", kmax);
-        for (int it = 0; it < 10; ++it) {
-          const double mid = 0.5 * (sub + bad);
-          RSV_TRY(last_component(L, m, mid, &ylast));
-          if (bk * ylast * nrm <= tol) sub = mid;
-          else bad = mid;
+        const double bk = std::sqrt(std::max(ab[1], 0.0));  // beta_{k-1}
+        bks[k] = bk;
+        L.beta[k - 1] = bk;
+        L.scale[k] = 1.0 / bk;
+        m = k;
+        course.add(L.alpha[k - 1], bk);
+        if (k < kmax && bk != 0.0 && !course.due(log2_tol)) continue;
+        double ylast = 0.0;
+        RSV_TRY(small_exponential(L, m, remaining, &ylast));
+        if (bk * ylast * nrm <= tol || bk == 0.0) {
+          // a smaller dimension may do: the tests begin near the tolerance, not before it
+          while (m > 1) {
+            RSV_TRY(small_exponential(L, m - 1, remaining, &ylast));
+            if (!(bks[m - 1] * ylast * nrm <= tol)) break;
+            --m;
+          }
+          done = true;
+          break;
         }
-        L.st->substeps += 1;
-        break;
+        course.found(bk * ylast * nrm);
+        if (k == kmax) {
+          // Not converged: advance by the longest part of the step that this basis already
+          // resolves (same H_k, so the split is exact), then restart from the new state.
+          // The first dyadic fraction that converges brackets it; bisection refines it.
+          bool ok = false;
+          double bad = remaining;
+          for (int d = 1; d <= max_depth && !ok; ++d) {
+            sub = std::ldexp(remaining, -d);
+            RSV_TRY(small_exponential(L, m, sub, &ylast));
+            ok = bk * ylast * nrm <= tol;
+            if (!ok) bad = sub;
+          }
+          if (!ok) return fail(RSV_ENOTCONV, "Krylov exponential not converged with kmax = %d", kmax);
+          for (int it = 0; it < 10; ++it) {
+            const double mid = 0.5 * (sub + bad);
+            RSV_TRY(small_exponential(L, m, mid, &ylast));
+            if (bk * ylast * nrm <= tol) sub = mid;
+            else bad = mid;
+          }
+          L.st->substeps += 1;
+          done = true;
+        }
       }
-      L.beta[k - 1] = bk;
-      L.scale[k] = 1.0 / bk;
-      if (!speculate) {
-        RSV_TRY(later(k));
-        RSV_TRY(form(k + 1));
-        L.st->krylov_iters += 1;
-        L.st->bytes_hpsi += hbytes;
+      if (!done) {
+        next = reorth ? 1 : course.ahead(log2_tol, kmax - m);
+        if (large && !course.tested) next = std::max(1, next - 2);
       }
     }
+    hint = m;
     L.st->krylov_max = std::max<int64_t>(L.st->krylov_max, m);
-    if (tridiag_expm(m, L.alpha, L.beta, L.dir * sub, L.yre, L.yim, L.work.data()) != 0)
-      return fail(RSV_ENUMERIC, "tridiagonal eigensolver failed (m = %d)", m);
+    double ylast = 0.0;
+    RSV_TRY(small_exponential(L, m, L.dir * sub, &ylast));
     CombineCoef cc;
     std::memset(&cc, 0, sizeof cc);
     cc.m = m;
@@ -648,7 +678,6 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
       HIP_TRY(krylov_combine(prec, n, cc, ws.z, ws.pnorm, L.s));
     HIP_TRY(finalize_sum(ws.pnorm, vec_num_partials(prec, n), ws.dscal + kNormSlot, L.s));
     std::swap(ws.basis[0], ws.z);
-    RSV_TRY(fetch_scalars(L, kNormSlot, 1, &L.norm2));
     remaining = (sub == remaining) ? 0.0 : remaining - sub;
   }
   return RSV_OK;
@@ -837,7 +866,6 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
     std::memset(L.beta, 0, sizeof L.beta);
     std::memset(L.scale, 0, sizeof L.scale);
     L.work.assign(tridiag_work_doubles(kMaxKrylov), 0.0);
-    RSV_TRY(fetch_scalars(L, kNormSlot, 1, &L.norm2));
     const double tau = o->dt_ns * 1e-3;  // us
     for (int64_t k = first; k < first + count; ++k) {
       const StepCoef c = step_coef(pl, n, k, o->dt_ns);
@@ -848,8 +876,7 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
       st->steps += 1;
     }
     HIP_TRY(hipMemcpyAsync(d_psi, ws.basis[0], vb, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    norm2 = L.norm2;
+    RSV_TRY(fetch_scalars(L, kNormSlot, 1, &norm2));
   }
   if (n_obs > 0) {
     std::vector<double> h((size_t)n_obs * (n + 1));

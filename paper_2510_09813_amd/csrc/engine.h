@@ -111,6 +111,7 @@ struct Workspace {
   void* z = nullptr;  // H u of the latest Krylov vector; also the combination target
   void* t = nullptr;  // high-bit partial of H u
   double* pnorm = nullptr;
+  double* pnorm2 = nullptr;  // the norm partials of every other iteration (inside pnorm's array)
   double* pdot = nullptr;
   double* dscal = nullptr;
   size_t bytes = 0;
@@ -147,8 +148,6 @@ struct rsv_register {
   double* h_scal = nullptr;  // pinned host scalars of the per-iteration exchange
   bool own_h_scal = false;
   double* h_arnoldi = nullptr;  // pinned scalars of the Arnoldi process (arnoldi_host)
-  hipEvent_t ev[rsv::kMaxKrylov + 1] = {};  // iteration k's scalars have reached h_scal
-  bool have_ev = false;
 };
 
 struct rsv_result {

@@ -63,6 +63,10 @@ static_assert(Geo<double>::RL == 3 && Geo<double>::RLW == 6 && Geo<float>::RL ==
                   Geo<float>::RLW == 6,
               "launch_hi instantiates run lengths 3..6");
 
+// Run (one cache line) and smallest tile of sweep_plan's high passes.
+template <class R> constexpr int mid_run() { return sizeof(R) == 8 ? 3 : 4; }
+constexpr int kMidMinTile = 8;
+
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
 
 // Sum of a double over an NT-thread workgroup (fixed tree; valid in thread 0).
@@ -89,10 +93,13 @@ struct PassArgs {
   const Cx<R>* x1;
   const Cx<R>* x2;
   double a0, a1, a2;
-  const double* dot;  // optional: a1 += dot_coef * dot[0]
+  double* dot;  // optional: a1 += dot_coef * dot[0]
   double dot_coef;
-  const double* nrm1;  // optional: coefficients from device norms (see SweepIn)
+  double* nrm1;  // optional: coefficients from device norms (see SweepIn)
   const double* nrm2;
+  const double* in_dot;  // n_dot > 0: the partials of dot[0] (and nrm1[0]), still to be summed
+  const double* in_nrm;
+  int n_dot, n_nrm;
   Cx<R>* u_out;       // optional: store the formed input
   double* part_norm;  // optional: per-workgroup |u|^2
   // high pass
@@ -127,12 +134,46 @@ struct Coefs {
   double a0, b1, a2;
 };
 
-template <class R>
-__device__ __forceinline__ Coefs input_coefs(const PassArgs<R>& p) {
+// SUM (n_dot > 0): every workgroup first sums the partials of dot and nrm1 (a few hundred values,
+// one LDS exchange, the same order in each): cheaper, up to kFusedParts of them, than two more
+// launches per iteration (3.6-4.5 us each at 17-20 atoms).
+template <int NT, bool SUM, class R>
+__device__ __forceinline__ Coefs input_coefs(const PassArgs<R>& p, double* red /* SUM: NT / 32 doubles */) {
   if (p.nrm1) {  // s_{k-1}, s_{k-2} from the norms of the stored vectors
-    const double s1 = 1.0 / sqrt(p.nrm1[0]);
+    double d = 0.0, n1 = 0.0;
+    if constexpr (SUM) {
+      for (int i = threadIdx.x; i < p.n_dot; i += NT) d += p.in_dot[i];
+      for (int i = threadIdx.x; i < p.n_nrm; i += NT) n1 += p.in_nrm[i];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        d += __shfl_xor(d, off, 64);
+        n1 += __shfl_xor(n1, off, 64);
+      }
+      constexpr int W = NT / 64;
+      if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = d;
+        red[W + (threadIdx.x >> 6)] = n1;
+      }
+      __syncthreads();
+      d = n1 = 0.0;
+#pragma unroll 2
+      for (int w = 0; w < W; ++w) {  // (unrolled in full, its reads would set the register count)
+        d += red[w];
+        n1 += red[W + w];
+      }
+      __syncthreads();
+      if (p.n_nrm == 0) n1 = p.nrm1[0];
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        p.dot[0] = d;
+        if (p.n_nrm > 0) p.nrm1[0] = n1;
+      }
+    } else {
+      d = p.dot[0];
+      n1 = p.nrm1[0];
+    }
+    const double s1 = 1.0 / sqrt(n1);
     const double s2 = p.nrm2 ? 1.0 / sqrt(p.nrm2[0]) : 0.0;
-    return Coefs{s1, -s1 * s1 * s1 * p.dot[0], -s2 / s1};
+    return Coefs{s1, -s1 * s1 * s1 * d, -s2 / s1};
   }
   return Coefs{p.a0, p.dot ? p.a1 + p.dot_coef * p.dot[0] : p.a1, p.a2};
 }
@@ -335,7 +376,7 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
   const uint32_t base = blk << LB;
   if (CM == kCoefSite) build_delta_lut<R>(c, lut);
 
-  const Coefs co = input_coefs(p);
+  const Coefs co = input_coefs<NT, false>(p, red);
   C v[A], tv[A];
   R dg[A];
   double nrm = 0.0;
@@ -491,8 +532,9 @@ __global__ __launch_bounds__(kBlock) void hpsi_small_kernel(const StepCoef c, co
   if (CM == kCoefSite) build_delta_lut<R>(c, lut);
   C v = {0, 0};
   double nrm = 0.0, dot = 0.0;
+  const Coefs co = input_coefs<kBlock, false>(p, red);
   if (tid < dim) {
-    v = form<R>(p, input_coefs(p), tid);
+    v = form<R>(p, co, tid);
     tile[tid] = v;
     if (p.u_out) p.u_out[tid] = v;
     nrm = norm_add(0.0, (double)v.x, (double)v.y);
@@ -519,22 +561,27 @@ __global__ __launch_bounds__(kBlock) void hpsi_small_kernel(const StepCoef c, co
 
 // ----------------------------------------------------------------------------- high pass
 // Tile: bits [0, RL) and [a, a + HB - RL) of the index; flips bits in [f0, f1) only.
-template <class R, int HB, int RL, int NT, int CM>
-__global__ __launch_bounds__(NT) void hpsi_hi_kernel(const StepCoef c, const PassArgs<R> p) {
+// Waves per SIMD to leave room for: two complex64 workgroups of 1024 threads per CU (one only, at 66
+// registers, took 203 us instead of 139 at 24 atoms), and the small tiles of sweep_plan likewise.
+template <class R, int HB, int NT>
+constexpr int hi_min_waves() { return (1 << HB) / NT * sizeof(R) <= 16 || NT < 1024 ? 8 : 4; }
+
+template <class R, int HB, int RL, int NT, int CM, bool SUM>
+__global__ __launch_bounds__(NT, (hi_min_waves<R, HB, NT>())) void hpsi_hi_kernel(const StepCoef c, const PassArgs<R> p) {
   using C = Cx<R>;
   constexpr int G = HB - RL;
   constexpr int TB = ilog2(NT);
   static_assert(HB >= TB && TB > RL, "tile shape");
   constexpr int A = 1 << (HB - TB);
   __shared__ C tile[1 << HB];
-  __shared__ double red[NT / 64];
+  __shared__ double red[NT / (SUM ? 32 : 64)];
 
   const uint32_t tid = threadIdx.x;
   const uint32_t blk = xcd_remap(blockIdx.x, p.nblk);
   const int gap = p.a - RL;  // outside bits between the contiguous run and the tile's high bits
   const uint32_t obase = ((blk & ((1u << gap) - 1u)) << RL) | ((blk >> gap) << (p.a + G));
 
-  const Coefs co = input_coefs(p);
+  const Coefs co = input_coefs<NT, SUM>(p, red);
   C v[A], tv[A];
   uint32_t gi[A];
   double nrm = 0.0;
@@ -605,7 +652,18 @@ void launch_lo_ext(int ext, const StepCoef& c, const PassArgs<R>& p, int n, hipS
 
 template <class R, int CM>
 void launch_lo_any(int lb, int ext, const StepCoef& c, const PassArgs<R>& p, int n, hipStream_t s) {
-  if (ext > 0) {  // extensions are planned on 12-bit tiles, and complex64's 13-bit ones
+  if (ext > 0) {  // extensions are planned on 12-bit tiles, complex64's 13-bit ones, and sweep_plan's
+    switch (8 * lb + ext) {  // sweep_plan's of 13..18 atoms
+      case 8 * 9 + 4: return launch_lo<R, 9, CM, 4>(c, p, n, s);
+      case 8 * 9 + 5: return launch_lo<R, 9, CM, 5>(c, p, n, s);
+      case 8 * 9 + 6: return launch_lo<R, 9, CM, 6>(c, p, n, s);
+      case 8 * 10 + 5: return launch_lo<R, 10, CM, 5>(c, p, n, s);
+      case 8 * 10 + 6: return launch_lo<R, 10, CM, 6>(c, p, n, s);
+      case 8 * 10 + 7: return launch_lo<R, 10, CM, 7>(c, p, n, s);
+      case 8 * 11 + 6: return launch_lo<R, 11, CM, 6>(c, p, n, s);
+      case 8 * 11 + 7: return launch_lo<R, 11, CM, 7>(c, p, n, s);
+      default: break;
+    }
     if constexpr (Geo<R>::L >= 13) {
       if (lb == 13) return launch_lo_ext<R, CM, 13>(ext, c, p, n, s);
     }
@@ -623,15 +681,38 @@ void launch_lo_any(int lb, int ext, const StepCoef& c, const PassArgs<R>& p, int
   }
 }
 
+template <class R, int CM, int HB, int RL>
+void launch_hi_tile(const StepCoef& c, const PassArgs<R>& p, hipStream_t s) {
+  // sweep_plan's tiles: at most 512 threads, so that several workgroups share a CU
+  constexpr int NT = HB >= 12 ? Geo<R>::NH : HB >= 9 ? 512 : 256;
+  if (p.n_dot > 0)
+    hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, RL, NT, CM, true>), dim3(p.nblk), dim3(NT), 0, s, c, p);
+  else
+    hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, RL, NT, CM, false>), dim3(p.nblk), dim3(NT), 0, s, c, p);
+}
+
 template <class R, int CM>
-void launch_hi(int rl, const StepCoef& c, const PassArgs<R>& p, hipStream_t s) {
-  constexpr int HB = Geo<R>::H, NT = Geo<R>::NH;
-  switch (rl) {
-    case 3: hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, 3, NT, CM>), dim3(p.nblk), dim3(NT), 0, s, c, p); break;
-    case 4: hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, 4, NT, CM>), dim3(p.nblk), dim3(NT), 0, s, c, p); break;
-    case 5: hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, 5, NT, CM>), dim3(p.nblk), dim3(NT), 0, s, c, p); break;
-    default: hipLaunchKernelGGL((hpsi_hi_kernel<R, HB, 6, NT, CM>), dim3(p.nblk), dim3(NT), 0, s, c, p); break;
+hipError_t launch_hi(int hb, int rl, const StepCoef& c, const PassArgs<R>& p, hipStream_t s) {
+  constexpr int HB = Geo<R>::H;
+  if (hb == HB) {
+    switch (rl) {
+      case 3: launch_hi_tile<R, CM, HB, 3>(c, p, s); break;
+      case 4: launch_hi_tile<R, CM, HB, 4>(c, p, s); break;
+      case 5: launch_hi_tile<R, CM, HB, 5>(c, p, s); break;
+      default: launch_hi_tile<R, CM, HB, 6>(c, p, s); break;
+    }
+    return hipSuccess;
   }
+  constexpr int kMidRun = mid_run<R>();
+  if (rl != kMidRun) return hipErrorInvalidValue;
+  switch (hb) {
+    case 8: launch_hi_tile<R, CM, 8, kMidRun>(c, p, s); break;
+    case 9: launch_hi_tile<R, CM, 9, kMidRun>(c, p, s); break;
+    case 10: launch_hi_tile<R, CM, 10, kMidRun>(c, p, s); break;
+    case 11: launch_hi_tile<R, CM, 11, kMidRun>(c, p, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipSuccess;
 }
 
 template <class R, int CM>
@@ -648,9 +729,17 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
   base.dot_coef = in.dot_coef;
   base.nrm1 = in.nrm1;
   base.nrm2 = in.nrm2;
-  const int lbits = make_tile_plan(sizeof(R) == 8 ? kC128 : kC64, n).lo_bits;
+  base.in_dot = in.part_dot;
+  base.in_nrm = in.part_nrm;
+  base.n_dot = in.n_dot;
+  base.n_nrm = in.n_nrm;
+  // the formed input, once stored, is the plain input of every later pass
+  const bool forming = in.x1 || in.x2 || in.a0 != 1.0 || in.dot || in.nrm1;
+  // (the later passes of a formed sweep follow the plan its first pass did)
+  const bool stored_in = !forming && part == kAllPasses && !so.u_out && !so.part_norm;
+  const TilePlan plan = sweep_plan(sizeof(R) == 8 ? kC128 : kC64, n, stored_in);
   base.elo = dtab;
-  base.etile = dtab + (size_t(1) << lbits);
+  base.etile = dtab + (size_t(1) << plan.lo_bits);
   base.out = (Cx<R>*)out;
   // vectors of 64 MiB and more stream past the caches: a Lanczos iteration touches five of
   // them, more than the 256 MB last-level cache holds (from 64 MiB rather than 256 MiB the
@@ -667,9 +756,6 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
     hipLaunchKernelGGL((hpsi_small_kernel<R, CM>), dim3(1), dim3(kBlock), 0, s, c, p);
     return hipGetLastError();
   }
-  const TilePlan plan = make_tile_plan(sizeof(R) == 8 ? kC128 : kC64, n);
-  // the formed input, once stored, is the plain input of every later pass
-  const bool forming = in.x1 || in.x2 || in.a0 != 1.0 || in.dot || in.nrm1;
   if (forming && plan.n_hi_passes > 0 && !so.u_out) return hipErrorInvalidValue;
   const Cx<R>* stored = so.u_out ? (const Cx<R>*)so.u_out : (const Cx<R>*)in.x0;
   for (int i = 0; i < plan.n_hi_passes; ++i) {
@@ -680,7 +766,9 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
       p.x1 = p.x2 = nullptr;
       p.a0 = 1.0;
       p.dot = nullptr;
-      p.nrm1 = p.nrm2 = nullptr;
+      p.nrm1 = nullptr;
+      p.nrm2 = nullptr;
+      p.n_dot = 0;
     } else {
       p.u_out = (Cx<R>*)so.u_out;
       p.part_norm = so.part_norm;
@@ -691,7 +779,8 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
     p.f0 = plan.flip_lo[i];
     p.f1 = plan.flip_hi[i];
     p.nblk = 1u << (n - plan.hi_bits);
-    launch_hi<R, CM>(plan.run_bits[i], c, p, s);
+    const hipError_t e = launch_hi<R, CM>(plan.hi_bits, plan.run_bits[i], c, p, s);
+    if (e != hipSuccess) return e;
   }
   if ((plan.n_hi_passes > 0 && !later) || (plan.n_hi_passes == 0 && !first)) return hipGetLastError();
   PassArgs<R> p = base;
@@ -700,7 +789,9 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
     p.x1 = p.x2 = nullptr;
     p.a0 = 1.0;
     p.dot = nullptr;
-    p.nrm1 = p.nrm2 = nullptr;
+    p.nrm1 = nullptr;
+    p.nrm2 = nullptr;
+    p.n_dot = 0;
     p.tb = (Cx<R>*)tbuf;
   } else {
     p.u_out = (Cx<R>*)so.u_out;
@@ -708,8 +799,7 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
   }
   p.part_dot = so.part_dot;
   // an extended low pass reads the neighbouring tiles of a stored input
-  if (plan.lo_ext > 0 && ((plan.lo_bits != 12 && plan.lo_bits != Geo<R>::L) ||
-                          plan.n_hi_passes == 0 || p.x1 || p.x2 || p.a0 != 1.0 || p.dot || p.nrm1))
+  if (plan.lo_ext > 0 && (p.x1 || p.x2 || p.a0 != 1.0 || p.dot || p.nrm1))
     return hipErrorInvalidValue;
   p.ext_bit = plan.lo_ext_bit - plan.lo_bits;
   launch_lo_any<R, CM>(plan.lo_bits, plan.lo_ext, c, p, n, s);
@@ -787,9 +877,37 @@ TilePlan make_tile_plan(int prec, int n) {
   return p;
 }
 
+// Sizes above one workgroup's whose vectors stay in the caches.  make_tile_plan's tiles (2^12,
+// 2^13 amplitudes) leave most of the chip idle there: at 17 atoms complex128 its forming pass ran
+// on 16 workgroups (17 us) and its low pass on 32 (12 us).  So the index is halved: low tiles of
+// about half the bits, and one high pass over the rest with runs of one cache line, 32 to 512
+// workgroups each.  A stored input of up to 18 atoms (19 in complex64) needs no high pass at all:
+// the low pass reads every neighbour beyond its tile through the cache, in one launch.  From 21
+// atoms on make_tile_plan's tiles give 256 workgroups and more.
+TilePlan sweep_plan(int prec, int n, bool stored) {
+  if (n < 13 || n > 20) return make_tile_plan(prec, n);
+  TilePlan p{};
+  p.n = n;
+  const int run = prec == kC128 ? mid_run<double>() : mid_run<float>();
+  p.lo_bits = (n + run + 1) / 2 > 9 ? (n + run + 1) / 2 : 9;
+  const int rest = n - p.lo_bits;
+  p.hi_bits = rest + run > kMidMinTile ? rest + run : kMidMinTile;
+  p.lo_ext_bit = p.lo_bits;
+  if (stored && rest <= kMaxLoExt) {
+    p.lo_ext = rest;
+    return p;
+  }
+  p.n_hi_passes = 1;
+  p.flip_lo[0] = p.lo_bits;
+  p.flip_hi[0] = n;
+  p.run_bits[0] = run;
+  p.tile_a[0] = n - (p.hi_bits - run);  // the whole tile inside the index
+  return p;
+}
+
 int64_t sweep_num_partials(int prec, int n) {
   if (n < 8) return 1;
-  const TilePlan p = make_tile_plan(prec, n);
+  const TilePlan p = sweep_plan(prec, n, false);
   const int64_t lo = int64_t(1) << (n - p.lo_bits);
   const int64_t hi = p.n_hi_passes ? int64_t(1) << (n - p.hi_bits) : 0;
   return lo > hi ? lo : hi;
@@ -797,19 +915,19 @@ int64_t sweep_num_partials(int prec, int n) {
 
 int64_t sweep_norm_partials(int prec, int n) {
   if (n < 8) return 1;
-  const TilePlan p = make_tile_plan(prec, n);
+  const TilePlan p = sweep_plan(prec, n, false);
   return p.n_hi_passes ? int64_t(1) << (n - p.hi_bits) : int64_t(1) << (n - p.lo_bits);
 }
 
 int64_t sweep_dot_partials(int prec, int n) {
   if (n < 8) return 1;
-  const TilePlan p = make_tile_plan(prec, n);
+  const TilePlan p = sweep_plan(prec, n, false);
   return int64_t(1) << (n - p.lo_bits);
 }
 
 int sweep_passes(int prec, int n) {
   if (n < 8) return 1;
-  return 1 + make_tile_plan(prec, n).n_hi_passes;
+  return 1 + sweep_plan(prec, n, false).n_hi_passes;
 }
 
 hipError_t hpsi_sweep(int prec, int n, const StepCoef& c, const double* dtab, const SweepIn& in,

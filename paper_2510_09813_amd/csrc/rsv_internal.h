@@ -65,6 +65,10 @@ struct TilePlan {
   int lo_ext, lo_ext_bit;
 };
 TilePlan make_tile_plan(int prec, int n);
+// The plan a sweep over n bits follows: make_tile_plan's, and for the sizes between one
+// workgroup's and those that fill the chip with its tiles a plan of smaller ones.
+// stored: the sweep's input is a stored vector (the forming pass of the recurrence is not).
+TilePlan sweep_plan(int prec, int n, bool stored);
 
 // Input of one H sweep: u = a0 x0 + (a1 + dot_coef * dot[0]) x1 + a2 x2 (x1, x2, dot may
 // be null).  With only x0 and a0 = 1 the sweep applies H to a stored vector.  When nrm1 is
@@ -76,10 +80,16 @@ struct SweepIn {
   const void* x1;
   const void* x2;
   double a0, a1, a2;
-  const double* dot;
+  double* dot;
   double dot_coef;
-  const double* nrm1 = nullptr;
+  double* nrm1 = nullptr;
   const double* nrm2 = nullptr;
+  // n_dot > 0: dot[0] and nrm1[0] (the latter where n_nrm > 0) are not summed yet: every
+  // workgroup of the forming pass sums these partials itself, and the first one stores the sums
+  // in dot[0] and nrm1[0]
+  const double* part_dot = nullptr;
+  const double* part_nrm = nullptr;
+  int n_dot = 0, n_nrm = 0;
 };
 // Optional outputs: u_out stores the formed u (required when the sweep forms u and has
 // more than one pass); part_norm / part_dot receive per-workgroup FP64 partial sums of |u|^2
@@ -166,7 +176,10 @@ size_t static_sample_idx_offset_bytes();
 int tridiag_expm(int m, const double* alpha, const double* beta, double tau, double* y_re,
                  double* y_im, double* work);
 size_t tridiag_work_doubles(int m);
-// |[exp(-i tau T) e_1]_{m-1}| only (rows 0 and m-1 of the eigenvectors): the convergence test.
+// The same y by a Chebyshev series where the spectrum is narrow enough: the Lanczos driver's.
+int tridiag_expm_series(int m, const double* alpha, const double* beta, double tau, double* y_re,
+                        double* y_im, double* work);
+// |[exp(-i tau T) e_1]_{m-1}| only (rows 0 and m-1 of the eigenvectors).
 int tridiag_expm_last(int m, const double* alpha, const double* beta, double tau,
                       double* last_abs, double* work);
 

@@ -154,4 +154,65 @@ int tridiag_expm_last(int m, const double* alpha, const double* beta, double tau
   return 0;
 }
 
+// The same y by the Chebyshev series of the exponential: a + 8 a^(1/3) + 20 products with T for a
+// spectrum of half-width a / tau (28 rows, a = 16: 4 us, where the eigenvectors take 40), as exact
+// (J_k by Miller's recurrence, Gershgorin bounds).  Wider spectra take the eigenvectors.
+int tridiag_expm_series(int m, const double* alpha, const double* beta, double tau, double* y_re,
+                        double* y_im, double* work) {
+  if (m <= 0 || m > kMaxKrylov) return -1;
+  double lo = DBL_MAX, hi = -DBL_MAX;
+  for (int i = 0; i < m; ++i) {
+    const double w = (i > 0 ? std::fabs(beta[i - 1]) : 0.0) + (i + 1 < m ? std::fabs(beta[i]) : 0.0);
+    lo = std::fmin(lo, alpha[i] - w);
+    hi = std::fmax(hi, alpha[i] + w);
+  }
+  const double c = 0.5 * (hi + lo), a = std::fmax(0.5 * std::fabs(tau) * (hi - lo), 0.5);
+  const double terms = a + 8.0 * std::cbrt(a) + 20.0;
+  constexpr int kMost = 256;
+  if (!(terms < kMost)) return tridiag_expm(m, alpha, beta, tau, y_re, y_im, work);
+  const int K = (int)terms, M = K + 16;
+  double bes[kMost + 18];
+  bes[M + 1] = 0.0;
+  bes[M] = 1e-250;
+  for (int k = M; k >= 1; --k) {
+    bes[k - 1] = 2.0 * k / a * bes[k] - bes[k + 1];
+    if (std::fabs(bes[k - 1]) > 1e250)
+      for (int q = k - 1; q <= M; ++q) bes[q] *= 1e-250;
+  }
+  double norm = bes[0];
+  for (int k = 2; k <= M; k += 2) norm += 2.0 * bes[k];
+  // 2 X = 2 (T - c) |tau| / a, padded by a zero row at both ends
+  const double s = 2.0 * std::fabs(tau) / a, sign = tau < 0.0 ? -1.0 : 1.0;
+  double d[kMaxKrylov + 2] = {}, o[kMaxKrylov + 2] = {}, t0[kMaxKrylov + 2] = {}, t1[kMaxKrylov + 2] = {},
+         yr[kMaxKrylov + 2] = {}, yi[kMaxKrylov + 2] = {};
+  for (int i = 0; i < m; ++i) {
+    d[i + 1] = (alpha[i] - c) * s;
+    if (i + 1 < m) o[i + 1] = beta[i] * s;  // couples rows i and i + 1
+  }
+  t0[1] = 1.0;
+  t1[1] = 0.5 * d[1];
+  if (m > 1) t1[2] = 0.5 * o[1];
+  yr[1] = bes[0] / norm;
+  for (int k = 1; k <= K; ++k) {
+    const double b = 2.0 * bes[k] / norm;
+    double* y = (k & 1) ? yi : yr;
+    const double w = (k & 2) ? ((k & 1) ? b : -b) : ((k & 1) ? -b : b);  // (-i)^k
+    for (int i = 1; i <= m; ++i) y[i] += w * t1[i];
+    for (int i = 1; i <= m; ++i)
+      t0[i] = d[i] * t1[i] + o[i - 1] * t1[i - 1] + o[i] * t1[i + 1] - t0[i];
+    for (int i = 1; i <= m; ++i) {
+      const double v = t0[i];
+      t0[i] = t1[i];
+      t1[i] = v;
+    }
+  }
+  const double pr = std::cos(tau * c), pi = -std::sin(tau * c);
+  for (int i = 0; i < m; ++i) {
+    const double re = yr[i + 1], im = sign * yi[i + 1];
+    y_re[i] = pr * re - pi * im;
+    y_im[i] = pr * im + pi * re;
+  }
+  return 0;
+}
+
 }  // namespace rsv
