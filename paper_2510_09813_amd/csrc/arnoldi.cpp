@@ -18,8 +18,10 @@ namespace {
 using cd = std::complex<double>;
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
-// dscal: |u_i|^2, the second pass's inner products, then column j's 2 (j + 2) values.
-constexpr size_t kNorms = kMaxKrylov + 2, kAgain = kNorms, kCols = kNorms + 2 * (kMaxKrylov + 2);
+// dscal: |u_i|^2, the diagonal of H as the device has it, the second pass's inner products, then
+// column j's 2 (j + 2) values.
+constexpr size_t kNorms = kMaxKrylov + 2, kDiag = kNorms, kAgain = kDiag + 2 * (kMaxKrylov + 2),
+                 kCols = kAgain + 2 * (kMaxKrylov + 2);
 inline size_t col_off(int j) { return kCols + (size_t)j * j + 3 * (size_t)j; }
 
 struct Run {
@@ -43,7 +45,9 @@ struct Run {
     a.stride = sp.vb / amp_bytes(sp.prec);
     a.count = count;
     a.w = again ? vec(j + 1) : (void*)sp.base;
+    a.shift = sp.shift ? 1 : 0;
     a.nrm2 = sp.dscal;
+    a.diag = sp.dscal + kDiag;
     a.npart = sp.npart;
     a.nparts = !again && small && j > 0 ? parts : 0;
     a.part = sp.part;
@@ -132,7 +136,9 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
           return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
         H(i, j) = scale[i] * cd(d[2 * i], d[2 * i + 1]);  // <v_i, y1>
       }
-      if (j > 0) H(j - 1, j) -= 1.0 / scale[j];  // y = y1 - beta_{j-1} v_{j-1}
+      // y = y1 - beta_{j-1} v_{j-1} (+ h_{j-1,j-1} v_j)
+      if (j > 0) H(j - 1, j) -= 1.0 / scale[j];
+      if (j > 0 && sp.shift) H(j, j) += cd(sc[kDiag + 2 * j - 2], sc[kDiag + 2 * j - 1]);
       if (!std::isfinite(beta2)) return fail(RSV_ENUMERIC, "Arnoldi residual not finite");
       bool again = false;
       if (!(beta2 >= 0.5 * y2)) {

@@ -32,7 +32,9 @@ struct ArnoldiStep {
   void* base;
   size_t stride, count;
   const void* w;
+  int shift;            // take out h_{j-1,j-1} along u_j (see gram_schmidt.hip)
   double* nrm2;         // |u_i|^2, i <= j
+  double* diag;         // shift: h_ii re, im, i < j; h_jj is added
   const double* npart;  // nparts > 0: the partials of |u_j|^2, to be summed into nrm2[j]
   int nparts;
   double* part;         // 2 (j + 2) x arnoldi_parts partial inner products
@@ -56,6 +58,7 @@ struct ArnoldiSpace {
   double* npart = nullptr;  // partials of the newest norm
   double* dscal = nullptr;  // kMaxKrylov + 2 norms, the second pass's inner products, the columns
   double* h_scal = nullptr;  // pinned host copy of dscal
+  bool shift = false;        // the operator's diagonal in the basis is far from zero (-i H)
   int hint = 0;              // dimension of the previous run: how many iterations to queue first
 };
 size_t arnoldi_device_bytes(int prec, int nb, int kmax);

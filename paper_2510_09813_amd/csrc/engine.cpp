@@ -422,6 +422,22 @@ int workspace_acquire(rsv_register* reg, int kmax) {
   return RSV_OK;
 }
 
+// The register's 2^N interaction energies in FP64, built on first use and kept.
+int register_energies(rsv_register* reg, hipStream_t s, const double** out) {
+  if (!reg->d_efull) {
+    void* p = nullptr;
+    RSV_TRY(reg->alloc->alloc((size_t(1) << reg->n) * sizeof(double), &p));
+    const hipError_t e = diag_build(kC128, reg->n, reg->d_ub, p, s);
+    if (e != hipSuccess) {
+      reg->alloc->release(p, (size_t(1) << reg->n) * sizeof(double));
+      return fail(RSV_EDEVICE, "interaction energies: %s", hipGetErrorString(e));
+    }
+    reg->d_efull = (double*)p;
+  }
+  *out = reg->d_efull;
+  return RSV_OK;
+}
+
 // ------------------------------------------------------------------------------ Lanczos
 namespace {
 

@@ -142,7 +142,7 @@ struct rsv_register {
   double u_abs = 0;  // sum of |U_ij| over the pairs
   double* d_dtab = nullptr;  // interaction-diagonal tables of the H psi low pass
   void* d_hbuf = nullptr;  // high-bit partial of rsv_apply_hamiltonian
-  double* d_efull = nullptr;  // the 2^N interaction energies (FP64) of the Lindblad path
+  double* d_efull = nullptr;  // the 2^N interaction energies (register_energies)
   size_t bytes = 0;
   rsv::Workspace ws;
   double* h_scal = nullptr;  // pinned host scalars of the per-iteration exchange
@@ -171,6 +171,8 @@ int register_create(rsv_ctx* ctx, Allocator* alloc, int n, const double* xyz, do
                     int prec, hipStream_t stream, double* h_scal, rsv_register** out);
 void register_destroy(rsv_register* reg, hipStream_t stream);
 int workspace_acquire(rsv_register* reg, int kmax);
+// The register's 2^n interaction energies in FP64 on the device, built on first use and kept.
+int register_energies(rsv_register* reg, hipStream_t s, const double** out);
 
 // Evolves d_psi (2^n amplitudes of the register's precision) in place on `stream`.
 // With obs_out set, <n_i> of the state after every obs_every-th step are written to

@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "arnoldi.h"
+#include "augmented.h"
 #include "engine.h"
 
 using namespace rsv;
@@ -113,6 +114,9 @@ int rsv_gradient_occupations(rsv_register* reg, const rsv_pulses* pl, const rsv_
   RSV_TRY(arnoldi_host(reg, &h_scal));
   ArnoldiSpace sp;
   arnoldi_carve(p + fixed, h_scal, prec, n + 1, o->kmax, &sp);
+  sp.shift = true;
+  const double* energy = nullptr;
+  if (n <= kMaxAugmentedAtoms) RSV_TRY(register_energies(reg, s, &energy));
   HIP_TRY(hipMemsetAsync(zt, 0, tabs, s));
   if (psi0_host) {
     if (prec == kC128) {
@@ -169,8 +173,13 @@ int rsv_gradient_occupations(rsv_register* reg, const rsv_pulses* pl, const rsv_
         for (int q = 0; q < n; ++q) v.delta[q] = 1.0;
       }
       v.mode = kCoefSite;
+      const AugmentedCoef ac{n, which, c.up_re[0], c.up_im[0], c.delta[0], v.up_re[0], v.up_im[0]};
       // (a, b) -> -i (H a + V b, H b) on the augmented vector
       const OpFn op = [&](const void* in, void* out, hipStream_t st_) -> int {
+        if (energy) {
+          HIP_TRY(augmented_apply(prec, ac, energy, in, out, st_));
+          return RSV_OK;
+        }
         const char* ia = (const char*)in;
         const char* ib = ia + vraw;
         char* oa = (char*)out;

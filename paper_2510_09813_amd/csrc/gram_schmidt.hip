@@ -15,11 +15,15 @@
 // work on y1 = y + beta_{j-1} v_{j-1}; the inner products then measure what is left, the
 // coefficient of v_{j-1} is the sum of both parts, and the criterion compares with |y1|.  For
 // another operator the guess is merely a poor one: the result is the same, with more second passes.
+// With `shift` (the gradients' operator -i H, whose mean energy is far from zero) the diagonal
+// entry of the iteration before is taken out along u_j in the same way.
 //
 // Measured, with the host part of arnoldi.cpp, against inner products and coefficients that went
 // through the host, a second pass by |y| and the whole exponential of H_m at every dimension: a
 // Lindblad step of 12 atoms (28 vectors of 256 MiB) 109 -> 72 ms, 20 steps of 6 atoms (12 vectors
 // of 64 KiB each) 40 -> 8.7 ms.
+#include <type_traits>
+
 #include "arnoldi.h"
 #include "device_common.h"
 
@@ -31,32 +35,33 @@ __device__ __forceinline__ const Cx<R>* basis_vec(const ArnoldiStep& a, int i) {
   return i == 0 ? (const Cx<R>*)a.v0 : (const Cx<R>*)a.base + (size_t)i * a.stride;
 }
 
-// Sum of p[0..n), n <= kSmallParts, by every wave for itself (fixed order).
+// Sum of p[0..n), n <= kSmallParts, by every wave for itself (fixed order, uniform).
 __device__ __forceinline__ double wave_parts(const double* p, int n) {
   const int lane = threadIdx.x & 63;
   double v = lane < n ? p[lane] : 0.0;
   if (lane + 64 < n) v += p[lane + 64];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  return wave_total(v);
 }
 
 struct Scales {
-  double f, g;  // y1 = f w + g u_{j-1}
+  double f, g;    // y1 = f w + g u_{j-1} + (hr + i hi) u_j
+  double hr, hi;
 };
 
 // The coefficients of y1, with |u_j|^2 from its partial sums where they are not summed yet.
 __device__ __forceinline__ Scales scales(const ArnoldiStep& a, double n2) {
-  if (a.again) return Scales{1.0, 0.0};
+  if (a.again) return Scales{1.0, 0.0, 0.0, 0.0};
   const double s = 1.0 / sqrt(n2);
-  return Scales{s, a.j > 0 ? sqrt(n2) / sqrt(a.nrm2[a.j - 1]) : 0.0};
+  const bool sh = a.shift && a.j > 0;
+  return Scales{s, a.j > 0 ? sqrt(n2) / sqrt(a.nrm2[a.j - 1]) : 0.0,
+                sh ? -s * a.diag[2 * a.j - 2] : 0.0, sh ? -s * a.diag[2 * a.j - 1] : 0.0};
 }
 
 // Partial inner products <u_i, y1> (i <= j) and <y1, y1> (i = j + 1) of group blockIdx.y.
 template <class R>
 __global__ __launch_bounds__(kBlock) void arnoldi_dots_kernel(const ArnoldiStep a) {
   constexpr int G = kArnoldiGroup;
-  __shared__ double red[4][2 * G];
+  __shared__ double red[16][2 * G];  // per row of 16 lanes
   double n2;
   if (!a.again && a.nparts > 0) {
     n2 = wave_parts(a.npart, a.nparts);
@@ -67,6 +72,7 @@ __global__ __launch_bounds__(kBlock) void arnoldi_dots_kernel(const ArnoldiStep 
   const Scales sc = scales(a, n2);
   const Cx<R>* w = (const Cx<R>*)a.w;
   const Cx<R>* prev = sc.g != 0.0 ? basis_vec<R>(a, a.j - 1) : nullptr;
+  const Cx<R>* own = sc.hr != 0.0 || sc.hi != 0.0 ? basis_vec<R>(a, a.j) : nullptr;
   const int i0 = blockIdx.y * G, total = a.j + 2;
   const Cx<R>* x[G];
 #pragma unroll
@@ -75,36 +81,61 @@ __global__ __launch_bounds__(kBlock) void arnoldi_dots_kernel(const ArnoldiStep 
 #pragma unroll
   for (int q = 0; q < 2 * G; ++q) acc[q] = 0.0;
   const size_t stride = (size_t)gridDim.x * kBlock;
-  for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < a.count; e += stride) {
-    const Cx<R> we = w[e];
-    double yr = sc.f * (double)we.x, yi = sc.f * (double)we.y;
-    if (prev) {
-      const Cx<R> pe = prev[e];
-      yr += sc.g * (double)pe.x;
-      yi += sc.g * (double)pe.y;
+  // U elements at a time, their loads in flight together
+  auto elements = [&](size_t e0, auto ux) {
+    constexpr int U = decltype(ux)::value;
+    double yr[U], yi[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const size_t e = e0 + q * stride;
+      const Cx<R> we = w[e];
+      yr[q] = sc.f * (double)we.x;
+      yi[q] = sc.f * (double)we.y;
+      if (prev) {
+        const Cx<R> pe = prev[e];
+        yr[q] += sc.g * (double)pe.x;
+        yi[q] += sc.g * (double)pe.y;
+      }
+      if (own) {
+        const Cx<R> oe = own[e];
+        yr[q] += sc.hr * (double)oe.x - sc.hi * (double)oe.y;
+        yi[q] += sc.hr * (double)oe.y + sc.hi * (double)oe.x;
+      }
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       if (x[g]) {
-        const Cx<R> xe = x[g][e];
-        acc[2 * g] += (double)xe.x * yr + (double)xe.y * yi;
-        acc[2 * g + 1] += (double)xe.x * yi - (double)xe.y * yr;
+        Cx<R> xe[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) xe[q] = x[g][e0 + q * stride];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+          acc[2 * g] += (double)xe[q].x * yr[q] + (double)xe[q].y * yi[q];
+          acc[2 * g + 1] += (double)xe[q].x * yi[q] - (double)xe[q].y * yr[q];
+        }
       } else if (i0 + g == a.j + 1) {
-        acc[2 * g] += yr * yr + yi * yi;
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc[2 * g] += yr[q] * yr[q] + yi[q] * yi[q];
       }
     }
-  }
+  };
+  size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+  for (; e + stride < a.count; e += 2 * stride) elements(e, std::integral_constant<int, 2>());
+  for (; e < a.count; e += stride) elements(e, std::integral_constant<int, 1>());
+  // (DPP adds inside rows of 16 lanes: a shuffle tree over the wave for 16 values costs more than
+  // the loads at these sizes)
 #pragma unroll
   for (int q = 0; q < 2 * G; ++q) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = acc[q];
+    const double v = row_reduce(acc[q], OpAdd());
+    if ((threadIdx.x & 15) == 0) red[threadIdx.x >> 4][q] = v;
   }
   __syncthreads();
   if (threadIdx.x < 2 * G && i0 + (int)(threadIdx.x >> 1) < total) {
     const int q = threadIdx.x;
-    a.part[(size_t)(2 * i0 + q) * gridDim.x + blockIdx.x] =
-        (red[0][q] + red[1][q]) + (red[2][q] + red[3][q]);
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v += red[r][q];
+    a.part[(size_t)(2 * i0 + q) * gridDim.x + blockIdx.x] = v;
   }
 }
 
@@ -114,10 +145,22 @@ template <class R>
 __global__ __launch_bounds__(kBlock) void arnoldi_update_kernel(const ArnoldiStep a) {
   __shared__ double cr[kMaxKrylov + 2], ci[kMaxKrylov + 2], red[4];
   const int rows = 2 * (a.j + 2), tid = threadIdx.x;
-  if (a.dparts > 0) {  // sum the partial inner products, one wave per value
-    for (int r = tid >> 6; r < rows; r += kBlock / 64) {
-      const double v = wave_parts(a.part + (size_t)r * a.dparts, a.dparts);
-      if ((tid & 63) == 0) ((r & 1) ? ci : cr)[r >> 1] = v;
+  if (a.dparts > 0) {
+    // sum the partial inner products: eight lanes per value, every load of a lane in flight (one
+    // wave per value took a memory latency for each of its turns)
+    static_assert(kSmallParts == 128, "16 partials per lane");
+    for (int r0 = 0; r0 < rows; r0 += kBlock / 8) {
+      const int r = r0 + (tid >> 3), l = tid & 7;
+      const double* q = a.part + (size_t)(r < rows ? r : 0) * a.dparts;
+      double v[16], t = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = l + 8 * k < a.dparts ? q[l + 8 * k] : 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) t += v[k];
+      t += dpp<kDppXor1>(t);
+      t += dpp<kDppXor2>(t);
+      t += dpp<kDppHalfMirror>(t);
+      if (l == 0 && r < rows) ((r & 1) ? ci : cr)[r >> 1] = t;
     }
     __syncthreads();
     if (blockIdx.x == 0 && tid < kBlock)
@@ -127,33 +170,55 @@ __global__ __launch_bounds__(kBlock) void arnoldi_update_kernel(const ArnoldiSte
     __syncthreads();
   }
   const Scales sc = scales(a, a.nrm2[a.j]);
+  if (!a.again && a.shift && blockIdx.x == 0 && tid == 0) {
+    // h_jj = <v_j, y>: what the inner product measured and what was taken out before it
+    a.diag[2 * a.j] = sc.f * cr[a.j] + (a.j > 0 ? a.diag[2 * a.j - 2] : 0.0);
+    a.diag[2 * a.j + 1] = sc.f * ci[a.j] + (a.j > 0 ? a.diag[2 * a.j - 1] : 0.0);
+  }
+  __syncthreads();
   if (tid <= a.j) {
     const double s2 = 1.0 / a.nrm2[tid];  // v_i = u_i / |u_i|
-    cr[tid] = -s2 * cr[tid] + (tid == a.j - 1 ? sc.g : 0.0);
-    ci[tid] = -s2 * ci[tid];
+    cr[tid] = -s2 * cr[tid] + (tid == a.j - 1 ? sc.g : tid == a.j ? sc.hr : 0.0);
+    ci[tid] = -s2 * ci[tid] + (tid == a.j ? sc.hi : 0.0);
   }
   __syncthreads();
   const Cx<R>* w = (const Cx<R>*)a.w;
   Cx<R>* out = (Cx<R>*)a.base + (size_t)(a.j + 1) * a.stride;
   double acc = 0.0;
   const size_t stride = (size_t)gridDim.x * kBlock;
-  for (size_t e = (size_t)blockIdx.x * kBlock + tid; e < a.count; e += stride) {
-    const Cx<R> we = w[e], x0 = ((const Cx<R>*)a.v0)[e];
-    double re = sc.f * (double)we.x + (cr[0] * (double)x0.x - ci[0] * (double)x0.y);
-    double im = sc.f * (double)we.y + (cr[0] * (double)x0.y + ci[0] * (double)x0.x);
-    const Cx<R>* x = (const Cx<R>*)a.base + a.stride + e;
+  auto elements = [&](size_t e0, auto ux) {
+    constexpr int U = decltype(ux)::value;
+    double re[U], im[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const Cx<R> we = w[e0 + q * stride], x0 = ((const Cx<R>*)a.v0)[e0 + q * stride];
+      re[q] = sc.f * (double)we.x + (cr[0] * (double)x0.x - ci[0] * (double)x0.y);
+      im[q] = sc.f * (double)we.y + (cr[0] * (double)x0.y + ci[0] * (double)x0.x);
+    }
+    const Cx<R>* x = (const Cx<R>*)a.base + a.stride + e0;
 #pragma unroll 4
     for (int i = 1; i <= a.j; ++i, x += a.stride) {
-      const Cx<R> xe = *x;
-      re += cr[i] * (double)xe.x - ci[i] * (double)xe.y;
-      im += cr[i] * (double)xe.y + ci[i] * (double)xe.x;
+      Cx<R> xe[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) xe[q] = x[q * stride];
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        re[q] += cr[i] * (double)xe[q].x - ci[i] * (double)xe[q].y;
+        im[q] += cr[i] * (double)xe[q].y + ci[i] * (double)xe[q].x;
+      }
     }
-    Cx<R> r;
-    r.x = (R)re;
-    r.y = (R)im;
-    out[e] = r;
-    acc = norm_add(acc, (double)r.x, (double)r.y);
-  }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      Cx<R> r;
+      r.x = (R)re[q];
+      r.y = (R)im[q];
+      out[e0 + q * stride] = r;
+      acc = norm_add(acc, (double)r.x, (double)r.y);
+    }
+  };
+  size_t e = (size_t)blockIdx.x * kBlock + tid;
+  for (; e + stride < a.count; e += 2 * stride) elements(e, std::integral_constant<int, 2>());
+  for (; e < a.count; e += stride) elements(e, std::integral_constant<int, 1>());
   const double t = block_sum_256(acc, red);
   if (tid == 0) a.npart_out[blockIdx.x] = t;
 }

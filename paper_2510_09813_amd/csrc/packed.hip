@@ -47,49 +47,6 @@ namespace {
 constexpr int kMaxBessel = 512;
 constexpr int kBesselPad = 16;  // Miller's start above the last term, and the loop's round-up
 
-// ------------------------------------------------------------------ sums inside a wave (DPP)
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)b, CTRL, 0xF, 0xF, true);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_update_dpp(
-                                       0u, __builtin_bit_cast(uint32_t, v), CTRL, 0xF, 0xF, true));
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-constexpr int kDppFromBelow = 0x138, kDppFromAbove = 0x130;  // lane i takes lane i - 1 / i + 1
-
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
-  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
-struct OpAdd { __device__ double operator()(double a, double b) const { return a + b; } };
-struct OpMin { __device__ double operator()(double a, double b) const { return fmin(a, b); } };
-struct OpMax { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
-
-// Reduction over rows of 16 lanes, the same value in all of a row's lanes.
-template <class Op>
-__device__ __forceinline__ double row_reduce(double v, Op op) {
-  v = op(v, dpp<kDppXor1>(v));
-  v = op(v, dpp<kDppXor2>(v));
-  v = op(v, dpp<kDppHalfMirror>(v));
-  return op(v, dpp<kDppMirror>(v));
-}
-// Over the wave, uniform.  Every lane must be active.
-template <class Op>
-__device__ __forceinline__ double wave_reduce(double v, Op op) {
-  v = row_reduce(v, op);
-  return op(op(lane_value(v, 0), lane_value(v, 16)), op(lane_value(v, 32), lane_value(v, 48)));
-}
-__device__ __forceinline__ double wave_total(double v) { return wave_reduce(v, OpAdd()); }
-
 // exp(i x).  Not inlined: its range reduction would take registers from the whole kernel.
 __device__ __attribute__((noinline)) double2 unit_phase(double x) {
   double s, c;
