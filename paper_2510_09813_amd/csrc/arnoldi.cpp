@@ -45,6 +45,7 @@ struct Run {
     a.stride = sp.vb / amp_bytes(sp.prec);
     a.count = count;
     a.w = again ? vec(j + 1) : (void*)sp.base;
+    a.herm = sp.herm;
     a.shift = sp.shift ? 1 : 0;
     a.nrm2 = sp.dscal;
     a.diag = sp.dscal + kDiag;
@@ -60,7 +61,7 @@ struct Run {
   int orthogonalise(int j, bool again) {
     const ArnoldiStep a = step(j, again);
     HIP_TRY(arnoldi_dots(sp.prec, a, s));
-    if (!small) HIP_TRY(finalize_rows(sp.part, parts, 2 * (j + 2), a.dots, s));
+    if (!small) HIP_TRY(finalize_rows(sp.part, parts, (sp.herm ? 1 : 2) * (j + 2), a.dots, s));
     HIP_TRY(arnoldi_update(sp.prec, a, s));
     if (!small) HIP_TRY(finalize_sum(sp.npart, parts, sp.dscal + j + 1, s));
     return RSV_OK;
@@ -72,7 +73,7 @@ struct Run {
   }
   // |u_upto|^2 and everything up to column upto - 1 (or the second pass's inner products).
   int fetch(int upto) {
-    if (small) HIP_TRY(finalize_sum(sp.npart, parts, sp.dscal + upto, s));
+    if (small) HIP_TRY(arnoldi_norm(sp.npart, parts, sp.dscal + upto, s));
     HIP_TRY(hipMemcpyAsync(sp.h_scal, sp.dscal, col_off(upto) * sizeof(double),
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -109,7 +110,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
     for (int l = 0; l < dim; ++l) {
       const cd c = nx * scale[l] * y[l];
       cc.re[l] = c.real();
-      cc.im[l] = c.imag();
+      cc.im[l] = sp.herm ? 0.0 : c.imag();  // (real there up to rounding)
       cc.x[l] = run.vec(l);
     }
     *sub = part;
@@ -128,13 +129,18 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
       course.start(tau, nx);
     }
     for (int j = m; j < upto; ++j) {
+      // inner product i as fetched at d (real ones for Hermitian matrices)
+      auto value = [&](const double* d, int i) {
+        return sp.herm ? cd(d[i], 0.0) : cd(d[2 * i], d[2 * i + 1]);
+      };
       const double* d = sc + col_off(j);
-      const double y2 = d[2 * (j + 1)];
+      const double y2 = value(d, j + 1).real();
       double beta2 = sc[j + 1];
       for (int i = 0; i <= j; ++i) {
-        if (!std::isfinite(d[2 * i]) || !std::isfinite(d[2 * i + 1]))
+        const cd di = value(d, i);
+        if (!std::isfinite(di.real()) || !std::isfinite(di.imag()))
           return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
-        H(i, j) = scale[i] * cd(d[2 * i], d[2 * i + 1]);  // <v_i, y1>
+        H(i, j) = scale[i] * di;  // <v_i, y1>
       }
       // y = y1 - beta_{j-1} v_{j-1} (+ h_{j-1,j-1} v_j)
       if (j > 0) H(j - 1, j) -= 1.0 / scale[j];
@@ -149,7 +155,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
         RSV_TRY(run.orthogonalise(j, true));
         RSV_TRY(run.fetch(j + 1));
         for (int i = 0; i <= j; ++i) {
-          const cd d2(sc[kAgain + 2 * i], sc[kAgain + 2 * i + 1]);
+          const cd d2 = value(sc + kAgain, i);
           if (!std::isfinite(d2.real()) || !std::isfinite(d2.imag()))
             return fail(RSV_ENUMERIC, "Arnoldi inner product not finite");
           H(i, j) += scale[i] * d2;

@@ -22,6 +22,7 @@ int hess_expm_e1(int m, const std::complex<double>* a, int ld, double tau, std::
 
 // ------------------------------------------------------------------------------- kernels
 constexpr int kArnoldiGroup = 8;  // vectors per pass over y in the inner products
+constexpr int kHermGroup = 16;    // the same of Hermitian matrices, whose inner products are real
 constexpr int kSmallBits = 18;    // vectors up to 2^18 elements: partial sums summed by their reader
 constexpr int kSmallParts = 128;  // at most
 // One Gram-Schmidt pass of iteration j.  u_0 = v0, u_i = base + i stride (elements); w = Op u_j
@@ -32,6 +33,8 @@ struct ArnoldiStep {
   void* base;
   size_t stride, count;
   const void* w;
+  int herm;             // > 0: vectors are Hermitian 2^herm x 2^herm matrices (long vectors only);
+                        // dots then holds j + 2 real values
   int shift;            // take out h_{j-1,j-1} along u_j (see gram_schmidt.hip)
   double* nrm2;         // |u_i|^2, i <= j
   double* diag;         // shift: h_ii re, im, i < j; h_jj is added
@@ -45,6 +48,11 @@ struct ArnoldiStep {
 int arnoldi_parts(size_t count);
 hipError_t arnoldi_dots(int prec, const ArnoldiStep& a, hipStream_t s);
 hipError_t arnoldi_update(int prec, const ArnoldiStep& a, hipStream_t s);
+// |u_{j+1}|^2 from a small vector's partial sums.
+hipError_t arnoldi_norm(const double* npart, int parts, double* out, hipStream_t s);
+// Partials of |x - x^+|^2, then of |x|^2 (arnoldi_parts(4^n) each), of a 2^n x 2^n matrix; with
+// write, x <- (x + x^+) / 2 instead.  n >= 5.
+hipError_t hermitise(int prec, int n, void* x, bool write, double* part, hipStream_t s);
 
 // ------------------------------------------------------------------------------- process
 // Device vectors of 2^nb amplitudes (storage precision prec): the Krylov basis (kmax vectors
@@ -58,6 +66,7 @@ struct ArnoldiSpace {
   double* npart = nullptr;  // partials of the newest norm
   double* dscal = nullptr;  // kMaxKrylov + 2 norms, the second pass's inner products, the columns
   double* h_scal = nullptr;  // pinned host copy of dscal
+  int herm = 0;              // the vectors are Hermitian 2^herm x 2^herm matrices and op keeps them so
   bool shift = false;        // the operator's diagonal in the basis is far from zero (-i H)
   int hint = 0;              // dimension of the previous run: how many iterations to queue first
 };

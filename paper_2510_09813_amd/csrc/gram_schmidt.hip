@@ -20,12 +20,13 @@
 //
 // Measured, with the host part of arnoldi.cpp, against inner products and coefficients that went
 // through the host, a second pass by |y| and the whole exponential of H_m at every dimension: a
-// Lindblad step of 12 atoms (28 vectors of 256 MiB) 109 -> 72 ms, 20 steps of 6 atoms (12 vectors
-// of 64 KiB each) 40 -> 8.7 ms.
+// Lindblad step of 12 atoms (28 vectors of 256 MiB) 109 -> 72 ms (35 ms with the Hermitian forms
+// below), 20 steps of 6 atoms (12 vectors of 64 KiB each) 40 -> 7.2 ms.
 #include <type_traits>
 
 #include "arnoldi.h"
 #include "device_common.h"
+#include "herm_tile.h"
 
 namespace rsv {
 namespace {
@@ -223,6 +224,213 @@ __global__ __launch_bounds__(kBlock) void arnoldi_update_kernel(const ArnoldiSte
   if (tid == 0) a.npart_out[blockIdx.x] = t;
 }
 
+// ---------------------------------------------------------------------- Hermitian matrices
+// The Liouvillian maps Hermitian matrices to Hermitian matrices, so from a Hermitian density
+// matrix every Krylov vector is one, and the inner product of two is real and follows from one
+// triangle.  These forms of the two kernels read the upper triangle's tiles only: half the bytes of
+// the basis, which bound both.  The update writes both triangles, because the operator reads whole
+// rows and columns.  Means over a step of 12 atoms complex128 (28 vectors of 256 MiB): inner
+// products 855 -> 394 us, update 905 -> 490 us, both at 4.2 to 5.1 TB/s in the last iterations;
+// with the operator's half (527 -> 245 us) the step went from 72 to 35 ms.
+template <class R>
+__global__ __launch_bounds__(kBlock) void herm_dots_kernel(const ArnoldiStep a, const uint32_t tiles) {
+  constexpr int G = kHermGroup;
+  __shared__ double red[16][G];
+  const Scales sc = scales(a, a.nrm2[a.j]);
+  const Cx<R>* w = (const Cx<R>*)a.w;
+  const Cx<R>* prev = sc.g != 0.0 ? basis_vec<R>(a, a.j - 1) : nullptr;
+  const int i0 = blockIdx.y * G, total = a.j + 2;
+  double acc[G];
+#pragma unroll
+  for (int q = 0; q < G; ++q) acc[q] = 0.0;
+  const uint32_t row0 = threadIdx.x >> 5, col = threadIdx.x & 31;
+  const uint32_t b0 = xcd_remap(blockIdx.x, gridDim.x);
+  for (uint32_t t = b0; t < tiles; t += gridDim.x) {
+    const HermTile h = herm_tile(t, a.herm, true);
+    const size_t e0 = h.base + ((size_t)row0 << a.herm) + col;
+    double yr[kTileElems], yi[kTileElems];
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      const size_t e = e0 + ((size_t)(kTileRows * q) << a.herm);
+      const Cx<R> we = w[e];
+      const double wt = herm_weight(h, row0 + kTileRows * q, col);
+      yr[q] = sc.f * (double)we.x;
+      yi[q] = sc.f * (double)we.y;
+      if (prev) {
+        const Cx<R> pe = prev[e];
+        yr[q] += sc.g * (double)pe.x;
+        yi[q] += sc.g * (double)pe.y;
+      }
+      if (i0 + G >= total && i0 < total) {  // this group holds <y1, y1>
+        const int self = a.j + 1 - i0;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          if (g == self) acc[g] += wt * (yr[q] * yr[q] + yi[q] * yi[q]);
+      }
+      yr[q] *= wt;
+      yi[q] *= wt;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (i0 + g > a.j) continue;
+      const Cx<R>* x = basis_vec<R>(a, i0 + g) + e0;
+      Cx<R> xe[kTileElems];
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) xe[q] = x[(size_t)(kTileRows * q) << a.herm];
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) acc[g] += (double)xe[q].x * yr[q] + (double)xe[q].y * yi[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < G; ++q) {
+    const double v = row_reduce(acc[q], OpAdd());
+    if ((threadIdx.x & 15) == 0) red[threadIdx.x >> 4][q] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < G && i0 + (int)threadIdx.x < total) {
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v += red[r][threadIdx.x];
+    a.part[(size_t)(i0 + threadIdx.x) * gridDim.x + blockIdx.x] = v;
+  }
+}
+
+template <class R>
+__global__ __launch_bounds__(kBlock) void herm_update_kernel(const ArnoldiStep a, const uint32_t tiles) {
+  __shared__ double cr[kMaxKrylov + 2], red[4];
+  __shared__ Cx<R> lds[kTileSide][kTileSide + 1];
+  const int tid = threadIdx.x;
+  const Scales sc = scales(a, a.nrm2[a.j]);
+  if (tid <= a.j) cr[tid] = -a.dots[tid] / a.nrm2[tid] + (tid == a.j - 1 ? sc.g : 0.0);
+  __syncthreads();
+  const Cx<R>* w = (const Cx<R>*)a.w;
+  Cx<R>* out = (Cx<R>*)a.base + (size_t)(a.j + 1) * a.stride;
+  const uint32_t row0 = tid >> 5, col = tid & 31;
+  const uint32_t b0 = xcd_remap(blockIdx.x, gridDim.x);
+  double acc = 0.0;
+  for (uint32_t t = b0; t < tiles; t += gridDim.x) {
+    const HermTile h = herm_tile(t, a.herm, true);
+    const size_t e0 = h.base + ((size_t)row0 << a.herm) + col;
+    double re[kTileElems], im[kTileElems];
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      const size_t e = e0 + ((size_t)(kTileRows * q) << a.herm);
+      const Cx<R> we = w[e], x0 = ((const Cx<R>*)a.v0)[e];
+      re[q] = sc.f * (double)we.x + cr[0] * (double)x0.x;
+      im[q] = sc.f * (double)we.y + cr[0] * (double)x0.y;
+    }
+    const Cx<R>* x = (const Cx<R>*)a.base + a.stride + e0;
+#pragma unroll 2
+    for (int i = 1; i <= a.j; ++i, x += a.stride) {
+      const double c = cr[i];
+      Cx<R> xe[kTileElems];
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) xe[q] = x[(size_t)(kTileRows * q) << a.herm];
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) {
+        re[q] += c * (double)xe[q].x;
+        im[q] += c * (double)xe[q].y;
+      }
+    }
+    Cx<R> r[kTileElems];
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      const uint32_t row = row0 + kTileRows * q;
+      r[q].x = (R)re[q];
+      r[q].y = h.R == h.C && row == col ? (R)0 : (R)im[q];
+      lds[row][col] = r[q];
+      acc += herm_weight(h, row, col) * norm_add(0.0, (double)r[q].x, (double)r[q].y);
+    }
+    __syncthreads();
+    // the conjugate transpose: into the mirrored tile, or the lower half of a diagonal one
+    const size_t m0 = ((size_t)(h.C * kTileSide + row0) << a.herm) + h.R * kTileSide + col;
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      const uint32_t row = row0 + kTileRows * q;
+      const Cx<R> tr = lds[col][row], cj = {tr.x, -tr.y};
+      const size_t e = e0 + ((size_t)(kTileRows * q) << a.herm);
+      if (h.R != h.C) {
+        out[e] = r[q];
+        out[m0 + ((size_t)(kTileRows * q) << a.herm)] = cj;
+      } else {
+        const bool own = col >= row;
+        out[e] = Cx<R>{own ? r[q].x : cj.x, own ? r[q].y : cj.y};
+      }
+    }
+    __syncthreads();
+  }
+  const double t = block_sum_256(acc, red);
+  if (tid == 0) a.npart_out[blockIdx.x] = t;
+}
+
+// |u_j|^2 of a small vector for the host, in the order in which the other kernels sum it: the
+// coefficients do not depend on where a run of iterations ends.
+__global__ __launch_bounds__(64) void arnoldi_norm_kernel(const double* npart, int parts, double* out) {
+  const double v = wave_parts(npart, parts);
+  if (threadIdx.x == 0) *out = v;
+}
+
+// Partials of |x - x^+|^2 and |x|^2 (write = 0), or x <- (x + x^+) / 2 (write = 1).
+template <class R>
+__global__ __launch_bounds__(kBlock) void hermitise_kernel(Cx<R>* __restrict__ x, const int n,
+                                                           const uint32_t tiles, const int write,
+                                                           double* __restrict__ part) {
+  __shared__ Cx<R> lds[kTileSide][kTileSide + 1];
+  __shared__ double red[4];
+  const uint32_t tid = threadIdx.x, row0 = tid >> 5, col = tid & 31;
+  double diff = 0.0, all = 0.0;
+  for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const HermTile h = herm_tile(t, n, true);
+    const size_t e0 = h.base + ((size_t)row0 << n) + col;
+    const size_t m0 = ((size_t)(h.C * kTileSide + row0) << n) + h.R * kTileSide + col;
+    Cx<R> v[kTileElems];
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      v[q] = x[e0 + ((size_t)(kTileRows * q) << n)];
+      lds[row0 + kTileRows * q][col] = x[m0 + ((size_t)(kTileRows * q) << n)];
+    }
+    __syncthreads();
+    Cx<R> s[kTileElems];
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      const uint32_t row = row0 + kTileRows * q;
+      const Cx<R> o = lds[col][row];  // the mirrored element
+      const double wt = herm_weight(h, row, col);
+      const double dx = (double)v[q].x - (double)o.x, dy = (double)v[q].y + (double)o.y;
+      diff += wt * (dx * dx + dy * dy);
+      all += 0.5 * wt * ((double)v[q].x * (double)v[q].x + (double)v[q].y * (double)v[q].y +
+                         (double)o.x * (double)o.x + (double)o.y * (double)o.y);
+      s[q].x = (R)(0.5 * ((double)v[q].x + (double)o.x));
+      s[q].y = (R)(0.5 * ((double)v[q].y - (double)o.y));
+    }
+    __syncthreads();
+    if (write) {
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) {
+        x[e0 + ((size_t)(kTileRows * q) << n)] = s[q];
+        lds[row0 + kTileRows * q][col] = s[q];
+      }
+      __syncthreads();
+      if (h.R != h.C) {
+#pragma unroll
+        for (int q = 0; q < kTileElems; ++q) {
+          const Cx<R> o = lds[col][row0 + kTileRows * q];
+          x[m0 + ((size_t)(kTileRows * q) << n)] = Cx<R>{o.x, -o.y};
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (!write) {
+    const double a = block_sum_256(diff, red);
+    const double b = block_sum_256(all, red);
+    if (tid == 0) {
+      part[blockIdx.x] = a;
+      part[gridDim.x + blockIdx.x] = b;
+    }
+  }
+}
+
 }  // namespace
 
 int arnoldi_parts(size_t count) {
@@ -235,6 +443,14 @@ int arnoldi_parts(size_t count) {
 }
 
 hipError_t arnoldi_dots(int prec, const ArnoldiStep& a, hipStream_t s) {
+  if (a.herm) {
+    const dim3 g(arnoldi_parts(a.count), (a.j + 2 + kHermGroup - 1) / kHermGroup);
+    if (prec == kC128)
+      hipLaunchKernelGGL(herm_dots_kernel<double>, g, dim3(kBlock), 0, s, a, herm_tiles(a.herm, true));
+    else
+      hipLaunchKernelGGL(herm_dots_kernel<float>, g, dim3(kBlock), 0, s, a, herm_tiles(a.herm, true));
+    return hipGetLastError();
+  }
   const dim3 grid(arnoldi_parts(a.count), (a.j + 2 + kArnoldiGroup - 1) / kArnoldiGroup);
   if (prec == kC128)
     hipLaunchKernelGGL(arnoldi_dots_kernel<double>, grid, dim3(kBlock), 0, s, a);
@@ -245,10 +461,33 @@ hipError_t arnoldi_dots(int prec, const ArnoldiStep& a, hipStream_t s) {
 
 hipError_t arnoldi_update(int prec, const ArnoldiStep& a, hipStream_t s) {
   const dim3 grid(arnoldi_parts(a.count));
+  if (a.herm) {
+    if (prec == kC128)
+      hipLaunchKernelGGL(herm_update_kernel<double>, grid, dim3(kBlock), 0, s, a, herm_tiles(a.herm, true));
+    else
+      hipLaunchKernelGGL(herm_update_kernel<float>, grid, dim3(kBlock), 0, s, a, herm_tiles(a.herm, true));
+    return hipGetLastError();
+  }
   if (prec == kC128)
     hipLaunchKernelGGL(arnoldi_update_kernel<double>, grid, dim3(kBlock), 0, s, a);
   else
     hipLaunchKernelGGL(arnoldi_update_kernel<float>, grid, dim3(kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t arnoldi_norm(const double* npart, int parts, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(arnoldi_norm_kernel, dim3(1), dim3(64), 0, s, npart, parts, out);
+  return hipGetLastError();
+}
+
+hipError_t hermitise(int prec, int n, void* x, bool write, double* part, hipStream_t s) {
+  const dim3 grid(arnoldi_parts(size_t(1) << (2 * n)));
+  if (prec == kC128)
+    hipLaunchKernelGGL(hermitise_kernel<double>, grid, dim3(kBlock), 0, s, (double2*)x, n,
+                       herm_tiles(n, true), write ? 1 : 0, part);
+  else
+    hipLaunchKernelGGL(hermitise_kernel<float>, grid, dim3(kBlock), 0, s, (float2*)x, n,
+                       herm_tiles(n, true), write ? 1 : 0, part);
   return hipGetLastError();
 }
 

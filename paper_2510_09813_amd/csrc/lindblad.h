@@ -20,9 +20,10 @@ struct LindbladCoef {
 };
 
 // y = L x for vectorised density matrices of 4^n amplitudes; e: the 2^n interaction energies
-// (FP64, device).
+// (FP64, device).  upper (n >= 10): only the 32 x 32 tiles of the upper triangle, diagonal ones
+// whole, are written (x Hermitian: the rest of y follows).
 hipError_t liouvillian_apply(int prec, const LindbladCoef& c, const double* e, const void* x,
-                             void* y, hipStream_t s);
+                             void* y, bool upper, hipStream_t s);
 // out[r] = Re rho_rr for r < 2^n (device FP64).
 hipError_t rho_diagonal(int prec, int n, const void* x, double* out, hipStream_t s);
 

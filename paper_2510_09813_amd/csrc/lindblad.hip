@@ -16,10 +16,10 @@
 // where D_x = E_x - sum_p delta_p x_p is H's diagonal (E_x the interaction energy of pattern
 // x), h(1) = <1|h_p|0> = Omega_p/2 e^{-i phi_p} and h(0) = <0|h_p|1>.  Every element needs
 // 3n + 1 inputs; arithmetic is FP64, results are stored in the storage precision, and the
-// 4^n vector is at most 4 GiB (n <= 14).  Up to 12 atoms one thread per element gathers its
-// inputs through the cache (the whole density matrix fits the 256 MB last-level cache); from
-// 13 atoms on, tiles of 4096 elements go through LDS.
+// 4^n vector is at most 4 GiB (n <= 14).  Up to 9 atoms (4 MiB, one L2) one thread per element
+// gathers its inputs through the cache; from 10 atoms on, tiles of 32 x 32 go through LDS.
 #include "device_common.h"
+#include "herm_tile.h"
 #include "lindblad.h"
 
 namespace rsv {
@@ -77,130 +77,132 @@ __global__ __launch_bounds__(kBlock) void liouvillian_kernel(const LindbladCoef 
   }
 }
 
-// The same operator on tiles of 2^12 consecutive elements (n >= 13), one tile per
-// workgroup.  The tile holds whole column ranges: its columns' flips (index bits 0..11) read
-// LDS.  Every index bit above the tile (all row bits, and from 13 atoms the top column bits)
-// has one value across the tile, so its flip reads the neighbouring tile in one coalesced
-// sweep with one coefficient for the workgroup; as in the H|psi> low pass, the loads of one
-// neighbour tile are issued together before any is used, and all of them before the
-// barrier.  A relaxation source rho_{r|p, c|p} lies in the tile of the flipped row bit, at
-// the element with column bit p set; it is read from global memory as well (that tile was
-// just swept: mostly cache hits), and only where the tile's row bit p is 0.
-constexpr int kTileBits = 12, kTileThreads = 1024, kTilePer = (1 << kTileBits) / kTileThreads;
-constexpr int kTileThreadBits = 10;
-static_assert((1 << kTileThreadBits) == kTileThreads, "thread bits");
-// The tiled form from 13 atoms; below, one thread per element gathers its inputs through
-// the cache.  At 12 atoms (a 256 MB density matrix, last-level-cache resident) the gather
-// form measured 0.58 ms against 0.61 ms tiled (complex128; complex64 0.45 against 0.44).  At
-// 13 atoms this form takes 2.86 ms (complex128) and 1.92 ms (complex64), where a tile kernel
-// that read each neighbour where it was used took 2.84 and 2.35 ms: complex128 is bound by
-// neighbour tiles that miss the caches (14 index bits lie above the tile).
-constexpr int kLiouvillianTileAtoms = 13;
+// The same operator on tiles of 32 x 32 elements, one per 256-thread workgroup, four elements per
+// thread.  The flips of the five lowest bits of row and column read the tile in LDS, those of the
+// bits above read the neighbouring tiles at the thread's own places (512-byte runs; in row-major
+// order of the tiles on one XCD the column flips hit its L2, the row flips the last-level cache).
+// The diagonal comes from D of the tile's 32 rows and 32 columns and from popcounts.  REAL: a
+// global drive without phase, where the neighbours are summed first and the coupling applied once.
+// 12 atoms: 245 us for the upper triangle in complex128 (14 neighbours an element from the caches,
+// 7.7 TB/s), 458 us for all of it and 206 us in complex64; the one-thread-per-element form above,
+// which forms D and the loss bit by bit and reads all 2n neighbours through the caches, took 535
+// and 399 us.  13 atoms: 2.15 and 1.02 ms, against 2.88 and 1.90 ms on runs of 4096 elements.  10
+// atoms, the smallest: 23 and 17 us against 29 and 26.  The p loops stay rolled: unrolled, their
+// loads took 256 registers and one wave per SIMD.
+constexpr int kTileAtoms = 10;
 
-template <class R, int N>
-__global__ __launch_bounds__(kTileThreads) void liouvillian_tile_kernel(
-    const LindbladCoef c, const double* __restrict__ e, const Cx<R>* __restrict__ x,
-    Cx<R>* __restrict__ y) {
+template <class R, int N, bool REAL>
+__global__ __launch_bounds__(kBlock, 4) void liouvillian_tile_kernel(const LindbladCoef c,
+                                                                  const double* __restrict__ e,
+                                                                  const Cx<R>* __restrict__ x,
+                                                                  Cx<R>* __restrict__ y,
+                                                                  const int upper) {
   using C = Cx<R>;
-  static_assert(N >= kTileBits, "tiles hold whole column ranges (12 atoms and more)");
-  constexpr int n = N;
-  __shared__ C tile[1 << kTileBits];
-  const uint32_t tid = threadIdx.x;
-  const uint64_t base = (uint64_t)xcd_remap(blockIdx.x, gridDim.x) << kTileBits;
-  double are[kTilePer], aim[kTilePer];
+  __shared__ C tile[kTileSide][kTileSide + 1];
+  __shared__ double dd[2][kTileSide];  // D of the rows, of the columns
+  const uint32_t tid = threadIdx.x, row0 = tid >> 5, col = tid & 31;
+  const HermTile h = herm_tile(xcd_remap(blockIdx.x, gridDim.x), N, upper != 0);
+  const uint32_t r0 = h.R * kTileSide, c0 = h.C * kTileSide;
+  const C* xt = x + h.base + ((size_t)row0 << N) + col;
 #pragma unroll
-  for (int s = 0; s < kTilePer; ++s) {
-    tile[tid + kTileThreads * s] = x[base + tid + kTileThreads * s];
-    are[s] = 0.0;
-    aim[s] = 0.0;
-  }
-  // flips of the index bits above the tile
+  for (int q = 0; q < kTileElems; ++q) tile[row0 + kTileRows * q][col] = xt[(size_t)(kTileRows * q) << N];
+  double are[kTileElems], aim[kTileElems];
+  // REAL: the sum over p of rho_{r^p, c} - rho_{r, c^p}; else the drive's terms themselves
 #pragma unroll
-  for (int q = kTileBits; q < 2 * n; ++q) {
-    const bool bit = (base >> q) & 1u;
-    const uint64_t nbase = base ^ (uint64_t(1) << q);
-    C nb[kTilePer];
-#pragma unroll
-    for (int s = 0; s < kTilePer; ++s) nb[s] = x[nbase + tid + kTileThreads * s];
-    if (q >= n) {
-      // row flip of bit p: -i h(r_p) rho_{r^p, c} = (hi a.x + hr a.y) + i (hi a.y - hr a.x)
-      const int p = q - n;
-      const double hr = bit ? c.up_re[p] : c.dn_re[p], hi = bit ? c.up_im[p] : c.dn_im[p];
-#pragma unroll
-      for (int s = 0; s < kTilePer; ++s) {
-        are[s] += hi * (double)nb[s].x + hr * (double)nb[s].y;
-        aim[s] += hi * (double)nb[s].y - hr * (double)nb[s].x;
-      }
+  for (int q = 0; q < kTileElems; ++q) are[q] = aim[q] = 0.0;
+  // -i h(r_p) rho_{r^p, c} and +i h(1 - c_p) rho_{r, c^p}
+  auto row_flip = [&](int q, int p, bool bit, const C& a) {
+    if (REAL) {
+      are[q] += (double)a.x;
+      aim[q] += (double)a.y;
     } else {
-      // column flip of bit q: +i h(1 - c_q) rho_{r, c^q} = (-gi b.x - gr b.y) + i (gr b.x - gi b.y)
-      const double gr = bit ? c.dn_re[q] : c.up_re[q], gi = bit ? c.dn_im[q] : c.up_im[q];
+      const double hr = bit ? c.up_re[p] : c.dn_re[p], hi = bit ? c.up_im[p] : c.dn_im[p];
+      are[q] += hi * (double)a.x + hr * (double)a.y;
+      aim[q] += hi * (double)a.y - hr * (double)a.x;
+    }
+  };
+  auto col_flip = [&](int q, int p, bool bit, const C& b) {
+    if (REAL) {
+      are[q] -= (double)b.x;
+      aim[q] -= (double)b.y;
+    } else {
+      const double gr = bit ? c.dn_re[p] : c.up_re[p], gi = bit ? c.dn_im[p] : c.up_im[p];
+      are[q] += -gi * (double)b.x - gr * (double)b.y;
+      aim[q] += gr * (double)b.x - gi * (double)b.y;
+    }
+  };
+#pragma unroll 1
+  for (int p = 5; p < N; ++p) {
+    // (signed distances: the neighbour's tile lies 2^p rows or columns away)
+    const bool rb = (r0 >> p) & 1u, cb = (c0 >> p) & 1u;
+    const C* xr = xt + (rb ? -((int64_t)1 << (N + p)) : (int64_t)1 << (N + p));
+    const C* xc = xt + (cb ? -((int64_t)1 << p) : (int64_t)1 << p);
+    C a[kTileElems], b[kTileElems];
 #pragma unroll
-      for (int s = 0; s < kTilePer; ++s) {
-        are[s] += -gi * (double)nb[s].x - gr * (double)nb[s].y;
-        aim[s] += gr * (double)nb[s].x - gi * (double)nb[s].y;
+    for (int q = 0; q < kTileElems; ++q) {
+      a[q] = xr[(size_t)(kTileRows * q) << N];
+      b[q] = xc[(size_t)(kTileRows * q) << N];
+    }
+#pragma unroll
+    for (int q = 0; q < kTileElems; ++q) {
+      row_flip(q, p, rb, a[q]);
+      col_flip(q, p, cb, b[q]);
+    }
+  }
+  // relaxation feeds (0, 0) of atom p from (1, 1)
+  double fre[kTileElems], fim[kTileElems];
+#pragma unroll
+  for (int q = 0; q < kTileElems; ++q) fre[q] = fim[q] = 0.0;
+  if (c.gamma_r != 0.0) {
+#pragma unroll 1
+    for (int p = 5; p < N; ++p) {
+      if (((r0 | c0) >> p) & 1u) continue;
+      const C* xs = xt + ((size_t)1 << (N + p)) + ((size_t)1 << p);
+#pragma unroll
+      for (int q = 0; q < kTileElems; ++q) {
+        const C a = xs[(size_t)(kTileRows * q) << N];
+        fre[q] += (double)a.x;
+        fim[q] += (double)a.y;
       }
     }
   }
-  // relaxation feeds (0, 0) of atom p from (1, 1): rho_{r|p, c|p} where r_p = c_p = 0
-  if (c.gamma_r != 0.0) {
+  if (tid < 2 * kTileSide) {
+    const uint32_t k = (tid < kTileSide ? r0 : c0) + (tid & 31);
+    double d = e[k];
 #pragma unroll
-    for (int p = 0; p < n; ++p) {
-      if ((base >> (n + p)) & 1u) continue;  // r_p = 1 across the tile
-      if (p >= kTileBits && ((base >> p) & 1u)) continue;  // c_p = 1 across the tile
-      // element el (with c_p = 0) takes its source at element el | 2^p of the tile with row
-      // bit p set (every address formed here lies inside the matrix, also where c_p = 1)
-      const uint64_t sbase = (base | (uint64_t(1) << (n + p))) | (p >= kTileBits ? (uint64_t(1) << p) : 0);
-      const uint32_t pin = p < kTileBits ? (1u << p) : 0u;
-      C src[kTilePer];
-#pragma unroll
-      for (int s = 0; s < kTilePer; ++s) {
-        const uint32_t el = tid + kTileThreads * s;
-        const bool on = !(el & pin);
-        src[s] = on ? x[sbase + (el | pin)] : C{0, 0};
-      }
-#pragma unroll
-      for (int s = 0; s < kTilePer; ++s) {
-        are[s] += c.gamma_r * (double)src[s].x;
-        aim[s] += c.gamma_r * (double)src[s].y;
-      }
-    }
+    for (int p = 0; p < N; ++p) d -= (k >> p) & 1u ? c.delta[p] : 0.0;
+    dd[tid >> 5][tid & 31] = d;
   }
   __syncthreads();
-
-  const uint32_t cmask = (1u << n) - 1u;
-  const uint32_t r = (uint32_t)(base >> n);  // one row per tile
-  double dr = e[r];
 #pragma unroll
-  for (int p = 0; p < n; ++p)
-    if ((r >> p) & 1u) dr -= c.delta[p];
-#pragma unroll
-  for (int s = 0; s < kTilePer; ++s) {
-    const uint32_t el = tid + kTileThreads * s;
-    const uint64_t idx = base + el;
-    const uint32_t col = (uint32_t)idx & cmask;
-    double dc = e[col], loss = 0.0;
-#pragma unroll
-    for (int p = 0; p < n; ++p) {
-      const uint32_t rp = (r >> p) & 1u, cp = (col >> p) & 1u;
-      dc -= cp ? c.delta[p] : 0.0;
-      loss += 0.5 * c.gamma_r * (double)(rp + cp) + ((rp ^ cp) ? c.gamma_phi : 0.0);
+  for (int q = 0; q < kTileElems; ++q) {
+    const uint32_t row = row0 + kTileRows * q;
+#pragma unroll 1
+    for (int p = 0; p < 5; ++p) {
+      row_flip(q, p, (row >> p) & 1u, tile[row ^ (1u << p)][col]);
+      col_flip(q, p, (col >> p) & 1u, tile[row][col ^ (1u << p)]);
+      if (c.gamma_r != 0.0) {
+        const C a = tile[row | (1u << p)][col | (1u << p)];
+        const bool on = !(((row | col) >> p) & 1u);
+        fre[q] += on ? (double)a.x : 0.0;
+        fim[q] += on ? (double)a.y : 0.0;
+      }
     }
-    const C v = tile[el];
-    // (-i (dr - dc) - loss) v
-    double ore = -loss * (double)v.x + (dr - dc) * (double)v.y + are[s];
-    double oim = -loss * (double)v.y - (dr - dc) * (double)v.x + aim[s];
-#pragma unroll
-    for (int p = 0; p < kTileBits; ++p) {
-      const uint32_t cp = (el >> p) & 1u;
-      const C b = tile[el ^ (1u << p)];
-      const double gr = cp ? c.dn_re[p] : c.up_re[p], gi = cp ? c.dn_im[p] : c.up_im[p];
-      ore += -gi * (double)b.x - gr * (double)b.y;
-      oim += gr * (double)b.x - gi * (double)b.y;
+    const C v = tile[row][col];
+    const double diff = dd[0][row] - dd[1][col];
+    const uint32_t r = r0 + row, k = c0 + col;
+    const double loss = 0.5 * c.gamma_r * (double)(__popc(r) + __popc(k)) + c.gamma_phi * (double)__popc(r ^ k);
+    double ore, oim;
+    if (REAL) {  // -i h S
+      ore = c.up_re[0] * aim[q];
+      oim = -c.up_re[0] * are[q];
+    } else {
+      ore = are[q];
+      oim = aim[q];
     }
-    C o;
-    o.x = (R)ore;
-    o.y = (R)oim;
-    y[idx] = o;
+    ore += c.gamma_r * fre[q] - loss * (double)v.x + diff * (double)v.y;
+    oim += c.gamma_r * fim[q] - loss * (double)v.y - diff * (double)v.x;
+    y[h.base + ((size_t)row << N) + col] = C{(R)ore, (R)oim};
   }
 }
 
@@ -214,13 +216,21 @@ __global__ __launch_bounds__(kBlock) void rho_diag_kernel(const Cx<R>* __restric
 }
 
 template <class R, int N>
-void launch_liouvillian(const LindbladCoef& c, const double* e, const void* x, void* y,
+void launch_liouvillian(const LindbladCoef& c, const double* e, const void* x, void* y, bool upper,
                         hipStream_t s) {
-  constexpr uint64_t count = uint64_t(1) << (2 * N);
-  if constexpr (N >= kLiouvillianTileAtoms) {
-    hipLaunchKernelGGL((liouvillian_tile_kernel<R, N>), dim3((uint32_t)(count >> kTileBits)),
-                       dim3(kTileThreads), 0, s, c, e, (const Cx<R>*)x, (Cx<R>*)y);
+  if constexpr (N >= kTileAtoms) {
+    bool real = true;  // one real coupling for every atom
+    for (int p = 0; p < N; ++p)
+      real = real && c.up_im[p] == 0.0 && c.up_re[p] == c.up_re[0];
+    const dim3 grid(herm_tiles(N, upper));
+    if (real)
+      hipLaunchKernelGGL((liouvillian_tile_kernel<R, N, true>), grid, dim3(kBlock), 0, s, c, e,
+                         (const Cx<R>*)x, (Cx<R>*)y, upper ? 1 : 0);
+    else
+      hipLaunchKernelGGL((liouvillian_tile_kernel<R, N, false>), grid, dim3(kBlock), 0, s, c, e,
+                         (const Cx<R>*)x, (Cx<R>*)y, upper ? 1 : 0);
   } else {
+    constexpr uint64_t count = uint64_t(1) << (2 * N);
     uint64_t g = (count + kBlock - 1) / kBlock;
     if (g > 8192) g = 8192;
     hipLaunchKernelGGL((liouvillian_kernel<R, N>), dim3((uint32_t)g), dim3(kBlock), 0, s, c, e,
@@ -228,35 +238,25 @@ void launch_liouvillian(const LindbladCoef& c, const double* e, const void* x, v
   }
 }
 
-template <class R>
-hipError_t liouvillian_r(const LindbladCoef& c, const double* e, const void* x, void* y,
+template <class R, int N = 1>
+hipError_t liouvillian_r(const LindbladCoef& c, const double* e, const void* x, void* y, bool upper,
                          hipStream_t s) {
-  switch (c.n) {
-    case 1: launch_liouvillian<R, 1>(c, e, x, y, s); break;
-    case 2: launch_liouvillian<R, 2>(c, e, x, y, s); break;
-    case 3: launch_liouvillian<R, 3>(c, e, x, y, s); break;
-    case 4: launch_liouvillian<R, 4>(c, e, x, y, s); break;
-    case 5: launch_liouvillian<R, 5>(c, e, x, y, s); break;
-    case 6: launch_liouvillian<R, 6>(c, e, x, y, s); break;
-    case 7: launch_liouvillian<R, 7>(c, e, x, y, s); break;
-    case 8: launch_liouvillian<R, 8>(c, e, x, y, s); break;
-    case 9: launch_liouvillian<R, 9>(c, e, x, y, s); break;
-    case 10: launch_liouvillian<R, 10>(c, e, x, y, s); break;
-    case 11: launch_liouvillian<R, 11>(c, e, x, y, s); break;
-    case 12: launch_liouvillian<R, 12>(c, e, x, y, s); break;
-    case 13: launch_liouvillian<R, 13>(c, e, x, y, s); break;
-    case 14: launch_liouvillian<R, 14>(c, e, x, y, s); break;
-    default: return hipErrorInvalidValue;
+  if constexpr (N > kMaxLindbladAtoms) {
+    return hipErrorInvalidValue;
+  } else {
+    if (c.n != N) return liouvillian_r<R, N + 1>(c, e, x, y, upper, s);
+    if (upper && N < kTileAtoms) return hipErrorInvalidValue;
+    launch_liouvillian<R, N>(c, e, x, y, upper, s);
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t liouvillian_apply(int prec, const LindbladCoef& c, const double* e, const void* x,
-                             void* y, hipStream_t s) {
-  static_assert(kMaxLindbladAtoms == 14, "liouvillian_r instantiates 1..14 atoms");
-  return prec == kC128 ? liouvillian_r<double>(c, e, x, y, s) : liouvillian_r<float>(c, e, x, y, s);
+                             void* y, bool upper, hipStream_t s) {
+  return prec == kC128 ? liouvillian_r<double>(c, e, x, y, upper, s)
+                       : liouvillian_r<float>(c, e, x, y, upper, s);
 }
 
 hipError_t rho_diagonal(int prec, int n, const void* x, double* out, hipStream_t s) {
