@@ -24,7 +24,7 @@ int hess_expm_e1(int m, const std::complex<double>* a, int ld, double tau, std::
 constexpr int kArnoldiGroup = 8;  // vectors per pass over y in the inner products
 constexpr int kHermGroup = 16;    // the same of Hermitian matrices, whose inner products are real
 constexpr int kSmallBits = 18;    // vectors up to 2^18 elements: partial sums summed by their reader
-constexpr int kSmallParts = 128;  // at most
+constexpr int kSmallParts = 256;  // at most
 // One Gram-Schmidt pass of iteration j.  u_0 = v0, u_i = base + i stride (elements); w = Op u_j
 // (again: w = u_{j+1}, the second pass, which orthogonalises u_{j+1} once more in place).
 struct ArnoldiStep {

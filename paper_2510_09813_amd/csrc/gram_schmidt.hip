@@ -21,7 +21,7 @@
 // Measured, with the host part of arnoldi.cpp, against inner products and coefficients that went
 // through the host, a second pass by |y| and the whole exponential of H_m at every dimension: a
 // Lindblad step of 12 atoms (28 vectors of 256 MiB) 109 -> 72 ms (35 ms with the Hermitian forms
-// below), 20 steps of 6 atoms (12 vectors of 64 KiB each) 40 -> 7.2 ms.
+// below), 20 steps of 6 atoms (12 vectors of 64 KiB each) 26 -> 5.5 ms.
 #include <type_traits>
 
 #include "arnoldi.h"
@@ -40,7 +40,8 @@ __device__ __forceinline__ const Cx<R>* basis_vec(const ArnoldiStep& a, int i) {
 __device__ __forceinline__ double wave_parts(const double* p, int n) {
   const int lane = threadIdx.x & 63;
   double v = lane < n ? p[lane] : 0.0;
-  if (lane + 64 < n) v += p[lane + 64];
+#pragma unroll
+  for (int k = 64; k < kSmallParts; k += 64) v += lane + k < n ? p[lane + k] : 0.0;
   return wave_total(v);
 }
 
@@ -149,15 +150,18 @@ __global__ __launch_bounds__(kBlock) void arnoldi_update_kernel(const ArnoldiSte
   if (a.dparts > 0) {
     // sum the partial inner products: eight lanes per value, every load of a lane in flight (one
     // wave per value took a memory latency for each of its turns)
-    static_assert(kSmallParts == 128, "16 partials per lane");
+    static_assert(kSmallParts % 128 == 0, "turns of 16 partials per lane");
     for (int r0 = 0; r0 < rows; r0 += kBlock / 8) {
       const int r = r0 + (tid >> 3), l = tid & 7;
       const double* q = a.part + (size_t)(r < rows ? r : 0) * a.dparts;
-      double v[16], t = 0.0;
+      double t = 0.0;
+      for (int p0 = l; p0 < a.dparts; p0 += 128) {
+        double v[16];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = l + 8 * k < a.dparts ? q[l + 8 * k] : 0.0;
+        for (int k = 0; k < 16; ++k) v[k] = p0 + 8 * k < a.dparts ? q[p0 + 8 * k] : 0.0;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) t += v[k];
+        for (int k = 0; k < 16; ++k) t += v[k];
+      }
       t += dpp<kDppXor1>(t);
       t += dpp<kDppXor2>(t);
       t += dpp<kDppHalfMirror>(t);
@@ -435,8 +439,10 @@ __global__ __launch_bounds__(kBlock) void hermitise_kernel(Cx<R>* __restrict__ x
 
 int arnoldi_parts(size_t count) {
   if (count <= (size_t(1) << kSmallBits)) {
-    // 512 elements per workgroup, 4 to kSmallParts of them
-    size_t g = count / 512;
+    // 256 elements per workgroup and more, 4 to kSmallParts of them: the gradients' 2^17 elements
+    // take 10.1 + 9.5 us (update, inner products) on 256 workgroups, 13.0 + 11.9 on 128 and 12.4 +
+    // 11.0 on 512, whose partial sums every workgroup of the update reads
+    size_t g = count / 256;
     return (int)(g < 4 ? 4 : g > kSmallParts ? kSmallParts : g);
   }
   return (int)stream_grid(count, 8);
