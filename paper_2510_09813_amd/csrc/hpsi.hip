@@ -200,30 +200,6 @@ __device__ __forceinline__ Cx<R> form(const PassArgs<R>& p, const Coefs& co, siz
   return r;
 }
 
-// Detuning lookup: lut[256 q + v] = -sum_j delta[8q + j] over the set bits j of byte v.
-template <class R>
-__device__ __forceinline__ void build_delta_lut(const StepCoef& c, R* lut) {
-  for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
-    const int q = i >> 8, v = i & 255;
-    double s = 0.0;
-    for (int j = 0; j < 8; ++j) {
-      const int p = 8 * q + j;
-      if (p < c.n && ((v >> j) & 1)) s -= c.delta[p];
-    }
-    lut[i] = (R)s;
-  }
-}
-
-template <class R, int CM>
-__device__ __forceinline__ R detuning(const StepCoef& c, const R* lut, uint32_t b) {
-  if (CM == kCoefSite) {
-    return (lut[b & 255u] + lut[256 + ((b >> 8) & 255u)]) +
-           (lut[512 + ((b >> 16) & 255u)] + lut[768 + ((b >> 24) & 255u)]);
-  } else {
-    return (R)(-c.delta[0] * (double)__popc(b));
-  }
-}
-
 // acc += coef(bit) * v with the coefficients of bit position p.
 template <class R>
 __device__ __forceinline__ void cmad(Cx<R>& acc, const StepCoef& c, int p, bool bit, Cx<R> v) {
@@ -272,7 +248,7 @@ template <class R, int LB, int NT, int CM, int E>
 constexpr int lo_min_waves() {
   // two complex128 workgroups per CU (4 waves per SIMD) where the registers allow it without
   // spilling: the extension's loads would otherwise push the global-drive forms past 128
-  return sizeof(R) == 8 && LB == 12 && NT == 512 && CM != kCoefSite ? 4 : 1;
+  return sizeof(R) == 8 && LB == 12 && NT == 512 ? 4 : 1;
 }
 
 // Which tile positions a thread holds.  The extended low pass issues about ten vector
@@ -363,7 +339,6 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
   constexpr int VB = lo_vec_bits<R, A, E>();
   constexpr int V = 1 << VB;         // adjacent amplitudes per access
   __shared__ __align__(16) C tile[1 << LB];
-  __shared__ R lut[CM == kCoefSite ? 1024 : 1];
   __shared__ double red[NT / 64];
 
   const uint32_t tid = threadIdx.x;
@@ -374,7 +349,6 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
     blk = (rest & ((1u << g0) - 1u)) | (h << g0) | ((rest >> g0) << (g0 + E));
   }
   const uint32_t base = blk << LB;
-  if (CM == kCoefSite) build_delta_lut<R>(c, lut);
 
   const Coefs co = input_coefs<NT, false>(p, red);
   C v[A], tv[A];
@@ -387,6 +361,16 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
 #pragma unroll
   for (int q = 0; q < TB; ++q)
     if ((tid >> q) & 1u) eth += et[1 + VB + q];
+  if constexpr (CM == kCoefSite) {
+    // Per-site detunings join the energy the same way.  A table by bytes of the pattern in LDS,
+    // which every workgroup built first and read four times per amplitude, cost 1.2 us of a pass
+    // at 17 atoms (6.9 -> 5.7 us), and its registers kept complex128 from two workgroups per CU:
+    // a per-site sweep of 27 atoms took 3.24 ms, now 2.96.
+#pragma unroll
+    for (int q = LB; q < kMaxAtoms; ++q) eth -= (blk >> (q - LB)) & 1u ? c.delta[q] : 0.0;
+#pragma unroll
+    for (int q = 0; q < TB; ++q) eth -= (tid >> q) & 1u ? c.delta[VB + q] : 0.0;
+  }
   // (the input test sits outside the loops, so that the loads of a stored input are issued
   // back to back rather than one branch at a time)
   if (!p.x1 && !p.x2 && co.a0 == 1.0) {
@@ -410,7 +394,8 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
     double es = eth;
 #pragma unroll
     for (int q = 0; q < RB; ++q)
-      if ((s >> q) & 1) es += et[1 + lo_reg_bit<TB, VB>(q)];
+      if ((s >> q) & 1)
+        es += et[1 + lo_reg_bit<TB, VB>(q)] - (CM == kCoefSite ? c.delta[lo_reg_bit<TB, VB>(q)] : 0.0);
     dg[s] = (R)(p.elo[lo_pos<TB, VB>(tid, s)] + es);
   }
 #pragma unroll
@@ -461,8 +446,7 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
     C acc[A];
 #pragma unroll
     for (int s = 0; s < A; ++s) {
-      const R d = dg[s] + detuning<R, CM>(c, lut, base + lo_pos<TB, VB>(tid, s));
-      acc[s] = C{d * v[s].x, d * v[s].y};
+      acc[s] = C{dg[s] * v[s].x, dg[s] * v[s].y};
     }
 #pragma unroll
     for (int q = 0; q < TB; ++q) {
@@ -494,7 +478,7 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
       for (int k = 0; k < V; ++k) {
         const int s = s0 + k;
         const uint32_t e = lo_pos<TB, VB>(tid, s);
-        const R d = dg[s] + detuning<R, CM>(c, lut, base + e);
+        const R d = dg[s] + (R)(-c.delta[0] * (double)__popc(base + e));
         acc[k] = C{d * v[s].x, d * v[s].y};
         DriveSum<R, CM> ds;
 #pragma unroll
@@ -525,11 +509,9 @@ template <class R, int CM>
 __global__ __launch_bounds__(kBlock) void hpsi_small_kernel(const StepCoef c, const PassArgs<R> p) {
   using C = Cx<R>;
   __shared__ C tile[128];
-  __shared__ R lut[CM == kCoefSite ? 1024 : 1];
   __shared__ double red[4];
   const uint32_t tid = threadIdx.x;
   const uint32_t dim = 1u << c.n;
-  if (CM == kCoefSite) build_delta_lut<R>(c, lut);
   C v = {0, 0};
   double nrm = 0.0, dot = 0.0;
   const Coefs co = input_coefs<kBlock, false>(p, red);
@@ -541,7 +523,12 @@ __global__ __launch_bounds__(kBlock) void hpsi_small_kernel(const StepCoef c, co
   }
   __syncthreads();
   if (tid < dim) {
-    const R d = (R)(p.elo[tid] + p.etile[0]) + detuning<R, CM>(c, lut, tid);
+    double es = p.elo[tid] + p.etile[0];
+    if (CM == kCoefSite)
+      for (int q = 0; q < c.n; ++q) es -= (tid >> q) & 1u ? c.delta[q] : 0.0;
+    else
+      es -= c.delta[0] * (double)__popc(tid);
+    const R d = (R)es;
     C acc = {d * v.x, d * v.y};
     DriveSum<R, CM> ds;
     for (int q = 0; q < c.n; ++q) ds.add(c, q, (tid >> q) & 1, tile[tid ^ (1u << q)]);
