@@ -414,6 +414,10 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
   // are issued together into their own registers before any is used: written as one
   // load-and-add per amplitude, the compiler issues them one at a time at this register
   // budget, which made the pass about 30 % slower.
+  // (one or two amplitudes per thread: there is room to sum them with the tile's own flips, as one
+  // pass over a whole small register would, so complex64 rounds no more often than there)
+  constexpr bool kOwnSum = E > 0 && A <= 2 && CM != kCoefSite;
+  DriveSum<R, CM> ext[kOwnSum ? A : 1];
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     const int tb = p.ext_bit + j;  // tile-index bit
@@ -427,8 +431,12 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
     for (int s = 0; s < A; s += V) ld_run<R, VB>(&p.x0[nbase + lo_pos<TB, VB>(tid, s)], &nb[s]);
 #pragma unroll
     for (int s = 0; s < A; ++s) {
-      tv[s].x += cr * nb[s].x - ci * nb[s].y;
-      tv[s].y += cr * nb[s].y + ci * nb[s].x;
+      if constexpr (kOwnSum) {
+        ext[s].add(c, LB + tb, bit, nb[s]);
+      } else {
+        tv[s].x += cr * nb[s].x - ci * nb[s].y;
+        tv[s].y += cr * nb[s].y + ci * nb[s].x;
+      }
     }
   }
   __syncthreads();
@@ -481,6 +489,7 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
         const R d = dg[s] + (R)(-c.delta[0] * (double)__popc(base + e));
         acc[k] = C{d * v[s].x, d * v[s].y};
         DriveSum<R, CM> ds;
+        if constexpr (kOwnSum) ds = ext[s];
 #pragma unroll
         for (int q = 0; q < TB; ++q) ds.add(c, VB + q, (tid >> q) & 1, tile[e ^ (1u << (VB + q))]);
 #pragma unroll
