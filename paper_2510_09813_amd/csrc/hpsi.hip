@@ -577,6 +577,21 @@ __global__ __launch_bounds__(NT, (hi_min_waves<R, HB, NT>())) void hpsi_hi_kerne
   const int gap = p.a - RL;  // outside bits between the contiguous run and the tile's high bits
   const uint32_t obase = ((blk & ((1u << gap) - 1u)) << RL) | ((blk >> gap) << (p.a + G));
 
+  // Per-site couplings of the thread bits, chosen once and requested with everything else: inside
+  // the flips' conditions each one waited for its own scalar loads (a forming pass of 17 atoms 9.3
+  // us, now 8.5).  Larger tiles have no registers for them.
+  constexpr bool kEarly = CM == kCoefSite && HB <= (sizeof(R) == 8 ? 10 : 11);
+  constexpr int TF = TB < HB ? TB : HB;
+  R cr[kEarly ? TF - RL : 1], ci[kEarly ? TF - RL : 1];
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int eb = RL; eb < TF; ++eb) {
+      const int q = p.a + eb - RL;
+      const bool bit = (tid >> eb) & 1u;
+      cr[eb - RL] = (R)(bit ? c.up_re[q] : c.dn_re[q]);
+      ci[eb - RL] = (R)(bit ? c.up_im[q] : c.dn_im[q]);
+    }
+  }
   const Coefs co = input_coefs<NT, SUM>(p, red);
   C v[A], tv[A];
   uint32_t gi[A];
@@ -613,7 +628,12 @@ __global__ __launch_bounds__(NT, (hi_min_waves<R, HB, NT>())) void hpsi_hi_kerne
       const int q = p.a + eb - RL;
       if (q < p.f0 || q >= p.f1) continue;
       const C nb = eb < TB ? tile[e ^ (1u << eb)] : v[s ^ (1 << (eb - TB))];
-      ds.add(c, q, (e >> eb) & 1u, nb);
+      if (kEarly && eb < TB) {
+        ds.acc.x += cr[eb - RL] * nb.x - ci[eb - RL] * nb.y;
+        ds.acc.y += cr[eb - RL] * nb.y + ci[eb - RL] * nb.x;
+      } else {
+        ds.add(c, q, (e >> eb) & 1u, nb);
+      }
     }
     ds.finish(c, acc);
     if (p.accumulate) cadd<R>(acc, tv[s]);
