@@ -224,7 +224,7 @@ int rsv_lindblad_apply(rsv_register* reg, const rsv_pulses* pulses, int64_t step
  * FP64 exponential of the Hessenberg matrix) to the
  * estimate |rho| h_{m+1,m} |[exp(dt H_m) e_1]_m| <= tol; without convergence the longest
  * part of the step that the kmax vectors resolve is taken first.  From 10 atoms on a matrix that is
- * Hermitian to rounding (|rho - rho^+| <= 8 eps |rho|) is made exactly so and stays so.  stats->norm_final is the Frobenius norm of the final rho. */
+ * Hermitian to rounding (|rho - rho^+| <= 8 eps |rho|, 2 eps for RSV_C64) is made so and stays so.  stats->norm_final is the Frobenius norm of the final rho. */
 int rsv_lindblad_evolve_device(rsv_register* reg, const rsv_pulses* pulses,
                                const rsv_evolve_opts* opts, const rsv_lindblad* rates,
                                void* d_rho_inout, void* hip_stream, rsv_stats* stats_out);

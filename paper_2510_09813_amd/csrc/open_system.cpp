@@ -117,7 +117,7 @@ int rsv_lindblad_evolve_device(rsv_register* reg, const rsv_pulses* pl, const rs
   ArnoldiSpace sp;
   arnoldi_carve(blk.p, h_scal, prec, 2 * n, o->kmax, &sp);
   // A Hermitian density matrix (up to the rounding of whatever formed it: |rho - rho^+| within 8
-  // eps |rho|) stays Hermitian, and from 10 atoms on, where the Krylov basis is streamed from
+  // eps |rho|, 2 eps in complex64) stays Hermitian, and from 10 atoms on, where the Krylov basis is streamed from
   // memory, its Arnoldi process reads one triangle of it.
   if (n >= kHermAtoms && count > 0) {
     const int64_t parts = arnoldi_parts(size_t(1) << (2 * n));
@@ -125,8 +125,8 @@ int rsv_lindblad_evolve_device(rsv_register* reg, const rsv_pulses* pl, const rs
     HIP_TRY(finalize_rows(sp.part, parts, 2, sp.dscal, s));
     HIP_TRY(hipMemcpyAsync(sp.h_scal, sp.dscal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const double eps = prec == kC128 ? 2.3e-16 : 1.2e-7;
-    if (sp.h_scal[0] <= 64.0 * eps * eps * sp.h_scal[1]) {
+    const double tol = prec == kC128 ? 8 * 2.3e-16 : 2 * 1.2e-7;
+    if (sp.h_scal[0] <= tol * tol * sp.h_scal[1]) {
       if (sp.h_scal[0] > 0.0) HIP_TRY(hermitise(prec, n, d_rho, true, sp.part, s));
       sp.herm = n;
     }
