@@ -97,8 +97,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
   const double log2_tol = std::log2(tol);
   KrylovCourse course;
   double nx = 0.0;
-  // an iteration too many costs a long vector more than a round trip
-  int next = sp.hint > 0 ? (run.small ? sp.hint : sp.hint - 1) : 6;
+  int next = KrylovCourse::first(sp.hint, !run.small);
   int m = 0;            // columns gone through
   bool careful = false;  // a second pass was needed: go on one iteration at a time
   auto finish = [&](int dim, double part) -> int {
@@ -126,7 +125,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
       if (!std::isfinite(nx)) return fail(RSV_ENUMERIC, "state norm is not finite");
       if (nx == 0.0) return RSV_OK;
       scale[0] = 1.0 / nx;
-      course.start(tau, nx);
+      course.start(tau, nx, !run.small);
     }
     for (int j = m; j < upto; ++j) {
       // inner product i as fetched at d (real ones for Hermitian matrices)
@@ -178,7 +177,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
         double est = 0.0;
         RSV_TRY(estimate(tau, &est));
         if (!(est > tol) || beta == 0.0) return finish(m, tau);
-        course.found(est);
+        course.found(est, log2_tol);
         if (m == kmax) {
           // the longest part of the step this basis resolves (same operator, so the split is
           // exact): the estimate grows like the m-th power of the time
@@ -198,7 +197,6 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
       if (again) break;  // what was queued after this vector used its first form
     }
     next = course.ahead(log2_tol, kmax - m);
-    if (!course.tested && !run.small) next = std::max(1, next - 2);
   }
 }
 

@@ -598,7 +598,7 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
     int m = 0;  // dimensions gone through
     double nrm = 0.0, sub = remaining;
     bool done = false;
-    int next = reorth ? 1 : hint <= 0 ? 6 : large ? hint - 1 : hint;
+    int next = reorth ? 1 : KrylovCourse::first(hint, large);
     KrylovCourse course;
     double bks[kMaxKrylov + 1];  // |u_k|
     while (!done) {
@@ -615,7 +615,7 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
         nrm = std::sqrt(L.norm2);
         if (!(nrm > 0.0) || !std::isfinite(nrm)) return fail(RSV_ENUMERIC, "state norm is %g", nrm);
         L.scale[0] = 1.0 / nrm;
-        course.start(remaining, nrm);
+        course.start(remaining, nrm, large);
       }
       for (int k = m + 1; k <= upto && !done; ++k) {
         double ab[2] = {scal[2 * k - 1], scal[2 * k]};  // <u_{k-1}, z_{k-1}>, |u_k|^2
@@ -647,7 +647,7 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
           done = true;
           break;
         }
-        course.found(bk * ylast * nrm);
+        course.found(bk * ylast * nrm, log2_tol);
         if (k == kmax) {
           // Not converged: advance by the longest part of the step that this basis already
           // resolves (same H_k, so the split is exact), then restart from the new state.
@@ -671,10 +671,7 @@ int propagate(Lanczos& L, const StepCoef& c, double tau, double tol, int kmax, i
           done = true;
         }
       }
-      if (!done) {
-        next = reorth ? 1 : course.ahead(log2_tol, kmax - m);
-        if (large && !course.tested) next = std::max(1, next - 2);
-      }
+      if (!done) next = reorth ? 1 : course.ahead(log2_tol, kmax - m);
     }
     hint = m;
     L.st->krylov_max = std::max<int64_t>(L.st->krylov_max, m);
