@@ -116,8 +116,16 @@ const char* rsv_last_error(void);
 /* hbm_budget_bytes = 0: no budget beyond the device's free memory. */
 int rsv_ctx_create(int hip_device, size_t hbm_budget_bytes, rsv_ctx** out);
 void rsv_ctx_destroy(rsv_ctx* ctx);
-/* Bytes of device memory currently held by the context's registers and results. */
+/* Bytes of device memory currently held by the context's registers and results, without the scratch
+ * that finished calls left behind (below). */
 size_t rsv_ctx_bytes_in_use(const rsv_ctx* ctx);
+/* A context keeps the device scratch of finished calls for the next ones: at most 32 blocks and a
+ * thirty-second of the device's memory, blocks of 1 GiB and more only while half of the
+ * device is free.  It gives all of it back before it refuses a request for lack of memory or budget,
+ * when any context of the process finds the device full, and when it is destroyed.  This call gives it
+ * back at once (for other users of the device, such as another library's allocator) and returns its
+ * bytes. */
+size_t rsv_ctx_trim(rsv_ctx* ctx);
 
 /* ------------------------------------------------------------------ register
  * Builds U_ij = C/|r_i - r_j|^6 on the host (eq. 3) and, on the device, the tables from

@@ -32,7 +32,7 @@ struct Scratch {
   Scratch(rsv_ctx* c, hipStream_t st) : ctx(c), s(st) {}
   int get(size_t b) {
     bytes = b;
-    RSV_TRY(ctx->dev->alloc(b, &p));
+    RSV_TRY(ctx->dev->borrow(b, &p));
     h = ctx->dev->pinned_take();
     if (!h) return fail(RSV_EDEVICE, "hipHostMalloc failed");
     return RSV_OK;
@@ -40,7 +40,7 @@ struct Scratch {
   ~Scratch() {
     if (!p) return;
     const bool idle = hipStreamSynchronize(s) == hipSuccess;
-    ctx->dev->release(p, bytes, idle);
+    ctx->dev->give_back(p, bytes, idle);
     ctx->dev->pinned_give(h);
   }
 };
@@ -88,7 +88,7 @@ int rsv_ctx_create(int hip_device, size_t budget, rsv_ctx** out) {
   c->device = hip_device;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) total_b = 0;
-  c->dev = new (std::nothrow) DeviceAllocator(budget, total_b);
+  c->dev = new (std::nothrow) DeviceAllocator(hip_device, budget, total_b);
   if (!c->dev) {
     delete c;
     return fail(RSV_ENOMEM, "host allocation failed");
@@ -109,6 +109,8 @@ void rsv_ctx_destroy(rsv_ctx* ctx) {
 }
 
 size_t rsv_ctx_bytes_in_use(const rsv_ctx* ctx) { return ctx ? ctx->dev->in_use() : 0; }
+
+size_t rsv_ctx_trim(rsv_ctx* ctx) { return ctx ? ctx->dev->trim() : 0; }
 
 size_t rsv_workspace_bytes(int n, int kmax, rsv_precision prec) {
   if (n < 1 || n > kMaxAtoms || kmax < 2 || kmax > kMaxKrylov) return 0;
@@ -195,7 +197,7 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
   const int64_t np_dot = sweep_dot_partials(prec, n), np_norm = sweep_norm_partials(prec, n);
   const size_t bytes = vb + (size_t)(np_dot + np_norm + 2) * sizeof(double);
   void* blk = nullptr;
-  RSV_TRY(reg->alloc->alloc(bytes, &blk));
+  RSV_TRY(reg->alloc->borrow(bytes, &blk));
   hipStream_t s = as_stream(stream);
   double* pdot = (double*)((char*)blk + vb);
   double* pnorm = pdot + np_dot;
@@ -210,7 +212,7 @@ int rsv_energy_device(rsv_register* reg, const rsv_pulses* pl, int64_t step, int
   if (e == hipSuccess) e = hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   const bool idle = hipStreamSynchronize(s) == hipSuccess;
-  reg->alloc->release(blk, bytes, idle);
+  reg->alloc->give_back(blk, bytes, idle);
   if (e != hipSuccess) return fail(RSV_EDEVICE, "energy: %s", hipGetErrorString(e));
   if (!(h[1] > 0.0)) return fail(RSV_ENUMERIC, "state has zero norm");
   *energy = h[0] / h[1];
@@ -264,12 +266,12 @@ int rsv_evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o
       e = hipMemcpy(r->d_psi, psi0_host, b128, hipMemcpyHostToDevice);
     } else {
       void* tmp = nullptr;
-      rc = reg->ctx->dev->alloc(b128, &tmp);
+      rc = reg->ctx->dev->borrow(b128, &tmp);
       if (rc == RSV_OK) {
         e = hipMemcpy(tmp, psi0_host, b128, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = convert_from_c128(prec, n, tmp, r->d_psi, nullptr);
         if (e == hipSuccess) e = hipDeviceSynchronize();
-        reg->ctx->dev->release(tmp, b128, e == hipSuccess);
+        reg->ctx->dev->give_back(tmp, b128, e == hipSuccess);
       }
     }
   } else {
@@ -304,10 +306,10 @@ int rsv_result_state(const rsv_result* r, void* host) {
     return RSV_OK;
   }
   void* tmp = nullptr;
-  RSV_TRY(r->ctx->dev->alloc(b128, &tmp));
+  RSV_TRY(r->ctx->dev->borrow(b128, &tmp));
   hipError_t e = convert_to_c128(r->prec, r->n, r->d_psi, tmp, nullptr);
   if (e == hipSuccess) e = hipMemcpy(host, tmp, b128, hipMemcpyDeviceToHost);
-  r->ctx->dev->release(tmp, b128, e == hipSuccess);  // hipMemcpy waited
+  r->ctx->dev->give_back(tmp, b128, e == hipSuccess);  // hipMemcpy waited
   if (e != hipSuccess) return fail(RSV_EDEVICE, "state download: %s", hipGetErrorString(e));
   return RSV_OK;
 }
@@ -331,8 +333,7 @@ int rsv_result_stats(const rsv_result* r, rsv_stats* out) {
 void rsv_result_destroy(rsv_result* r) {
   if (!r) return;
   (void)hipSetDevice(r->ctx->device);
-  const bool idle = hipStreamSynchronize(nullptr) == hipSuccess;  // results use the null stream
-  r->ctx->dev->release(r->d_psi, r->bytes, idle);
+  r->ctx->dev->release(r->d_psi, r->bytes);
   delete r;
 }
 

@@ -56,96 +56,60 @@ int fail(int code, const char* fmt, ...) {
 const char* last_error() { return g_err.c_str(); }
 
 // ------------------------------------------------------------------------------ memory
+bool DeviceMem::get(size_t bytes, void** p) const {
+  if (hipMalloc(p, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+void DeviceMem::put(void* p) const { (void)hipFree(p); }
+void DeviceMem::wait() const { (void)hipDeviceSynchronize(); }
+bool DeviceMem::half_free() const {
+  size_t free_b = 0, total_b = 0;
+  return hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= total_b / 2;
+}
+void DeviceMem::reclaim() const { DeviceAllocator::trim_device(owner->device(), owner); }
+
 namespace {
-constexpr size_t kKeepBlocks = 32, kKeepPinned = 16;
-// Blocks are kept and matched by this size.
-inline size_t block_size(size_t bytes) { return (bytes + 4095) / 4096 * 4096; }
+std::mutex g_allocators_mu;
+DeviceAllocator* g_allocators = nullptr;
 }  // namespace
 
+DeviceAllocator::DeviceAllocator(int device, size_t budget, size_t device_bytes)
+    : device_(device), budget_(budget), pool_(budget, device_bytes / 32, DeviceMem{this}) {
+  std::lock_guard<std::mutex> lk(g_allocators_mu);
+  next_ = g_allocators;
+  if (next_) next_->prev_ = this;
+  g_allocators = this;
+}
+
 DeviceAllocator::~DeviceAllocator() {
-  trim();
-  for (double* h : pinned_) (void)hipHostFree(h);
+  {
+    std::lock_guard<std::mutex> lk(g_allocators_mu);
+    if (next_) next_->prev_ = prev_;
+    (prev_ ? prev_->next_ : g_allocators) = next_;
+  }
+  while (n_pinned_ > 0) (void)hipHostFree(pinned_[--n_pinned_]);
 }
 
-int DeviceAllocator::alloc(size_t bytes, void** p) {
-  *p = nullptr;
-  const size_t size = block_size(bytes);
-  bool squeeze = false;
-  {
-    std::lock_guard<std::mutex> lk(mu_);
-    if (budget_ && in_use_ + bytes > budget_)
-      return fail(RSV_ENOMEM, "HBM budget exceeded: %zu in use + %zu requested > %zu budget",
-                  in_use_, bytes, budget_);
-    in_use_ += bytes;
-    for (size_t i = kept_.size(); i-- > 0;) {
-      if (kept_[i].size != size) continue;
-      *p = kept_[i].p;
-      kept_bytes_ -= size;
-      kept_.erase(kept_.begin() + i);
-      return RSV_OK;
-    }
-    squeeze = budget_ && in_use_ + kept_bytes_ > budget_;
-  }
-  if (squeeze) trim();  // a budget bounds what the context holds, kept blocks included
-  hipError_t e = hipMalloc(p, size);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    trim();
-    e = hipMalloc(p, size);
-  }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    *p = nullptr;
-    std::lock_guard<std::mutex> lk(mu_);
-    in_use_ -= bytes;
-    return fail(RSV_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
-  }
+void DeviceAllocator::trim_device(int device, const DeviceAllocator* except) {
+  std::lock_guard<std::mutex> lk(g_allocators_mu);
+  for (DeviceAllocator* a = g_allocators; a; a = a->next_)
+    if (a != except && a->device_ == device) (void)a->trim();
+}
+
+int DeviceAllocator::status(ScratchPool<DeviceMem>::Status st, size_t bytes) const {
+  if (st == ScratchPool<DeviceMem>::kOverBudget)
+    return fail(RSV_ENOMEM, "HBM budget exceeded: %zu in use + %zu requested > %zu budget", in_use(),
+                bytes, budget_);
+  if (st == ScratchPool<DeviceMem>::kNoMemory)
+    return fail(RSV_ENOMEM, "hipMalloc(%zu) failed: out of memory", bytes);
   return RSV_OK;
-}
-
-void DeviceAllocator::release(void* p, size_t bytes, bool idle) {
-  if (!p) return;
-  // a kept block may next be used on another stream, so nothing may still run on it (hipFree
-  // waits for the device too)
-  if (!idle) (void)hipDeviceSynchronize();
-  const size_t size = block_size(bytes);
-  std::vector<void*> out;
-  {
-    std::lock_guard<std::mutex> lk(mu_);
-    in_use_ -= bytes;
-    if (size > keep_max_) {
-      out.push_back(p);
-    } else {
-      kept_.push_back(Kept{p, size});
-      kept_bytes_ += size;
-      while (kept_bytes_ > keep_max_ || kept_.size() > kKeepBlocks) {
-        out.push_back(kept_.front().p);
-        kept_bytes_ -= kept_.front().size;
-        kept_.erase(kept_.begin());
-      }
-    }
-  }
-  for (void* q : out) (void)hipFree(q);
-}
-
-void DeviceAllocator::trim() {
-  std::vector<Kept> out;
-  {
-    std::lock_guard<std::mutex> lk(mu_);
-    out.swap(kept_);
-    kept_bytes_ = 0;
-  }
-  for (const Kept& k : out) (void)hipFree(k.p);
 }
 
 double* DeviceAllocator::pinned_take() {
   {
     std::lock_guard<std::mutex> lk(mu_);
-    if (!pinned_.empty()) {
-      double* h = pinned_.back();
-      pinned_.pop_back();
-      return h;
-    }
+    if (n_pinned_ > 0) return pinned_[--n_pinned_];
   }
   double* h = nullptr;
   if (hipHostMalloc((void**)&h, kPinnedDoubles * sizeof(double), hipHostMallocDefault) != hipSuccess) {
@@ -159,17 +123,12 @@ void DeviceAllocator::pinned_give(double* h) {
   if (!h) return;
   {
     std::lock_guard<std::mutex> lk(mu_);
-    if (pinned_.size() < kKeepPinned) {
-      pinned_.push_back(h);
+    if (n_pinned_ < kKeepPinned) {
+      pinned_[n_pinned_++] = h;
       return;
     }
   }
   (void)hipHostFree(h);
-}
-
-size_t DeviceAllocator::in_use() const {
-  std::lock_guard<std::mutex> lk(mu_);
-  return in_use_;
 }
 
 ArenaAllocator::~ArenaAllocator() {
@@ -201,7 +160,7 @@ int ArenaAllocator::alloc(size_t bytes, void** p) {
   return RSV_OK;
 }
 
-void ArenaAllocator::release(void* p, size_t bytes, bool) {
+void ArenaAllocator::release(void* p, size_t bytes) {
   if (!p) return;
   bytes = round_up(bytes ? bytes : 1);
   std::lock_guard<std::mutex> lk(mu_);
@@ -709,7 +668,7 @@ struct Borrowed {
   ~Borrowed() {
     if (p) {
       const bool idle = hipStreamSynchronize(s) == hipSuccess;
-      a->release(p, bytes, idle);
+      a->give_back(p, bytes, idle);
     }
   }
 };
@@ -858,7 +817,7 @@ int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, vo
     ob.a = reg->alloc;
     ob.s = s;
     ob.bytes = (part + (size_t)n_obs * (n + 1)) * sizeof(double);
-    RSV_TRY(reg->alloc->alloc(ob.bytes, &ob.p));
+    RSV_TRY(reg->alloc->borrow(ob.bytes, &ob.p));
     obs_dev = (double*)ob.p + part;
   }
   double norm2 = 0.0;

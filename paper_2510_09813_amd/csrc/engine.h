@@ -13,6 +13,7 @@
 #include "first_fit.h"
 #include "rsv.h"
 #include "rsv_internal.h"
+#include "scratch_pool.h"
 
 namespace rsv {
 
@@ -39,39 +40,55 @@ class Allocator {
  public:
   virtual ~Allocator() = default;
   virtual int alloc(size_t bytes, void** p) = 0;
-  // idle: the caller has waited for every kernel and copy that used the block
-  virtual void release(void* p, size_t bytes, bool idle = false) = 0;
+  virtual void release(void* p, size_t bytes) = 0;
   virtual size_t in_use() const = 0;
+  // Memory for one call.  idle: the caller has waited for every kernel and copy that used it.
+  virtual int borrow(size_t bytes, void** p) { return alloc(bytes, p); }
+  virtual void give_back(void* p, size_t bytes, bool /* idle */) { release(p, bytes); }
 };
 
-// hipMalloc / hipFree under an optional byte budget, keeping released blocks for the next
-// request of the same size: a call's scratch would otherwise cost more than its kernels
-// (measured on one MI355X: the outputs of a 25-atom state 16.8 ms of which 2.0 ms kernels, a
-// 12-atom Lindblad step with its 9 GB Arnoldi space 260 ms of which 92 ms).  Kept blocks total
-// at most an eighth of the device's memory and 32 blocks, oldest freed first; they count
-// neither as in use nor against the budget, and all are freed before a request fails.
+class DeviceAllocator;
+// hipMalloc and hipFree for the pool of one context.
+struct DeviceMem {
+  DeviceAllocator* owner;
+  bool get(size_t bytes, void** p) const;
+  void put(void* p) const;
+  void wait() const;
+  bool half_free() const;
+  void reclaim() const;
+};
+
+// hipMalloc / hipFree under an optional byte budget, with the scratch of finished calls kept (see
+// scratch_pool.h) up to a thirty-second of the device's memory: 9 GB of 288, which holds the Arnoldi
+// space of a 12-atom density matrix.
 class DeviceAllocator : public Allocator {
  public:
-  explicit DeviceAllocator(size_t budget, size_t device_bytes = 0)
-      : budget_(budget), keep_max_(device_bytes / 8) {}
+  DeviceAllocator(int device, size_t budget, size_t device_bytes);
   ~DeviceAllocator() override;
-  int alloc(size_t bytes, void** p) override;
-  void release(void* p, size_t bytes, bool idle = false) override;
-  size_t in_use() const override;
-  void trim();  // frees every kept block
+  DeviceAllocator(const DeviceAllocator&) = delete;
+  int alloc(size_t bytes, void** p) override { return status(pool_.alloc(bytes, p), bytes); }
+  void release(void* p, size_t bytes) override { pool_.release(p, bytes); }
+  int borrow(size_t bytes, void** p) override { return status(pool_.borrow(bytes, p), bytes); }
+  void give_back(void* p, size_t bytes, bool idle) override { pool_.give_back(p, bytes, idle); }
+  size_t in_use() const override { return pool_.in_use(); }
+  size_t trim() { return pool_.trim(); }  // frees every kept block, returns their bytes
+  // Trims every context's pool on the device but `except`.
+  static void trim_device(int device, const DeviceAllocator* except);
+  int device() const { return device_; }
   // pinned host scalars (kPinnedDoubles) of one call
   double* pinned_take();
   void pinned_give(double* h);
 
  private:
-  struct Kept {
-    void* p;
-    size_t size;
-  };
-  size_t budget_, in_use_ = 0, keep_max_ = 0, kept_bytes_ = 0;
-  std::vector<Kept> kept_;  // oldest first
-  std::vector<double*> pinned_;
-  mutable std::mutex mu_;
+  int status(ScratchPool<DeviceMem>::Status st, size_t bytes) const;
+  const int device_;
+  const size_t budget_;
+  ScratchPool<DeviceMem> pool_;
+  static constexpr int kKeepPinned = 16;
+  double* pinned_[kKeepPinned];
+  int n_pinned_ = 0;
+  std::mutex mu_;  // of pinned_
+  DeviceAllocator *next_ = nullptr, *prev_ = nullptr;  // the process's allocators
 };
 constexpr int kPinnedDoubles = 64;
 
@@ -83,7 +100,7 @@ class ArenaAllocator : public Allocator {
   ~ArenaAllocator() override;
   int init(size_t bytes);
   int alloc(size_t bytes, void** p) override;  // RSV_ENOMEM when no gap is large enough
-  void release(void* p, size_t bytes, bool idle = false) override;
+  void release(void* p, size_t bytes) override;
   size_t in_use() const override;
   size_t capacity() const { return ff_.size(); }
 

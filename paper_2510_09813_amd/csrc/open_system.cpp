@@ -58,12 +58,12 @@ struct Block {
   Block(Allocator* al, hipStream_t st) : a(al), s(st) {}
   int get(size_t b) {
     bytes = b;
-    return a->alloc(b, &p);
+    return a->borrow(b, &p);
   }
   ~Block() {
     if (p) {
       const bool idle = hipStreamSynchronize(s) == hipSuccess;
-      a->release(p, bytes, idle);
+      a->give_back(p, bytes, idle);
     }
   }
 };

@@ -52,7 +52,7 @@ class BumpAllocator : public Allocator {
     used_ += bytes;
     return RSV_OK;
   }
-  void release(void*, size_t, bool) override {}
+  void release(void*, size_t) override {}
   size_t in_use() const override { return used_; }
 
  private:
@@ -718,7 +718,7 @@ int rsv_server_create(rsv_ctx* ctx, const rsv_server_opts* opts, rsv_server** ou
     return fail(RSV_EINVAL, "pack_max_atoms must be in 0..%d", kMaxPackBits);
   if (opts->pack_max_jobs < 0) return fail(RSV_EINVAL, "pack_max_jobs must be >= 0");
   HIP_TRY(hipSetDevice(ctx->device));
-  ctx->dev->trim();  // kept scratch blocks make room for the arena
+  DeviceAllocator::trim_device(ctx->device, nullptr);  // kept scratch makes room for the arena
   size_t bytes = opts->arena_bytes;
   if (bytes == 0) {
     size_t free_b = 0, total_b = 0;

@@ -24,6 +24,7 @@ PRECISIONS = {"c128": RSV_C128, "c64": RSV_C64}
 # Every symbol include/rsv.h declares; the CPU test suite checks that the library exports them.
 EXPORTED = [
     "rsv_version", "rsv_last_error", "rsv_ctx_create", "rsv_ctx_destroy", "rsv_ctx_bytes_in_use",
+    "rsv_ctx_trim",
     "rsv_register_create", "rsv_register_destroy", "rsv_register_diagonal", "rsv_workspace_bytes",
     "rsv_apply_hamiltonian", "rsv_evolve_device", "rsv_evolve", "rsv_result_state",
     "rsv_result_occupations", "rsv_result_sample", "rsv_result_stats", "rsv_result_destroy",
@@ -88,6 +89,7 @@ def lib():
         "rsv_ctx_create": (i32, [i32, sz, C.POINTER(vp)]),
         "rsv_ctx_destroy": (None, [vp]),
         "rsv_ctx_bytes_in_use": (sz, [vp]),
+        "rsv_ctx_trim": (sz, [vp]),
         "rsv_register_create": (i32, [vp, i32, pd, dbl, i32, C.POINTER(vp)]),
         "rsv_register_destroy": (None, [vp]),
         "rsv_register_diagonal": (i32, [vp, vp, vp]),
@@ -247,6 +249,11 @@ def rsv_ctx_destroy(ctx):
 
 def rsv_ctx_bytes_in_use(ctx) -> int:
     return int(lib().rsv_ctx_bytes_in_use(ctx))
+
+
+def rsv_ctx_trim(ctx) -> int:
+    """Gives the device scratch kept from finished calls back; returns its bytes."""
+    return int(lib().rsv_ctx_trim(ctx))
 
 
 def rsv_register_create(ctx, xyz, c6: float, precision="c128") -> Register:
