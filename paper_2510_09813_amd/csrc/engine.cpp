@@ -685,8 +685,7 @@ static bool small_route(const rsv_register* reg, double tau, double max_drive, d
          packed_resolves(tau, 0.5 * (reg->u_abs + max_detuning + max_drive));
 }
 
-// Steps [0, count) of values mid(j, dst) -> the n_steps x sites values of omega, delta (and phi)
-// of steps j.., in launches of as many steps as the kernel arguments hold.
+// `count` steps in launches of as many as the kernel arguments hold.
 struct SmallRun {
   rsv_register* reg;
   double tau, tol, dir;
@@ -694,9 +693,10 @@ struct SmallRun {
   bool with_phi;  // direct: whether any coupling has an imaginary part
 };
 
-static int run_small(const SmallRun& r, const double* om, const double* de, const double* ph,
-                     int64_t stride, int64_t count, void* d_psi, double* obs, int64_t obs_every,
-                     hipStream_t s, rsv_stats* st, double* norm2) {
+// values(k, c, dst): omega, delta (and phi) of steps k..k+c-1, sites x c values each, to dst.
+template <class Values>
+static int run_small(const SmallRun& r, const Values& values, int64_t count, void* d_psi, double* obs,
+                     int64_t obs_every, hipStream_t s, rsv_stats* st, double* norm2) {
   rsv_register* reg = r.reg;
   RSV_TRY(workspace_acquire(reg, r.kmax));
   Workspace& ws = reg->ws;
@@ -725,12 +725,7 @@ static int run_small(const SmallRun& r, const double* om, const double* de, cons
   double mid[kMidValues];
   for (int64_t k = 0; k < count; k += per) {
     const int64_t c = std::min(per, count - k);
-    double* dst = mid;
-    for (const double* x : {om, de, ph}) {
-      if (!x) continue;
-      for (int64_t i = 0; i < sites; ++i, dst += c)
-        std::memcpy(dst, x + i * stride + k, (size_t)c * sizeof(double));
-    }
+    values(k, c, mid);
     jb.n_steps = c;
     jb.resume = k > 0;
     jb.obs_first = k;
@@ -757,7 +752,8 @@ static int run_small(const SmallRun& r, const double* om, const double* de, cons
   return RSV_OK;
 }
 
-// evolve on one workgroup.  *taken = 0: the call takes the host driver.
+// evolve on one workgroup.  *taken = false: the call takes the host driver.  (Allocates nothing on
+// the host, whatever the number of steps.)
 static int evolve_small(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o,
                         int64_t first, int64_t count, void* d_psi, double* obs_dev, int obs_every,
                         hipStream_t s, rsv_stats* st, double* norm2, bool* taken) {
@@ -766,32 +762,34 @@ static int evolve_small(rsv_register* reg, const rsv_pulses* pl, const rsv_evolv
   const int64_t rows = pl->per_site ? n : 1;
   *taken = false;
   if (count < 1 || o->reorth || n > packed_max_atoms(reg->prec)) return RSV_OK;
-  std::vector<double> v((size_t)3 * rows * count);
-  double* om = v.data();
-  double* de = om + rows * count;
-  double* ph = de + rows * count;
-  for (int64_t i = 0; i < rows; ++i) {
-    const int64_t src = i * pl->n_samples;
-    step_midpoints(pl->omega + src, first, count, o->dt_ns, om + i * count);
-    step_midpoints(pl->delta + src, first, count, o->dt_ns, de + i * count);
-    if (pl->phi) step_midpoints(pl->phi + src, first, count, o->dt_ns, ph + i * count);
-  }
+  // the widest step, 64 at a time
   double drive = 0.0, detuning = 0.0;
-  for (int64_t k = 0; k < count; ++k) {
-    double a = 0.0, d = 0.0;
+  for (int64_t k = 0; k < count; k += 64) {
+    const int64_t c = std::min<int64_t>(64, count - k);
+    double a[64] = {}, d[64] = {}, x[64];
     for (int64_t i = 0; i < rows; ++i) {
-      a += std::fabs(om[i * count + k]);
-      d += std::fabs(de[i * count + k]);
+      step_midpoints(pl->omega + i * pl->n_samples, first + k, c, o->dt_ns, x);
+      for (int64_t j = 0; j < c; ++j) a[j] += std::fabs(x[j]);
+      step_midpoints(pl->delta + i * pl->n_samples, first + k, c, o->dt_ns, x);
+      for (int64_t j = 0; j < c; ++j) d[j] += std::fabs(x[j]);
     }
-    drive = std::max(drive, a * (double)(n / rows));
-    detuning = std::max(detuning, d * (double)(n / rows));
+    for (int64_t j = 0; j < c; ++j) {
+      drive = std::max(drive, a[j] * (double)(n / rows));
+      detuning = std::max(detuning, d[j] * (double)(n / rows));
+    }
   }
   if (!small_route(reg, tau, drive, detuning)) return RSV_OK;
   *taken = true;
   const SmallRun r{reg, tau, o->tol, 1.0, o->kmax, o->max_substep_depth, pl->per_site, 0,
                    pl->phi != nullptr};
-  return run_small(r, om, de, pl->phi ? ph : nullptr, count, count, d_psi, obs_dev, obs_every, s, st,
-                   norm2);
+  const auto values = [&](int64_t k, int64_t c, double* dst) {
+    for (const double* x : {pl->omega, pl->delta, pl->phi}) {
+      if (!x) continue;
+      for (int64_t i = 0; i < rows; ++i, dst += c)
+        step_midpoints(x + i * pl->n_samples, first + k, c, o->dt_ns, dst);
+    }
+  };
+  return run_small(r, values, count, d_psi, obs_dev, obs_every, s, st, norm2);
 }
 
 int evolve(rsv_register* reg, const rsv_pulses* pl, const rsv_evolve_opts* o, void* d_psi,
@@ -883,7 +881,10 @@ int krylov_exp(rsv_register* reg, const StepCoef& c, double tau, double dir, dou
     const bool phi = c.mode != kCoefReal;
     const SmallRun r{reg, tau, tol, dir < 0 ? -1.0 : 1.0, kmax, max_depth, sites > 1 ? 1 : 0, 1, phi};
     double norm2 = 1.0;
-    const int rc = run_small(r, v, v + sites, phi ? v + 2 * sites : nullptr, 1, 1, d_psi, nullptr, 1, s, st, &norm2);
+    const auto values = [&](int64_t, int64_t, double* dst) {
+      std::memcpy(dst, v, (size_t)sites * (phi ? 3 : 2) * sizeof(double));
+    };
+    const int rc = run_small(r, values, 1, d_psi, nullptr, 1, s, st, &norm2);
     return norm2 == 0.0 ? RSV_OK : rc;  // exp(...) 0 = 0
   }
   RSV_TRY(workspace_acquire(reg, kmax));
