@@ -34,6 +34,8 @@
 // kCoefReal (shared and phi = 0: one real coupling, the cheapest form) and kCoefSite.
 //
 // No MFMA: the operator has no dense contraction.
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace rsv {
@@ -673,24 +675,39 @@ void launch_lo_ext(int ext, const StepCoef& c, const PassArgs<R>& p, int n, hipS
   }
 }
 
+template <class R, int CM, int LB, int E, bool PLANNED = true>
+hipError_t launch_lo_small(const StepCoef& c, const PassArgs<R>& p, int n, hipStream_t s) {
+  if constexpr (!PLANNED) return hipErrorInvalidValue;
+  else launch_lo<R, LB, CM, E>(c, p, n, s);
+  return hipSuccess;
+}
+
+// Extensions are planned on 12-bit tiles, complex64's 13-bit ones, and sweep_plan's smaller ones of 13
+// to 18 atoms, which differ by precision.
 template <class R, int CM>
-void launch_lo_any(int lb, int ext, const StepCoef& c, const PassArgs<R>& p, int n, hipStream_t s) {
-  if (ext > 0) {  // extensions are planned on 12-bit tiles, complex64's 13-bit ones, and sweep_plan's
-    switch (8 * lb + ext) {  // sweep_plan's of 13..18 atoms
-      case 8 * 9 + 4: return launch_lo<R, 9, CM, 4>(c, p, n, s);
-      case 8 * 9 + 5: return launch_lo<R, 9, CM, 5>(c, p, n, s);
-      case 8 * 9 + 6: return launch_lo<R, 9, CM, 6>(c, p, n, s);
-      case 8 * 10 + 5: return launch_lo<R, 10, CM, 5>(c, p, n, s);
-      case 8 * 10 + 6: return launch_lo<R, 10, CM, 6>(c, p, n, s);
-      case 8 * 10 + 7: return launch_lo<R, 10, CM, 7>(c, p, n, s);
-      case 8 * 11 + 6: return launch_lo<R, 11, CM, 6>(c, p, n, s);
-      case 8 * 11 + 7: return launch_lo<R, 11, CM, 7>(c, p, n, s);
+hipError_t launch_lo_any(int lb, int ext, const StepCoef& c, const PassArgs<R>& p, int n, hipStream_t s) {
+  if (ext > 0) {
+    constexpr bool kWide = sizeof(R) == 8;
+    switch (8 * lb + ext) {
+      case 8 * 9 + 4: return launch_lo_small<R, CM, 9, 4>(c, p, n, s);
+      case 8 * 9 + 5: return launch_lo_small<R, CM, 9, 5>(c, p, n, s);
+      case 8 * 9 + 6: return launch_lo_small<R, CM, 9, 6, kWide>(c, p, n, s);
+      case 8 * 10 + 5: return launch_lo_small<R, CM, 10, 5, !kWide>(c, p, n, s);
+      case 8 * 10 + 6: return launch_lo_small<R, CM, 10, 6>(c, p, n, s);
+      case 8 * 10 + 7: return launch_lo_small<R, CM, 10, 7, kWide>(c, p, n, s);
+      case 8 * 11 + 6: return launch_lo_small<R, CM, 11, 6, !kWide>(c, p, n, s);
+      case 8 * 11 + 7: return launch_lo_small<R, CM, 11, 7>(c, p, n, s);
       default: break;
     }
     if constexpr (Geo<R>::L >= 13) {
-      if (lb == 13) return launch_lo_ext<R, CM, 13>(ext, c, p, n, s);
+      if (lb == 13) {
+        launch_lo_ext<R, CM, 13>(ext, c, p, n, s);
+        return hipSuccess;
+      }
     }
-    return launch_lo_ext<R, CM, 12>(ext, c, p, n, s);
+    if (lb != 12) return hipErrorInvalidValue;
+    launch_lo_ext<R, CM, 12>(ext, c, p, n, s);
+    return hipSuccess;
   }
   switch (lb) {
     case 8: launch_lo<R, 8, CM>(c, p, n, s); break;
@@ -699,9 +716,15 @@ void launch_lo_any(int lb, int ext, const StepCoef& c, const PassArgs<R>& p, int
     case 11: launch_lo<R, 11, CM>(c, p, n, s); break;
     case 12: launch_lo<R, 12, CM>(c, p, n, s); break;
     default:
-      if constexpr (Geo<R>::L >= 13) launch_lo<R, 13, CM>(c, p, n, s);
-      break;
+      if constexpr (Geo<R>::L >= 13) {
+        if (lb == 13) {
+          launch_lo<R, 13, CM>(c, p, n, s);
+          break;
+        }
+      }
+      return hipErrorInvalidValue;
   }
+  return hipSuccess;
 }
 
 template <class R, int CM, int HB, int RL>
@@ -825,7 +848,8 @@ hipError_t sweep_t(int n, const StepCoef& c, const double* dtab, const SweepIn& 
   if (plan.lo_ext > 0 && (p.x1 || p.x2 || p.a0 != 1.0 || p.dot || p.nrm1 || p.u_out || p.part_norm))
     return hipErrorInvalidValue;
   p.ext_bit = plan.lo_ext_bit - plan.lo_bits;
-  launch_lo_any<R, CM>(plan.lo_bits, plan.lo_ext, c, p, n, s);
+  const hipError_t e = launch_lo_any<R, CM>(plan.lo_bits, plan.lo_ext, c, p, n, s);
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 
