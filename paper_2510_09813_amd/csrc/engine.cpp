@@ -445,7 +445,7 @@ int reorthogonalise(Lanczos& L, int k, double* b2) {
     d.g = std::min(kDotGroup, k - l0);
     for (int g = 0; g < d.g; ++g) d.x[g] = ws.basis[l0 + g];
     HIP_TRY(multi_dot(prec, n, d, ws.basis[k], ws.pnorm, L.s));
-    HIP_TRY(finalize_rows(ws.pnorm, nw, 2 * d.g, ws.dscal + kDotSlot + 2 * l0, L.s));
+    HIP_TRY(finalize_rows(ws.pnorm, dot_num_partials(n), 2 * d.g, ws.dscal + kDotSlot + 2 * l0, L.s));
   }
   double dots[2 * kMaxKrylov];
   RSV_TRY(fetch_scalars(L, kDotSlot, 2 * k, dots));

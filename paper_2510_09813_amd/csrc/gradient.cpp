@@ -202,7 +202,7 @@ int rsv_gradient_occupations(rsv_register* reg, const rsv_pulses* pl, const rsv_
       d.g = 1;
       d.x[0] = lam;
       HIP_TRY(multi_dot(prec, n, d, aug, part, s));
-      HIP_TRY(finalize_rows(part, vec_num_partials(prec, n), 1, res, s));
+      HIP_TRY(finalize_rows(part, dot_num_partials(n), 1, res, s));
       HIP_TRY(hipMemcpyAsync(reg->h_scal, res, sizeof(double), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
       const double g = 2.0 * reg->h_scal[0];

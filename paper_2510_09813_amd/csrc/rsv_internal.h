@@ -141,7 +141,9 @@ hipError_t finalize_sum(const double* partial, int64_t count, double* dst, hipSt
 // dst[r] = sum of partial[r * count .. (r + 1) * count) for r < rows, the same fixed order.
 hipError_t finalize_rows(const double* partial, int64_t count, int rows, double* dst,
                          hipStream_t s);
-// Partials of Re and Im <x_g, y>: partial[(2 g + c) * vec_num_partials + w], c = 0 re, 1 im.
+// Partials of Re and Im <x_g, y>: partial[(2 g + c) * dot_num_partials(n) + w], c = 0 re, 1 im
+// (dot_num_partials is at most vec_num_partials).
+int64_t dot_num_partials(int n);
 hipError_t multi_dot(int prec, int n, const DotGroup& d, const void* y, double* partial,
                      hipStream_t s);
 // Precision conversion for state import/export: complex128 <-> storage precision.

@@ -165,7 +165,7 @@ int verify_fp64(rsv_server* srv, Job* job, const void* d_psi64,
   d.g = 1;
   d.x[0] = d_psi;
   HIP_TRY(multi_dot(kC128, n, d, wide, part, stream));
-  HIP_TRY(finalize_rows(part, nw, 2, res, stream));
+  HIP_TRY(finalize_rows(part, dot_num_partials(n), 2, res, stream));
   HIP_TRY(norm2_partial(kC128, n, d_psi, part, stream));
   HIP_TRY(finalize_sum(part, nw, res + 2, stream));
   HIP_TRY(norm2_partial(kC128, n, wide, part, stream));

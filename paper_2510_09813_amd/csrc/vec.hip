@@ -10,9 +10,19 @@
 namespace rsv {
 namespace {
 
-// One element per thread up to 2048 workgroups, then a grid-stride loop (with eight per thread the
-// combination of 30 vectors of 2^20 amplitudes ran on 512 workgroups: 99 us).
+// One element per thread up to 2048 workgroups, then a grid-stride loop.  Eight per thread leave most
+// of the chip idle below 2^18 elements (the combination of about 25 vectors complex128, eight / one
+// per thread: 15.9 / 4.9 us at 2^14, 28 / 7.8 at 2^16, 16.4 / 10.8 at 2^17); above, both stream
+// alike (20.1 / 20.6 at 2^18, 95 / 96 at 2^20, 222 / 222 at 2^21).
 constexpr int kPerThread = 1;
+// The inner products end in a block reduction of 16 values per workgroup, so they take fewer: one
+// element per thread up to 1024 workgroups, more only where each has eight per thread.  Eight
+// vectors complex128, 2048 workgroups / this: 26.5 / 18.8 us at 2^19, 36.2 / 28.7 at 2^20, 64.8 / 52.6
+// at 2^21 (eight per thread throughout: 15.7 at 2^16, where this takes 9.1).
+uint32_t dot_grid(size_t count) {
+  const uint32_t one = stream_grid(count, 1), eight = stream_grid(count, 8);
+  return one <= 1024 ? one : eight > 1024 ? eight : 1024;
+}
 // loop bits of the fused occupation sums: at most n - 19 (30 atoms, 2048 workgroups)
 constexpr int kOccLoopBits = 11;
 constexpr int kOccCombSlots = 1 + 8 + kOccLoopBits;
@@ -232,6 +242,8 @@ int64_t vec_num_partials(int prec, int n) {
   return stream_grid(size_t(1) << n, kPerThread);
 }
 
+int64_t dot_num_partials(int n) { return dot_grid(size_t(1) << n); }
+
 hipError_t krylov_combine(int prec, int n, const CombineCoef& c, void* out, double* partial,
                           hipStream_t s) {
   const size_t count = size_t(1) << n;
@@ -293,7 +305,7 @@ hipError_t finalize_rows(const double* partial, int64_t count, int rows, double*
 hipError_t multi_dot(int prec, int n, const DotGroup& d, const void* y, double* partial,
                      hipStream_t s) {
   const size_t count = size_t(1) << n;
-  const uint32_t g = stream_grid(count, kPerThread);
+  const uint32_t g = dot_grid(count);
   if (prec == kC128)
     hipLaunchKernelGGL(multi_dot_kernel<double>, dim3(g), dim3(kBlock), 0, s, d,
                        (const double2*)y, partial, count);
