@@ -258,10 +258,10 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t s) {
 __device__ __forceinline__ uint32_t padded(uint32_t e) { return e + (e >> 4); }
 constexpr int kPaddedChunk = (1 << kChunkBits) + (1 << (kChunkBits - 4));
 
-// Exclusive prefix of tsum[0..255] on top of `run`, in thread order (thread 0; 16 values at a
+// Exclusive prefix of tsum[0..count) on top of `run`, in thread order (thread 0; 16 values at a
 // time through registers, so that the adds do not wait for the LDS); returns the end.
-__device__ __forceinline__ double serial_scan(double* tsum, double run) {
-  for (int t0 = 0; t0 < kBlock; t0 += 16) {
+__device__ __forceinline__ double serial_scan(double* tsum, double run, int count = kBlock) {
+  for (int t0 = 0; t0 < count; t0 += 16) {
     double v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) v[j] = tsum[t0 + j];
@@ -343,7 +343,13 @@ __global__ __launch_bounds__(kBlock) void block_scan_kernel(const double* __rest
   }
 }
 
-template <class R>
+// One workgroup per shot.  STAGED: the chunk's probabilities reach their threads through LDS (as in
+// block_prob_kernel).  A state of up to 2^kDirectBits amplitudes, one chunk, is read as it is: its few
+// lines stay in the caches, and without the staging's 35 KB and the search more than four workgroups
+// share a CU: 200 000 shots of 3 / 11 atoms 0.49 / 1.06 ms, staged 1.58 / 1.88 (12 atoms staged 2.05,
+// as it is 2.3).
+constexpr int kDirectBits = 11;
+template <class R, bool STAGED>
 __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict__ x,
                                                         const int cbits, const int64_t nb,
                                                         const double* __restrict__ pre,
@@ -351,7 +357,7 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
                                                         const uint64_t seed,
                                                         uint64_t* __restrict__ idx) {
   __shared__ double tsum[kBlock];
-  __shared__ double pr[kPaddedChunk];
+  __shared__ double pr[STAGED ? kPaddedChunk : 1];
   __shared__ int64_t blk_sh;
   __shared__ int fallback_sh;
   __shared__ unsigned int cand, last_sh, hit;
@@ -363,6 +369,7 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
   // each round tests 256 spaced candidates of the open range and keeps the gap below the first
   // that does (one memory latency per factor of 256 where a bisection takes eight)
   int64_t lo = 0, hi = nb;  // answer in [lo, hi]; hi == nb means none
+  if constexpr (!STAGED) lo = hi = pre[1] > target ? 0 : 1;  // a short chunk is the only one
   while (lo < hi) {
     if (tid == 0) hit = kBlock;
     __syncthreads();
@@ -397,22 +404,27 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
   __syncthreads();
   const int64_t blk = blk_sh;
   const size_t base = (size_t)blk << cbits;
+  if constexpr (STAGED) {
 #pragma unroll
-  for (uint32_t j = 0; j < 16; ++j) {
-    const uint32_t e = tid + kBlock * j;
-    pr[padded(e)] = e < chunk ? prob<R>(x[base + e]) : 0.0;
+    for (uint32_t j = 0; j < 16; ++j) {
+      const uint32_t e = tid + kBlock * j;
+      pr[padded(e)] = e < chunk ? prob<R>(x[base + e]) : 0.0;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   double p[16];
   double own = 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
-    p[j] = pr[padded(tid * 16 + j)];
+    const uint32_t e = tid * 16 + j;
+    if constexpr (STAGED) p[j] = pr[padded(e)];
+    else p[j] = e < chunk ? prob<R>(x[base + e]) : 0.0;
     own += p[j];
   }
   tsum[tid] = own;
   __syncthreads();
-  if (tid == 0) serial_scan(tsum, pre[blk]);
+  // (threads beyond a short chunk hold no probability and need no prefix)
+  if (tid == 0) serial_scan(tsum, pre[blk], STAGED ? kBlock : (int)((chunk + 15) / 16));
   __syncthreads();
   if (!fallback_sh) {
     double c = tsum[tid];
@@ -438,6 +450,17 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(const Cx<R>* __restrict_
     return;
   }
   if (tid == 0) idx[blockIdx.x] = (uint64_t)base + found;
+}
+
+template <class R>
+void launch_samples(const void* x, int cbits, int64_t nb, const double* pre, const double* bsum,
+                    uint64_t seed, int64_t shots, uint64_t* idx, hipStream_t s) {
+  if (cbits > kDirectBits)
+    hipLaunchKernelGGL((sample_kernel<R, true>), dim3((uint32_t)shots), dim3(kBlock), 0, s,
+                       (const Cx<R>*)x, cbits, nb, pre, bsum, seed, idx);
+  else
+    hipLaunchKernelGGL((sample_kernel<R, false>), dim3((uint32_t)shots), dim3(kBlock), 0, s,
+                       (const Cx<R>*)x, cbits, nb, pre, bsum, seed, idx);
 }
 
 // Scratch of the allocation-free sampling entry point: the block sums and their exclusive
@@ -522,12 +545,8 @@ hipError_t sample(int prec, int n, const void* x, uint64_t seed, int shots, doub
                        (const float2*)x, cbits, bsum);
   hipLaunchKernelGGL(block_scan_kernel, dim3(1), dim3(kBlock), 0, s, bsum, nb, pre);
   if (shots > 0) {
-    if (prec == kC128)
-      hipLaunchKernelGGL(sample_kernel<double>, dim3((uint32_t)shots), dim3(kBlock), 0, s,
-                         (const double2*)x, cbits, nb, pre, bsum, seed, idx);
-    else
-      hipLaunchKernelGGL(sample_kernel<float>, dim3((uint32_t)shots), dim3(kBlock), 0, s,
-                         (const float2*)x, cbits, nb, pre, bsum, seed, idx);
+    if (prec == kC128) launch_samples<double>(x, cbits, nb, pre, bsum, seed, shots, idx, s);
+    else launch_samples<float>(x, cbits, nb, pre, bsum, seed, shots, idx, s);
   }
   return hipGetLastError();
 }
