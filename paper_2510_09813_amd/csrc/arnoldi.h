@@ -64,7 +64,8 @@ struct ArnoldiSpace {
   size_t vb = 0;
   double* part = nullptr;   // partial inner products
   double* npart = nullptr;  // partials of the newest norm
-  double* dscal = nullptr;  // kMaxKrylov + 2 norms, the second pass's inner products, the columns
+  double* dscal = nullptr;  // the norms, the Hessenberg diagonal, the second pass's inner products
+                            // (kMaxKrylov + 2 of each), then the columns
   double* h_scal = nullptr;  // pinned host copy of dscal
   int herm = 0;              // the vectors are Hermitian 2^herm x 2^herm matrices and op keeps them so
   bool shift = false;        // the operator's diagonal in the basis is far from zero (-i H)

@@ -4,8 +4,9 @@
 // matrix.  The detuning part of the diagonal changes every step and is added on the fly by
 // the H|psi> kernels from the bit pattern, so only the interaction part is stored.
 //
-// diag_build writes the whole diagonal (for callers that want E itself, and for the packed
-// small-job path); the H|psi> passes use the much smaller tables of diag_tables_build.
+// diag_build writes the whole diagonal (for callers that want E itself, and for the Lindblad and
+// gradient operators); the H|psi> passes use the much smaller tables of diag_tables_build, and the
+// kernel of small registers forms its own.
 //
 // A workgroup owns 2^C amplitudes with equal high bits (C = min(n, 12)).  In LDS it keeps
 // the bit-indexed U, the energy of the high bits alone and, per low bit p, the coupling

@@ -45,8 +45,8 @@ int packed_max_atoms(int prec);
 // half-width of H_k's spectrum (rad/us).
 bool packed_resolves(double tau, double half_width);
 
-// Jobs of a batch in device memory; their sizes choose the launch (host array n of their atom
-// counts, which must be grouped: small jobs, n <= kPackSmallBits, first).
+// Jobs of a batch in device memory, the n_small of up to kPackSmallBits atoms first, then the n_large
+// others: one launch each, on their own streams.
 constexpr int kPackSmallBits = 10;
 hipError_t packed_evolve(int prec, const PackedJob* d_jobs, int n_small, int n_large,
                          hipStream_t s_small, hipStream_t s_large);

@@ -6,8 +6,9 @@
 // (at most 64 x 64), so the active block is kept as a dense matrix and every rotation
 // updates only the rows and columns it touches inside the band.  With T = Q diag(l) Q^T:
 //   y = Q exp(-i tau diag(l)) Q^T e_1,  y_j = sum_k Q[j][k] exp(-i tau l_k) Q[0][k].
-// The convergence test needs only y_{m-1}, i.e. rows 0 and m-1 of Q: the "last" variant
-// accumulates just those two rows, O(m) per rotation less work.
+// The Lanczos driver takes y from tridiag_expm_series; the eigenvectors serve spectra too wide for it
+// and the public call.  tridiag_expm_last (rows 0 and m-1 of Q only) is kept as a check of both: it
+// gives |y_{m-1}| by another path.
 #include <cfloat>
 #include <cmath>
 
