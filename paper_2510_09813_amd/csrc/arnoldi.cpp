@@ -82,8 +82,8 @@ struct Run {
 };
 
 // x <- exp(sub Op) x for the largest sub <= tau found that kmax vectors resolve.
-int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol, int max_depth,
-              hipStream_t s, rsv_stats* st, double* sub) {
+int expm_part(const OpFn& op, ArnoldiSpace& sp, ArnoldiSpace::Last& last, void* d_x, double tau, double tol,
+              int max_depth, hipStream_t s, rsv_stats* st, double* sub) {
   const int kmax = sp.kmax;
   const size_t count = size_t(1) << sp.nb;
   Run run{op, sp, d_x, s, st, count, count <= (size_t(1) << kSmallBits), arnoldi_parts(count)};
@@ -97,11 +97,18 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
   const double log2_tol = std::log2(tol);
   KrylovCourse course;
   double nx = 0.0;
-  int next = KrylovCourse::first(sp.hint, !run.small);
-  int m = 0;            // columns gone through
-  bool careful = false;  // a second pass was needed: go on one iteration at a time
+  // What is queued behind a vector that needs a second pass is computed again.  The same columns need
+  // one step after step (the gradients' second, whose diagonal entry is far from the first's; every
+  // one under strong dissipation), so a queue ends with the next column that did in the comparable
+  // run before.  After a surprise it goes on, after a second one a column at a time.
+  const int hint = last.dim, first = KrylovCourse::first(hint, !run.small);
+  const uint64_t expected = last.again;
+  last.again = 0;
+  int surprises = 0;
+  int m = 0;  // columns gone through
+  int next = first;
   auto finish = [&](int dim, double part) -> int {
-    sp.hint = dim;
+    last.dim = dim;
     st->krylov_max = std::max<int64_t>(st->krylov_max, dim);
     CombineCoef cc;
     std::memset(&cc, 0, sizeof cc);
@@ -117,7 +124,10 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
     return RSV_OK;
   };
   for (;;) {
-    const int upto = std::min(kmax, m + std::max(1, careful ? 1 : next));
+    if (surprises > 1) next = 1;
+    int upto = std::min(kmax, m + std::max(1, next));
+    for (int j = m; j < upto; ++j)
+      if ((expected >> j) & 1u) upto = j + 1;
     for (int j = m; j < upto; ++j) RSV_TRY(run.iterate(j));
     RSV_TRY(run.fetch(upto));
     if (m == 0) {
@@ -150,7 +160,9 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
         // the first pass removed most of the vector (|y'| < |y1| / sqrt(2), the criterion of
         // Daniel, Gragg, Kaufman and Stewart, 1976): rounding in what is left is no longer small
         // against it, so orthogonalise it once more
-        again = careful = true;
+        again = true;
+        last.again |= uint64_t(1) << j;
+        surprises += !((expected >> j) & 1u);
         RSV_TRY(run.orthogonalise(j, true));
         RSV_TRY(run.fetch(j + 1));
         for (int i = 0; i <= j; ++i) {
@@ -196,7 +208,7 @@ int expm_part(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double to
       }
       if (again) break;  // what was queued after this vector used its first form
     }
-    next = course.ahead(log2_tol, kmax - m);
+    next = hint > 0 && m < first ? first - m : course.ahead(log2_tol, kmax - m);
   }
 }
 
@@ -247,9 +259,11 @@ void arnoldi_carve(void* block, double* h_scal, int prec, int nb, int kmax, Arno
 int arnoldi_expm(const OpFn& op, ArnoldiSpace& sp, void* d_x, double tau, double tol,
                  int max_depth, hipStream_t s, rsv_stats* st) {
   if (sp.kmax < 2 || sp.kmax > kMaxKrylov - 1) return fail(RSV_EINVAL, "kmax must be in 2..%d", kMaxKrylov - 1);
+  int part = 0;
   for (double remaining = tau; remaining > 0.0;) {
     double sub = 0.0;
-    RSV_TRY(expm_part(op, sp, d_x, remaining, tol, max_depth, s, st, &sub));
+    RSV_TRY(expm_part(op, sp, sp.last[part], d_x, remaining, tol, max_depth, s, st, &sub));
+    part = std::min(part + 1, ArnoldiSpace::kParts - 1);
     remaining = sub >= remaining ? 0.0 : remaining - sub;
   }
   return RSV_OK;

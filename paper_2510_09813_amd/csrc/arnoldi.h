@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <complex>
+#include <cstdint>
 #include <functional>
 #include <vector>
 
@@ -69,7 +70,14 @@ struct ArnoldiSpace {
   double* h_scal = nullptr;  // pinned host copy of dscal
   int herm = 0;              // the vectors are Hermitian 2^herm x 2^herm matrices and op keeps them so
   bool shift = false;        // the operator's diagonal in the basis is far from zero (-i H)
-  int hint = 0;              // dimension of the previous run: how many iterations to queue first
+  // of the step before, by sub-step: its dimension (how many iterations to queue first) and the columns
+  // that needed a second Gram-Schmidt pass
+  struct Last {
+    int dim = 0;
+    uint64_t again = 0;
+  };
+  static constexpr int kParts = 8;
+  Last last[kParts];
 };
 size_t arnoldi_device_bytes(int prec, int nb, int kmax);
 // Lays out the device block (arnoldi_device_bytes); h_scal: arnoldi_host_doubles() pinned doubles.
