@@ -404,9 +404,9 @@ __global__ __launch_bounds__(NT, (lo_min_waves<R, LB, NT, CM, E>())) void hpsi_l
   for (int s = 0; s < A; ++s) tile[lo_pos<TB, VB>(tid, s)] = v[s];
   // An extended pass stores nothing here and returns no norm; the compiler lets the branch decide
   // which loads are issued together.  Complex64 without it: 160 registers instead of 135, still three
-  // workgroups per CU, and with it H psi of 22 to 25 atoms took 4 to 10 % longer (a low pass of 24
-  // atoms 97 us, now 89), per-site of 24 to 26 atoms 10 %.  Complex128 with it: 126 registers,
-  // without it 128 and spills, and per-site of 23 to 28 atoms takes 8 to 14 % longer.
+  // workgroups per CU; with it H psi of 22 to 25 atoms took 4 to 10 % longer (a low pass of 24 atoms
+  // 97 us, now 88), per-site of 24 to 26 atoms 6 to 12 %.  Complex128 with it: 126 registers, without
+  // it 128 and spills, and per-site of 23 to 28 atoms takes 8 to 15 % longer.
   if constexpr (E == 0 || sizeof(R) == 8) {
     if (p.u_out) {
 #pragma unroll
